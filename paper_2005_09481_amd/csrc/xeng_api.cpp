@@ -43,11 +43,13 @@ hipError_t launch_correlate_dma(const KernelArgs &a, int grid, int waves, hipStr
 hipError_t launch_correlate_dma_unsigned(const KernelArgs &a, int grid, bool fp8, hipStream_t stream);
 hipError_t launch_correlate_narrow(const KernelArgs &a, int grid, hipStream_t stream);
 hipError_t init_dma_kernel();
-hipError_t launch_dump(int32_t *acc, int32_t *diag, int n, int nt, int32_t *out, bool reset,
-                       hipStream_t stream);
-hipError_t launch_dump_batch(const DumpDesc *d_jobs, int n_jobs, int n_max, int nt_max, hipStream_t stream);
-hipError_t launch_dump_corr(int32_t *acc, int32_t *diag, int n, int nt, int32_t *out, bool reset,
-                            const int32_t *sums, int n4, int64_t t, int32_t *other, hipStream_t stream);
+hipError_t launch_dump(const DumpDesc &jd, hipStream_t stream);
+hipError_t launch_dump_batch(const DumpDesc *d_jobs, const int32_t *d_job_of, int tiles, int64_t total_tiles,
+                             hipStream_t stream);
+hipError_t launch_dump_corr(const DumpDesc &jd, const int32_t *sums, int n4, int64_t t, int32_t *other,
+                            hipStream_t stream);
+hipError_t launch_clear_slot(int32_t *acc, int64_t n_i32, int32_t *bias, int32_t *base, int64_t n_bias, int64_t *count,
+                             hipStream_t stream);
 hipError_t launch_zero(int32_t *p, int64_t n_i32, hipStream_t stream);
 hipError_t launch_pad_rows(const uint8_t *src, int64_t stride, int n, int64_t rows, int n16, uint8_t *dst,
                            hipStream_t stream);
@@ -537,8 +539,13 @@ struct xeng_ctx {
     uint32_t flags = 0;
     int32_t nt = 0;
     int64_t slot_i32 = 0;
-    int32_t *d_acc = nullptr;    // n_slots accumulators, then n_slots diagonal stagings
-    int32_t *d_diag = nullptr;
+    int32_t *d_acc = nullptr;    // n_slots accumulators, then n_slots bias arrays
+    int32_t *d_bias = nullptr;   // per slot bias_i32(N): see JobDesc::bias
+    // per slot two buffers of bias_i32(N) (after the pre-sums): the biases
+    // as of the slot's last reset in the current one; a resetting export
+    // reads it and stores the present biases to the other
+    int32_t *d_base = nullptr;
+    std::vector<uint8_t> base_cur;
     int64_t *d_count = nullptr;  // per slot: samples integrated, kept on the device for prepared batches
     int32_t *d_counts = nullptr; // XENG_COUNTS: per slot, int32 [count_i32]: samples per pair from flagged calls
     int64_t count_i32 = 0;       // N(N+1)/2 rounded up to a multiple of 4
@@ -598,6 +605,15 @@ hipError_t reset_counts(xeng_ctx *c, int32_t slot, hipStream_t stream)
     return launch_zero(c->d_counts + (int64_t)slot * c->count_i32, c->count_i32, stream);
 }
 
+// The host's side of a resetting export of a slot (which cleared its
+// accumulators and, on a bound slot, its device counter).
+hipError_t after_reset_export(xeng_ctx *c, int32_t slot, hipStream_t stream)
+{
+    c->acc_t[(size_t)slot] = 0;
+    c->base_cur[(size_t)slot] ^= 1;
+    return reset_counts(c, slot, stream);
+}
+
 // After an eager call changed a bound slot's count: the new value goes to
 // the device counter in stream order.
 hipError_t publish_count(xeng_ctx *c, int32_t slot, hipStream_t stream)
@@ -625,7 +641,31 @@ JobDesc make_job(const xeng_ctx *c, int32_t slot, const uint8_t *d_samples, int6
     if (may_store && c->acc_t[(size_t)slot] == 0 && c->bound[(size_t)slot] == 0) jd.flags |= JOB_FRESH;
     jd.pad = 0;
     jd.presum = nullptr;
+    jd.bias = c->d_bias + (int64_t)slot * bias_i32(c->n);
     return jd;
+}
+
+// Buffer `which` (0, 1) of the slot's bases.
+int32_t *base_buf(const xeng_ctx *c, int32_t slot, int which)
+{
+    return c->d_base + ((int64_t)slot * 2 + which) * bias_i32(c->n);
+}
+
+DumpDesc make_dump(const xeng_ctx *c, int32_t slot, int32_t *out, bool reset)
+{
+    DumpDesc d;
+    const int cur = c->base_cur[(size_t)slot];
+    d.acc = c->d_acc + (int64_t)slot * c->slot_i32;
+    d.out = out;
+    d.bias = c->d_bias + (int64_t)slot * bias_i32(c->n);
+    d.base = base_buf(c, slot, cur);
+    d.base_next = base_buf(c, slot, 1 - cur);
+    d.count = c->bound[(size_t)slot] > 0 ? c->d_count + slot : nullptr;
+    d.n = c->n;
+    d.nt = c->nt;
+    d.reset = reset ? 1 : 0;
+    d.first_tile = 0;
+    return d;
 }
 
 // Kernel choice for one job: the general kernel where the tuning asks for
@@ -1075,7 +1115,7 @@ int create_ctx(const xeng_config *cfg, hipStream_t stream, xeng_ctx **out)
         cfg->device < 0 || (cfg->flags & ~(XENG_NIBBLE_RE_LOW | XENG_COUNTS)) || cfg->mem_budget_bytes < 0)
         return XENG_EINVAL;
     const int64_t count_i32 = (cfg->flags & XENG_COUNTS) ? (tri64(cfg->n_inputs) + 3) / 4 * 4 : 0;
-    const int64_t slot_bytes = (slot_i32(cfg->n_inputs) + diag_i32(cfg->n_inputs) + count_i32) * 4;
+    const int64_t slot_bytes = (slot_i32(cfg->n_inputs) + bias_i32(cfg->n_inputs) + count_i32) * 4;
     if (slot_bytes > INT64_MAX / cfg->n_slots) return XENG_ENOMEM;
     const int64_t bytes = slot_bytes * cfg->n_slots;
     if (cfg->mem_budget_bytes > 0 && bytes > cfg->mem_budget_bytes) return XENG_ENOMEM;
@@ -1102,6 +1142,7 @@ int create_ctx(const xeng_config *cfg, hipStream_t stream, xeng_ctx **out)
     c->flagged_t.assign((size_t)cfg->n_slots, 0);
     c->psum_t.assign((size_t)cfg->n_slots, 0);
     c->psum_cur.assign((size_t)cfg->n_slots, 0);
+    c->base_cur.assign((size_t)cfg->n_slots, 0);
     c->bound.assign((size_t)cfg->n_slots, 0);
     c->count_i32 = count_i32;
     c->st = st;
@@ -1117,15 +1158,18 @@ int create_ctx(const xeng_config *cfg, hipStream_t stream, xeng_ctx **out)
         delete c;
         return map_err(e);
     }
-    const int64_t psum_i32 = (int64_t)cfg->n_slots * 4 * (((int64_t)cfg->n_inputs + 3) / 4 * 4);
+    // per slot two pre-sum buffers, then per slot two bases of its biases
+    const int64_t sums_i32 = (int64_t)cfg->n_slots * 4 * (((int64_t)cfg->n_inputs + 3) / 4 * 4);
+    const int64_t psum_i32 = sums_i32 + (int64_t)cfg->n_slots * 2 * bias_i32(cfg->n_inputs);
     if ((e = hipMalloc(&c->d_psum, (size_t)psum_i32 * 4)) != hipSuccess) {
         (void)hipFree(c->d_acc);
         (void)hipFree(c->d_count);
         delete c;
         return map_err(e);
     }
-    c->d_diag = c->d_acc + (int64_t)cfg->n_slots * c->slot_i32;
-    if (count_i32) c->d_counts = c->d_diag + (int64_t)cfg->n_slots * diag_i32(cfg->n_inputs);
+    c->d_bias = c->d_acc + (int64_t)cfg->n_slots * c->slot_i32;
+    c->d_base = c->d_psum + sums_i32;
+    if (count_i32) c->d_counts = c->d_bias + (int64_t)cfg->n_slots * bias_i32(cfg->n_inputs);
     e = launch_zero(c->d_acc, bytes / 4, stream);
     if (e == hipSuccess) e = launch_zero(c->d_psum, psum_i32, stream);
     if (stream) {
@@ -1407,13 +1451,11 @@ int xeng_dump(xeng_ctx *ctx, int32_t slot, int32_t *out, int32_t reset, void *hi
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int rc = refuse_capture(stream);
     if (rc != XENG_OK) return rc;
-    int32_t *acc = ctx->d_acc + (int64_t)slot * ctx->slot_i32;
-    int32_t *diag = ctx->d_diag + (int64_t)slot * diag_i32(ctx->n);
     hipError_t e = hipSuccess;
     if (reset && ctx->psum_t[(size_t)slot] > 0) {
         // the pending correction inside the export itself
         const int cur = ctx->psum_cur[(size_t)slot];
-        e = launch_dump_corr(acc, diag, ctx->n, ctx->nt, out, true, psum_buf(ctx, slot, cur), (int)psum_n4(ctx),
+        e = launch_dump_corr(make_dump(ctx, slot, out, true), psum_buf(ctx, slot, cur), (int)psum_n4(ctx),
                              ctx->psum_t[(size_t)slot], psum_buf(ctx, slot, 1 - cur), stream);
         if (e == hipSuccess) {
             ctx->psum_cur[(size_t)slot] = (uint8_t)(1 - cur);
@@ -1421,15 +1463,10 @@ int xeng_dump(xeng_ctx *ctx, int32_t slot, int32_t *out, int32_t reset, void *hi
         }
     } else {
         e = settle_presum(ctx, slot, stream);
-        if (e == hipSuccess) e = launch_dump(acc, diag, ctx->n, ctx->nt, out, reset != 0, stream);
+        if (e == hipSuccess) e = launch_dump(make_dump(ctx, slot, out, reset != 0), stream);
     }
     if (e != hipSuccess) return map_err(e);
-    if (reset) {
-        ctx->acc_t[(size_t)slot] = 0;
-        if ((e = reset_counts(ctx, slot, stream)) != hipSuccess) return map_err(e);
-        return map_err(publish_count(ctx, slot, stream));
-    }
-    return XENG_OK;
+    return reset ? map_err(after_reset_export(ctx, slot, stream)) : XENG_OK;
 }
 
 int xeng_dump_batch(const xeng_dump_job *jobs, int32_t n_jobs, void *hip_stream)
@@ -1445,14 +1482,7 @@ int xeng_dump_batch(const xeng_dump_job *jobs, int32_t n_jobs, void *hip_stream)
         if (!slot_ok(j.ctx, j.slot) || !j.out || (j.reset != 0 && j.reset != 1) || j.reserved != 0 ||
             j.ctx->device != device || !seen.insert({j.ctx, j.slot}).second)
             return XENG_EINVAL;
-        DumpDesc &d = descs[(size_t)k];
-        d.acc = j.ctx->d_acc + (int64_t)j.slot * j.ctx->slot_i32;
-        d.diag = j.ctx->d_diag + (int64_t)j.slot * diag_i32(j.ctx->n);
-        d.out = j.out;
-        d.n = j.ctx->n;
-        d.nt = j.ctx->nt;
-        d.reset = j.reset;
-        d.pad = 0;
+        descs[(size_t)k] = make_dump(j.ctx, j.slot, j.out, j.reset != 0);
     }
     DeviceGuard guard(device);
     if (!guard.ok) return XENG_EDEVICE;
@@ -1465,33 +1495,43 @@ int xeng_dump_batch(const xeng_dump_job *jobs, int32_t n_jobs, void *hip_stream)
         const hipError_t e = settle_presum(jobs[k].ctx, jobs[k].slot, stream);
         if (e != hipSuccess) return map_err(e);
     }
-    constexpr int32_t CHUNK = 65535;   // grid z limit
-    for (int32_t k0 = 0; k0 < n_jobs; k0 += CHUNK) {
-        const int32_t m = std::min(CHUNK, n_jobs - k0);
-        int n_max = 0, nt_max = 0;
-        for (int32_t k = k0; k < k0 + m; ++k) {
-            n_max = std::max(n_max, (int)descs[(size_t)k].n);
-            nt_max = std::max(nt_max, (int)descs[(size_t)k].nt);
+    for (int32_t k0 = 0; k0 < n_jobs;) {
+        // as many jobs as one launch's grid takes
+        int64_t total = 0;
+        int32_t m = 0;
+        bool same = true;
+        for (; k0 + m < n_jobs; ++m) {
+            DumpDesc &d = descs[(size_t)(k0 + m)];
+            const int64_t tiles = tri64(d.nt);
+            if (m > 0 && total + tiles > DUMP_MAX_TILES) break;
+            d.first_tile = (int32_t)total;
+            total += tiles;
+            same = same && d.nt == descs[(size_t)k0].nt;
         }
-        const size_t bytes = (size_t)m * sizeof(DumpDesc);
+        // [descriptors | the job of every tile, where their tiles differ]
+        const size_t b_desc = (size_t)m * sizeof(DumpDesc), b_tab = same ? 0 : (size_t)total * sizeof(int32_t);
         JobTable *tb = nullptr;
-        int rc = ring_acquire(st, bytes, &tb);
+        int rc = ring_acquire(st, b_desc + b_tab, &tb);
         if (rc != XENG_OK) return rc;
-        std::memcpy(tb->h, descs.data() + k0, bytes);
-        hipError_t e = hipMemcpyAsync(tb->d, tb->h, bytes, hipMemcpyHostToDevice, stream);
+        std::memcpy(tb->h, descs.data() + k0, b_desc);
+        if (!same) {
+            int32_t *tab = reinterpret_cast<int32_t *>(tb->h + b_desc);
+            for (int32_t k = 0; k < m; ++k) tab = std::fill_n(tab, tri64(descs[(size_t)(k0 + k)].nt), k);
+        }
+        hipError_t e = hipMemcpyAsync(tb->d, tb->h, b_desc + b_tab, hipMemcpyHostToDevice, stream);
         if (e == hipSuccess)
-            e = launch_dump_batch(reinterpret_cast<const DumpDesc *>(tb->d), m, n_max, nt_max, stream);
+            e = launch_dump_batch(reinterpret_cast<const DumpDesc *>(tb->d),
+                                  same ? nullptr : reinterpret_cast<const int32_t *>(tb->d + b_desc),
+                                  (int)tri64(descs[(size_t)k0].nt), total, stream);
         if (e == hipSuccess) e = hipEventRecord(tb->ev, stream);
         if (e != hipSuccess) return map_err(e);
         tb->pending = true;
+        // (a chunk's slots are reset as its launch is queued)
+        for (int32_t k = k0; k < k0 + m; ++k)
+            if (jobs[k].reset && (e = after_reset_export(jobs[k].ctx, jobs[k].slot, stream)) != hipSuccess)
+                return map_err(e);
+        k0 += m;
     }
-    for (int32_t k = 0; k < n_jobs; ++k)
-        if (jobs[k].reset) {
-            jobs[k].ctx->acc_t[(size_t)jobs[k].slot] = 0;
-            hipError_t e = reset_counts(jobs[k].ctx, jobs[k].slot, stream);
-            if (e == hipSuccess) e = publish_count(jobs[k].ctx, jobs[k].slot, stream);
-            if (e != hipSuccess) return map_err(e);
-        }
     return XENG_OK;
 }
 
@@ -1503,12 +1543,15 @@ int xeng_reset(xeng_ctx *ctx, int32_t slot, void *hip_stream)
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int rc = refuse_capture(stream);
     if (rc != XENG_OK) return rc;
-    hipError_t e = launch_zero(ctx->d_acc + (int64_t)slot * ctx->slot_i32, ctx->slot_i32, stream);
+    hipError_t e = launch_clear_slot(ctx->d_acc + (int64_t)slot * ctx->slot_i32, ctx->slot_i32,
+                                     ctx->d_bias + (int64_t)slot * bias_i32(ctx->n), base_buf(ctx, slot, 0),
+                                     bias_i32(ctx->n), ctx->bound[(size_t)slot] > 0 ? ctx->d_count + slot : nullptr,
+                                     stream);
     if (e == hipSuccess) e = settle_presum(ctx, slot, stream, true);
     if (e == hipSuccess) e = reset_counts(ctx, slot, stream);
     if (e != hipSuccess) return map_err(e);
     ctx->acc_t[(size_t)slot] = 0;
-    return map_err(publish_count(ctx, slot, stream));
+    return XENG_OK;
 }
 
 int64_t xeng_samples_integrated(const xeng_ctx *ctx, int32_t slot)
@@ -1528,7 +1571,7 @@ int64_t xeng_max_integration(void) { return T_MAX; }
 int64_t xeng_slot_bytes(int32_t n_inputs)
 {
     if (n_inputs < 1) return -1;
-    return (slot_i32(n_inputs) + diag_i32(n_inputs)) * 4;
+    return (slot_i32(n_inputs) + bias_i32(n_inputs)) * 4;
 }
 
 int32_t xeng_n_inputs(const xeng_ctx *ctx) { return ctx ? ctx->n : -1; }
@@ -1836,6 +1879,7 @@ int xeng_autotune(const xeng_job *jobs, int32_t n_jobs, int32_t iters, void *hip
     if (e != hipSuccess) return map_err(e);
     for (size_t k = 0; k < jl.descs.size(); ++k) {
         jl.descs[k].acc = scratch + off[k];
+        jl.descs[k].bias = nullptr;
         jl.descs[k].flags &= ~JOB_FRESH;
     }
 

@@ -49,8 +49,9 @@ inline int64_t tri64(int64_t n) { return n * (n + 1) / 2; }
 __host__ __device__ inline int n_tiles_side_hd(int n) { return (n + TILE - 1) / TILE; }
 inline int n_tiles_side(int n) { return (n + TILE - 1) / TILE; }
 inline int64_t slot_i32(int n) { return tri64(n_tiles_side(n)) * TILE_I32; }
-// Per-slot staging of the diagonal's imaginary parts for the dump.
-inline int64_t diag_i32(int n) { return ((int64_t)n + 63) / 64 * 64; }
+// Per-slot int32 per input, rounded up to 64: the imaginary biases the
+// signed int8 kernels add (see JobDesc::bias).
+inline int64_t bias_i32(int n) { return ((int64_t)n + 63) / 64 * 64; }
 
 // Register sums of one piece: the general kernel's B operands carry 16x the
 // sample values, so its sums reach 16 * 128 * length (pieces below 2^20
@@ -90,6 +91,14 @@ struct JobDesc {
     int32_t pad;
     int32_t *presum;          // optional: the slot's pre-sums ([SR | SI], N rounded up to 4 apart) for the
                               // wide kernel's FP8 instance of the unsigned form in a batch
+    // optional: the slot's imaginary biases.  The signed int8 kernels add
+    // Im V_ij - S_j with S_j = sum_t Im x_j(t) to every pair (i, j); the
+    // wave that holds pair (j, j) -- whose Im V is 0, so its sum is -S_j --
+    // also adds it to bias[j], which is only ever added to: an export
+    // subtracts what has come in since the slot's last reset (bias[j] -
+    // base[j], in wrapping int32 arithmetic) and a resetting one takes the
+    // present values as the next base.
+    int32_t *bias;
 };
 constexpr uint32_t JOB_RE_LOW = 1u;    // real part in the low nibble
 constexpr uint32_t JOB_ALIGNED8 = 2u;   // samples, stride and N are multiples of 8 bytes
@@ -131,16 +140,48 @@ struct GuardJob {
 };
 constexpr int ZERO_BYTES = 256;
 
-// One export of a batched dump: a slot's accumulators, its diagonal staging
-// (n int32) and the caller's output, [n(n+1)/2][2] int32.
+// One export: a slot's accumulators and biases (see JobDesc::bias; base as
+// of the slot's last reset) and the caller's output, [n(n+1)/2][2] int32.
+// A resetting export zeroes the words it exports, stores the present biases
+// to base_next and, for a slot of a live prepared batch, zeroes the slot's
+// device sample counter.
 struct DumpDesc {
     int32_t *acc;
-    int32_t *diag;
     int32_t *out;
+    const int32_t *bias;
+    const int32_t *base;
+    int32_t *base_next;
+    int64_t *count;      // null: no device counter to clear
     int32_t n;
     int32_t nt;
     int32_t reset;
-    int32_t pad;
+    int32_t first_tile;  // batched exports: tiles of the jobs before this one
 };
+
+// Most tiles one batched export launch takes (N of 65535 alone has 131328).
+constexpr int64_t DUMP_MAX_TILES = INT64_C(1) << 24;
+
+// Tile (ti, tj) of linear index t over the upper triangle of nt x nt tiles,
+// row by row: t = ti nt - ti (ti - 1) / 2 + (tj - ti).  The float square
+// root may be off by one either way, which the integer steps mend.
+__device__ inline void tile_of(int t, int nt, int &ti, int &tj)
+{
+    const float b = 2.0f * (float)nt + 1.0f;
+    int r = (int)((b - sqrtf(fmaxf(b * b - 8.0f * (float)t, 0.0f))) * 0.5f);
+    r = r < 0 ? 0 : (r > nt - 1 ? nt - 1 : r);
+    while (r > 0 && r * nt - r * (r - 1) / 2 > t) --r;
+    while (r + 1 < nt && (r + 1) * nt - (r + 1) * r / 2 <= t) ++r;
+    ti = r;
+    tj = r + t - (r * nt - r * (r - 1) / 2);
+}
+
+// Register of a 32 x 32 MFMA accumulator block in which this lane holds a
+// diagonal pair (row = column), or -1: column j = lane % 32 and row j sit in
+// register 4 (j / 8) + j % 4 of lane j + 32 ((j / 4) % 2).
+__device__ inline int diag_reg(int lane)
+{
+    const int j = lane & 31;
+    return ((j >> 2) & 1) == (lane >> 5) ? 4 * (j >> 3) + (j & 3) : -1;
+}
 
 }  // namespace xeng

@@ -23,8 +23,8 @@
 // packed sample by one XOR and one AND (no sign extension), and ~R never
 // overflows int8 where -R would (R = -8).  The imaginary accumulator thus
 // holds Im V_ij - S_j with S_j = sum_t I_j(t); since Im V_jj = 0 its diagonal
-// holds -S_j, and the dump subtracts it.  The general kernel stores the same
-// form.
+// holds -S_j, which the waves on the diagonal also add to the slot's biases
+// for the export to subtract.  The general kernel stores the same form.
 //
 // Workgroup tile: 128 rows (A) x 256 columns (B), NW waves in two rows of
 // NW / 2; wave (wa, wb) computes rows 64wa..64wa+63 against 256 / (NW / 2)
@@ -685,6 +685,33 @@ __device__ __forceinline__ void flush_atomic(gw64 *blk, const V &re, const V &im
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The diagonal's stored imaginary parts (-S_j, see the top) of one wave's
+// blocks on the diagonal of tile (ti, ti) into the slot's biases: one lane
+// per input, whichever register holds its pair (j, j).
+template <int NW, int SHIFT>
+__device__ __forceinline__ void add_bias(int32_t *bias, const Acc<NW, false> &acc, int n, int ti, int wa, int cb0,
+                                         int lane)
+{
+    const int dr = diag_reg(lane);
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        int32_t v = 0;
+        if constexpr (Layout<NW>::BW == 2) {
+            // a 64 x 64 region: its diagonal blocks are (0, 0) and (1, 1)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v = dr == r ? acc.im[a][a][r] : v;
+        } else {
+#pragma unroll
+            for (int b = 0; b < Layout<NW>::BW; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v = (cb0 + b == 2 * wa + a && dr == r) ? acc.im[a][b][r] : v;
+        }
+        const int j = WA_ROWS * ti + 64 * wa + 32 * a + (lane & 31);
+        if (dr >= 0 && j < n)
+            __hip_atomic_fetch_add(bias + j, acc_val<SHIFT>(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 // Whole-tile flush of one wave's 2 x BW blocks (column blocks cb0..): stores
 // if the slot holds zeros, else read-modify-write with the loads of a row of
 // blocks issued together (one memory latency per row, not one per value).
@@ -746,15 +773,22 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
     const int p_begin = args.wg_off[blockIdx.x], p_end = args.wg_off[blockIdx.x + 1];
     for (int pi = p_begin; pi < p_end; ++pi) {
         const Piece pce = args.pieces[pi];
-        const JobDesc jd = args.jobs ? args.jobs[pce.job] : args.job0;
-        const int ti = pce.tile & 0xFFFF, tj2 = (pce.tile >> 16) & 0xFFFF;
-        const bool atomic = pce.t1_atomic < 0;
+        JobDesc jd = args.jobs ? args.jobs[pce.job] : args.job0;
         // every field is wave-uniform: keep them in scalar registers
+        jd.acc = uniform(jd.acc);
+        jd.bias = uniform(jd.bias);
+        jd.presum = uniform(jd.presum);
+        jd.n = __builtin_amdgcn_readfirstlane(jd.n);
+        jd.nt = __builtin_amdgcn_readfirstlane(jd.nt);
+        jd.flags = (uint32_t)__builtin_amdgcn_readfirstlane((int)jd.flags);
+        const int tile = __builtin_amdgcn_readfirstlane(pce.tile);
+        const int ti = tile & 0xFFFF, tj2 = (tile >> 16) & 0xFFFF;
+        const bool atomic = __builtin_amdgcn_readfirstlane(pce.t1_atomic) < 0;
         Tile tl;
         tl.samples = uniform(jd.samples);
         tl.zeros = uniform(args.zeros);
         tl.stride = uniform(jd.stride);
-        tl.n = __builtin_amdgcn_readfirstlane(jd.n);
+        tl.n = jd.n;
         tl.row0 = __builtin_amdgcn_readfirstlane(ti * WA_ROWS);
         tl.col0 = __builtin_amdgcn_readfirstlane(tj2 * WB_COLS);
         tl.t0 = __builtin_amdgcn_readfirstlane(pce.t0);
@@ -845,6 +879,10 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
             // the sums carry 256x the values (both operands 16x), or 8x in
             // the unsigned form (the FP8 form's scale is undone in acc_val)
             constexpr int SHIFT = U ? 3 : 8;
+            // the unsigned form carries no bias
+            if constexpr (!U)
+                if (tj == ti && (L::BW == 4 || diag) && jd.bias != nullptr)
+                    add_bias<NW, SHIFT>(jd.bias, acc, jd.n, ti, wa, cb0, lane);
             const int64_t tile_idx = (int64_t)ti * jd.nt - (int64_t)ti * (ti - 1) / 2 + (tj - ti);
             gw64 *tb = (gw64 *)(jd.acc + tile_idx * TILE_I32) + lane;
             if (atomic) {

@@ -15,8 +15,9 @@
 // vectors per sample group (Re, Im, ~Re) and the column (B) side two (Re,
 // Im); one B operand feeds both products.  The stored imaginary part is
 // Im V_ij - S_j with S_j = sum_t Im x_j(t); as Im V_jj = 0, the diagonal
-// holds -S_j and the dump adds it back.  Every partial sum is an exact
-// int32.  The DMA kernel stores the same form.
+// holds -S_j, which also goes to the slot's biases, and the dump adds S_j
+// back.  Every partial sum is an exact int32.  The DMA kernel stores the same
+// form.
 //
 // Data path per 32-sample stage (double-buffered in LDS):
 //   global (time-major bytes) -> dword loads, 4 inputs x 8 samples per lane
@@ -519,6 +520,21 @@ __global__ __launch_bounds__(256, 2) void xcorr_mfma(KernelArgs args)
         constexpr int SHIFT = FP8 ? 0 : UNSIGNED ? 3 : 4;
         const int64_t tile_idx = (int64_t)ti * jd.nt - (int64_t)ti * (ti - 1) / 2 + (tj - ti);
         gw64 *tb = (gw64 *)(jd.acc + tile_idx * TILE_I32) + lane;
+        // the diagonal's imaginary sums are the slot's biases (the FP8 and
+        // unsigned instances carry none)
+        if constexpr (!UNSIGNED && !FP8)
+            if (ti == tj && wa == wb && jd.bias != nullptr) {
+                const int dr = diag_reg(lane);
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    int32_t v = 0;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v = dr == r ? acc.im[a][a][r] : v;
+                    const int j = TILE * ti + 64 * wa + BLK * a + (lane & 31);
+                    if (dr >= 0 && j < jd.n)
+                        __hip_atomic_fetch_add(jd.bias + j, v >> SHIFT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
         if (atomic) {
 #pragma unroll
             for (int a = 0; a < 2; ++a)
@@ -534,166 +550,151 @@ __global__ __launch_bounds__(256, 2) void xcorr_mfma(KernelArgs args)
     }
 }
 
-// Word of pair (i <= j) in a slot's tile layout.
-__device__ __forceinline__ int64_t acc_word(int i, int j, int nt)
-{
-    const int ti = i >> 7, tj = j >> 7;
-    const int ri = i & 127, rj = j & 127;
-    const int ca = ri >> 5, ra = ri & 31, cb = rj >> 5, lb = rj & 31;
-    const int reg = 4 * (ra >> 3) + (ra & 3);
-    const int ln = lb + 32 * ((ra >> 2) & 1);
-    const int64_t tile = (int64_t)ti * nt - (int64_t)ti * (ti - 1) / 2 + (tj - ti);
-    return tile * TILE_W + (ca * BLKS + cb) * BLOCK_W + reg * 64 + ln;
-}
-
-// Stored imaginary parts of the diagonal, d[j] = -S_j (see the operand
-// note at the top), staged before the tiles are exported and zeroed.
-__global__ __launch_bounds__(256) void diag_im(const int32_t *__restrict__ acc, int n, int nt,
-                                               int32_t *__restrict__ d)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j < n) d[j] = pair_im(reinterpret_cast<const uint64_t *>(acc)[acc_word(j, j, nt)]);
-}
-
-// Accumulators (tile layout) -> packed row-major upper triangle of (Re, Im),
-// optionally zeroing the slot in the same pass.  A workgroup takes DUMP_ROWS
-// rows of one 32-row block row of tile (ti, tj): blockIdx.y = ti and
-// blockIdx.x = (tj - ti) * DUMP_PARTS_PER_TILE + ca * DUMP_PARTS + part.
-// Reads: row r of the part is 64 threads, thread c taking the 16 bytes of
-// columns 32 (c / 16) + 2 (c % 16) .. + 1 (two consecutive words of one
-// accumulator register row, so a row is read as four coalesced 256-byte
-// runs), staged in LDS as (Re, Im) pairs.  Writes: consecutive threads take
-// consecutive pairs of an output row, 128 pairs (1 KB contiguous) per row.
-// Few rows per workgroup keep many small workgroups in flight: the export
-// is a single pass over memory, and this form measured twice as fast as
-// 32-row workgroups.  The imaginary part of (i, j) is stored as Im V_ij -
-// S_j, so d[j] is subtracted (exact in wrapping int32 arithmetic, since
-// Im V_ij itself fits).
-constexpr int DUMP_PITCH = TILE + 1;   // int2 per staged row (padding spreads banks)
-constexpr int DUMP_ROWS = 4;
-constexpr int DUMP_PARTS = BLK / DUMP_ROWS;
-constexpr int DUMP_PARTS_PER_TILE = 4 * DUMP_PARTS;   // workgroups per tile
+// Export of a slot: accumulators (tile layout) -> packed row-major upper
+// triangle of (Re, Im), optionally clearing the slot in the same pass.
+// Bound by memory: 8 bytes read and written per exported pair, and 8 more
+// written where it clears.
+//
+// A workgroup takes DUMP_ROWS rows x 128 columns of a tile, a wave one row
+// at a time: lane c takes the two consecutive words of columns
+// 32 (c / 16) + 2 (c % 16) .. + 1, so a row is read as four coalesced
+// 256-byte runs, and writes its two pairs straight to the output row, 1 KB
+// contiguous per wave (16-byte stores at 8-byte alignment).  Rows r and
+// r + 4 of an 8-row group lie next to each other in the accumulators; every
+// load of a thread is issued before its first store.  Pairs of
+// inputs at or past n and 32 x 32 blocks below the diagonal are neither read
+// nor cleared: whatever their words hold is never exported.  The imaginary
+// part of (i, j) is stored as Im V_ij - S_j, so bias[j] - base[j] = -S_j is
+// subtracted (exact in wrapping int32 arithmetic, since Im V_ij itself fits).
+//
+// Measured: N = 2048 with reset 9.8 us = 5.4 TB/s (4 rows per workgroup 9.4,
+// 16 9.8, 32 10.4); as two kernels, the diagonal gathered first, 4.8 + 9.1.
+// 1024 slots of N = 64 in one launch 27 us (4 rows 36, 16 24), where reading
+// and clearing every tile whole took 44 us + 4.5 for the diagonals; 64
+// sub-arrays of N 256 to 2048 136 us, where a grid sized for the largest
+// job's tiles took 202.
+constexpr int DUMP_ROWS = 8;
+constexpr int DUMP_WAVES = 4;
+constexpr int DUMP_PARTS = TILE / DUMP_ROWS;   // workgroups per tile
 
 // A pending unsigned-form correction (CORR; see presum_correct): per
 // input, SR at sums[i] and SI at sums[n4 + i] over the t samples that form
-// contributed.  It is added to each staged word in the packed 64-bit form,
-// before the word is split into (Re, Im): the uncorrected real part may have
-// passed the int32 range, which the split would carry into Im.
+// contributed.  It is added to each word in the packed 64-bit form, before
+// the word is split into (Re, Im): the uncorrected real part may have passed
+// the int32 range, which the split would carry into Im.  `other` (the
+// slot's second pre-sum buffer, 2 n4 int32, which the next calls of that
+// form will use) is cleared on the way.
 struct PendingCorr {
     const int32_t *sums;
+    int32_t *other;
     int n4;
     int64_t t;
 };
-__device__ __forceinline__ uint64_t corr_word(const PendingCorr &pc, int n, int i, int j)
+__device__ __forceinline__ uint64_t corr_word(int64_t ri, int64_t ii, int64_t rj, int64_t ij, int64_t t)
 {
-    const int64_t ri = i < n ? pc.sums[i] : 0, ii = i < n ? pc.sums[pc.n4 + i] : 0;
-    const int64_t rj = j < n ? pc.sums[j] : 0, ij = j < n ? pc.sums[pc.n4 + j] : 0;
-    const int64_t d_re = -8 * (ri + ii + rj + ij) + 128 * pc.t;
+    const int64_t d_re = -8 * (ri + ii + rj + ij) + 128 * t;
     const int64_t d_im = 8 * (ri - ii) - 8 * (rj - ij);
     return ((uint64_t)d_im << 32) + (uint64_t)d_re;
 }
 
-template <bool CORR = false>
-__device__ __forceinline__ void dump_block_row(int32_t *__restrict__ acc, int n, int nt,
-                                               const int32_t *__restrict__ d, int32_t *__restrict__ out,
-                                               int reset, int bx, int by, int2 *stage,
-                                               const PendingCorr &pc = PendingCorr{nullptr, 0, 0})
+typedef int dv4i_u __attribute__((ext_vector_type(4), aligned(8)));
+
+// Part `part` of tile (ti, tj) of one export.
+template <bool CORR>
+__device__ __forceinline__ void dump_part(const DumpDesc &jd, int ti, int tj, int part, const PendingCorr &pc)
 {
-    const int ti = by;
-    const int tj = ti + bx / DUMP_PARTS_PER_TILE;
-    if (tj >= nt) return;
-    const int ca = (bx / DUMP_PARTS) & 3, part = bx % DUMP_PARTS;
-    const int t = threadIdx.x;
-    const int64_t tile = (int64_t)ti * nt - (int64_t)ti * (ti - 1) / 2 + (tj - ti);
-    {
-        const int ri = t >> 6, c = t & 63;
-        const int ra = DUMP_ROWS * part + ri;
-        const int cb = c >> 4, cj0 = 2 * (c & 15);
-        const int reg = 4 * (ra >> 3) + (ra & 3), half = (ra >> 2) & 1;
-        uint64_t *base = reinterpret_cast<uint64_t *>(acc) + tile * TILE_W + (ca * BLKS + cb) * BLOCK_W + reg * 64 +
-                         32 * half + cj0;
-        int4 *pw = reinterpret_cast<int4 *>(base);
-        const int4 w = *pw;
-        if (reset) *pw = make_int4(0, 0, 0, 0);
-        uint64_t w0 = (uint64_t)(uint32_t)w.x | ((uint64_t)(uint32_t)w.y << 32);
-        uint64_t w1 = (uint64_t)(uint32_t)w.z | ((uint64_t)(uint32_t)w.w << 32);
+    const int c = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = jd.n, nt = jd.nt;
+    const int i0 = TILE * ti + DUMP_ROWS * part;   // first row of the part
+    if (ti == tj && part == 0) {
+        // once per 128 inputs: the biases as of this reset, and the pre-sum
+        // buffer the slot's next calls use
+        const int j = TILE * ti + (int)threadIdx.x;
+        if (jd.reset && threadIdx.x < TILE && j < n) jd.base_next[j] = jd.bias[j];
         if constexpr (CORR) {
-            const int i = TILE * ti + BLK * ca + ra, j0 = TILE * tj + BLK * cb + cj0;
-            w0 += corr_word(pc, n, i, j0);
-            w1 += corr_word(pc, n, i, j0 + 1);
+            if (threadIdx.x < TILE && j < pc.n4) {
+                pc.other[j] = 0;
+                pc.other[pc.n4 + j] = 0;
+            }
         }
-        int2 *row = stage + ri * DUMP_PITCH + BLK * cb + cj0;
-        row[0] = make_int2(pair_re(w0), pair_im(w0));
-        row[1] = make_int2(pair_re(w1), pair_im(w1));
+        if (ti == 0 && threadIdx.x == 0 && jd.reset && jd.count != nullptr) *jd.count = 0;
     }
-    __syncthreads();
-    const int col = t & (TILE - 1);
-    const int j = TILE * tj + col;
-    if (j >= n) return;
-    const uint32_t dj = (uint32_t)d[j];
-    int2 *o = reinterpret_cast<int2 *>(out);
+    const int cb = c >> 4, cj0 = 2 * (c & 15);
+    const int j0 = TILE * tj + BLK * cb + cj0;
+    const int ca = (DUMP_ROWS * part) >> 5;        // block row
+    // column block below the diagonal, or past the last input
+    if (i0 >= n || j0 >= n || (ti == tj && cb < ca)) return;
+    const int64_t tile = (int64_t)ti * nt - (int64_t)ti * (ti - 1) / 2 + (tj - ti);
+    uint64_t *blk = reinterpret_cast<uint64_t *>(jd.acc) + tile * TILE_W + (ca * BLKS + cb) * BLOCK_W + cj0;
+    constexpr int PER = DUMP_ROWS / DUMP_WAVES;    // rows per wave
+    int4 w[PER];
+    int4 *pw[PER];
 #pragma unroll
-    for (int r = t >> 7; r < DUMP_ROWS; r += 2) {
-        const int i = TILE * ti + BLK * ca + DUMP_ROWS * part + r;
-        if (i >= n || j < i) continue;
-        const int64_t k = (int64_t)i * n - (int64_t)i * (i - 1) / 2 + (j - i);
-        const int2 v = stage[r * DUMP_PITCH + col];
-        o[k] = make_int2(v.x, (int32_t)((uint32_t)v.y - dj));
+    for (int k = 0; k < PER; ++k) {
+        const int ra = (DUMP_ROWS * part + wave + DUMP_WAVES * k) & (BLK - 1);   // row in the block
+        pw[k] = reinterpret_cast<int4 *>(blk + (4 * (ra >> 3) + (ra & 3)) * 64 + 32 * ((ra >> 2) & 1));
+        w[k] = *pw[k];
+    }
+    // the second column may lie past the last input: its bias is then that
+    // of the first, and its pair is not stored
+    const bool two = j0 + 1 < n;
+    const int j1 = two ? j0 + 1 : j0;
+    const uint32_t d0 = (uint32_t)jd.bias[j0] - (uint32_t)jd.base[j0];
+    const uint32_t d1 = (uint32_t)jd.bias[j1] - (uint32_t)jd.base[j1];
+    int64_t rj0 = 0, ij0 = 0, rj1 = 0, ij1 = 0;
+    if constexpr (CORR) {
+        rj0 = pc.sums[j0];
+        ij0 = pc.sums[pc.n4 + j0];
+        rj1 = pc.sums[j1];
+        ij1 = pc.sums[pc.n4 + j1];
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = i0 + wave + DUMP_WAVES * k;
+        if (i >= n) continue;
+        if (jd.reset) *pw[k] = make_int4(0, 0, 0, 0);
+        uint64_t w0 = (uint64_t)(uint32_t)w[k].x | ((uint64_t)(uint32_t)w[k].y << 32);
+        uint64_t w1 = (uint64_t)(uint32_t)w[k].z | ((uint64_t)(uint32_t)w[k].w << 32);
+        if constexpr (CORR) {
+            const int64_t ri = pc.sums[i], ii = pc.sums[pc.n4 + i];
+            w0 += corr_word(ri, ii, rj0, ij0, pc.t);
+            w1 += corr_word(ri, ii, rj1, ij1, pc.t);
+        }
+        const int a_re = pair_re(w0), a_im = (int32_t)((uint32_t)pair_im(w0) - d0);
+        const int b_re = pair_re(w1), b_im = (int32_t)((uint32_t)pair_im(w1) - d1);
+        int32_t *o = jd.out + 2 * ((int64_t)i * n - (int64_t)i * (i - 1) / 2 + (j0 - i));
+        if (j0 >= i && two)
+            *reinterpret_cast<dv4i_u *>(o) = dv4i_u{a_re, a_im, b_re, b_im};
+        else if (j0 >= i)
+            *reinterpret_cast<int2 *>(o) = make_int2(a_re, a_im);
+        else if (j0 + 1 >= i && two)
+            *reinterpret_cast<int2 *>(o + 2) = make_int2(b_re, b_im);
     }
 }
 
-__global__ __launch_bounds__(256) void vis_dump(int32_t *__restrict__ acc, int n, int nt,
-                                                const int32_t *__restrict__ d,
-                                                int32_t *__restrict__ out, int reset)
+// One slot's export: workgroup x is part x % DUMP_PARTS of tile
+// x / DUMP_PARTS of the triangle.
+template <bool CORR>
+__global__ __launch_bounds__(64 * DUMP_WAVES) void vis_dump(DumpDesc jd, PendingCorr pc)
 {
-    __shared__ int2 stage[DUMP_ROWS * DUMP_PITCH];
-    dump_block_row(acc, n, nt, d, out, reset, blockIdx.x, blockIdx.y, stage);
+    int ti, tj;
+    tile_of((int)(blockIdx.x / DUMP_PARTS), jd.nt, ti, tj);
+    dump_part<CORR>(jd, ti, tj, (int)(blockIdx.x % DUMP_PARTS), pc);
 }
 
-// The export of a slot with a pending unsigned-form correction: the
-// diagonal words corrected before d[j] is taken (their imaginary part gets
-// no correction, their real part may have wrapped), and `other` (the slot's
-// second pre-sum buffer, 2 n4 int32, which the next calls of that form will
-// use) cleared.  The unsigned form's contributions carry no imaginary bias,
-// so d[j] stays that of the signed calls alone.
-__global__ __launch_bounds__(256) void diag_im_corr(const int32_t *__restrict__ acc, int n, int nt,
-                                                    int32_t *__restrict__ d, PendingCorr pc,
-                                                    int32_t *__restrict__ other)
+// Batched export: the jobs' tiles one after another, tile g being tile
+// g - first_tile of its job.  The job of a tile comes from the table
+// `job_of` (one entry per tile), or, with no table, every job having
+// `tiles` of them, by division.
+__global__ __launch_bounds__(64 * DUMP_WAVES) void vis_dump_batch(const DumpDesc *__restrict__ jobs,
+                                                                  const int32_t *__restrict__ job_of, int tiles)
 {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j < n) {
-        const uint64_t w = reinterpret_cast<const uint64_t *>(acc)[acc_word(j, j, nt)];
-        d[j] = pair_im(w + corr_word(pc, n, j, j));
-    }
-    if (j < 2 * pc.n4) other[j] = 0;
-}
-
-__global__ __launch_bounds__(256) void vis_dump_corr(int32_t *__restrict__ acc, int n, int nt,
-                                                     const int32_t *__restrict__ d, int32_t *__restrict__ out,
-                                                     int reset, PendingCorr pc)
-{
-    __shared__ int2 stage[DUMP_ROWS * DUMP_PITCH];
-    dump_block_row<true>(acc, n, nt, d, out, reset, blockIdx.x, blockIdx.y, stage, pc);
-}
-
-// Batched export: job blockIdx.z of the descriptor table, the grid sized
-// for the largest job (workgroups past a smaller job's tiles return).  One
-// launch keeps enough block rows in flight to run at memory speed, where one
-// export per launch leaves most of the chip waiting on a single wave of
-// workgroups.
-__global__ __launch_bounds__(256) void diag_im_batch(const DumpDesc *__restrict__ jobs)
-{
-    const DumpDesc jd = jobs[blockIdx.y];
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j < jd.n) jd.diag[j] = pair_im(reinterpret_cast<const uint64_t *>(jd.acc)[acc_word(j, j, jd.nt)]);
-}
-
-__global__ __launch_bounds__(256) void vis_dump_batch(const DumpDesc *__restrict__ jobs)
-{
-    __shared__ int2 stage[DUMP_ROWS * DUMP_PITCH];
-    const DumpDesc jd = jobs[blockIdx.z];
-    if ((int)blockIdx.y >= jd.nt || (int)blockIdx.x >= DUMP_PARTS_PER_TILE * jd.nt) return;
-    dump_block_row(jd.acc, jd.n, jd.nt, jd.diag, jd.out, jd.reset, blockIdx.x, blockIdx.y, stage);
+    const int g = (int)(blockIdx.x / DUMP_PARTS);
+    const int k = __builtin_amdgcn_readfirstlane(job_of ? job_of[g] : g / tiles);
+    const DumpDesc jd = jobs[k];
+    int ti, tj;
+    tile_of(g - jd.first_tile, jd.nt, ti, tj);
+    dump_part<false>(jd, ti, tj, (int)(blockIdx.x % DUMP_PARTS), PendingCorr{nullptr, nullptr, 0, 0});
 }
 
 // Ingest of host-sourced frames (the streaming server): up to GATHER_MAX
@@ -767,6 +768,22 @@ __global__ __launch_bounds__(256) void fill_zero(int4 *__restrict__ p, int64_t n
     for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n4;
          k += (int64_t)gridDim.x * 256)
         p[k] = make_int4(0, 0, 0, 0);
+}
+
+// A slot cleared without an export: its accumulators, its biases with both
+// bases (n_bias int32 each, a multiple of 4), and, if given, its device
+// sample counter.
+__global__ __launch_bounds__(256) void clear_slot(int4 *__restrict__ acc, int64_t n4, int4 *__restrict__ bias,
+                                                  int4 *__restrict__ base, int n_bias4, int64_t *count)
+{
+    const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+    for (int64_t k = first; k < n4; k += step) acc[k] = make_int4(0, 0, 0, 0);
+    for (int64_t k = first; k < n_bias4; k += step) {
+        bias[k] = make_int4(0, 0, 0, 0);
+        base[k] = make_int4(0, 0, 0, 0);
+        base[n_bias4 + k] = make_int4(0, 0, 0, 0);
+    }
+    if (first == 0 && count != nullptr) *count = 0;
 }
 
 // Integration guard of a prepared batch, run ahead of its correlation
@@ -866,36 +883,35 @@ hipError_t launch_correlate_unsigned(const KernelArgs &a, int grid, bool aligned
     return hipGetLastError();
 }
 
-hipError_t launch_dump(int32_t *acc, int32_t *diag, int n, int nt, int32_t *out, bool reset,
-                       hipStream_t stream)
+hipError_t launch_dump(const DumpDesc &jd, hipStream_t stream)
 {
-    hipLaunchKernelGGL(diag_im, dim3((n + 255) / 256), dim3(256), 0, stream, acc, n, nt, diag);
-    hipLaunchKernelGGL(vis_dump, dim3(DUMP_PARTS_PER_TILE * nt, nt), dim3(256), 0, stream, acc, n, nt, diag, out,
-                       reset ? 1 : 0);
+    const int64_t parts = (int64_t)jd.nt * (jd.nt + 1) / 2 * DUMP_PARTS;
+    hipLaunchKernelGGL(vis_dump<false>, dim3((unsigned)parts), dim3(64 * DUMP_WAVES), 0, stream, jd,
+                       PendingCorr{nullptr, nullptr, 0, 0});
     return hipGetLastError();
 }
 
 // An export that also applies a slot's pending unsigned-form correction
 // (`sums`: its SR, SI over `t` samples, n4 apart) and clears `other`.
-hipError_t launch_dump_corr(int32_t *acc, int32_t *diag, int n, int nt, int32_t *out, bool reset,
-                            const int32_t *sums, int n4, int64_t t, int32_t *other, hipStream_t stream)
+hipError_t launch_dump_corr(const DumpDesc &jd, const int32_t *sums, int n4, int64_t t, int32_t *other,
+                            hipStream_t stream)
 {
-    const PendingCorr pc{sums, n4, t};
-    const int threads = n > 2 * n4 ? n : 2 * n4;
-    hipLaunchKernelGGL(diag_im_corr, dim3((threads + 255) / 256), dim3(256), 0, stream, acc, n, nt, diag, pc, other);
-    hipLaunchKernelGGL(vis_dump_corr, dim3(DUMP_PARTS_PER_TILE * nt, nt), dim3(256), 0, stream, acc, n, nt, diag,
-                       out, reset ? 1 : 0, pc);
+    const int64_t parts = (int64_t)jd.nt * (jd.nt + 1) / 2 * DUMP_PARTS;
+    hipLaunchKernelGGL(vis_dump<true>, dim3((unsigned)parts), dim3(64 * DUMP_WAVES), 0, stream, jd,
+                       PendingCorr{sums, other, n4, t});
     return hipGetLastError();
 }
 
-// `d_jobs`: n_jobs descriptors in device memory (n_jobs <= 65535); n_max and
-// nt_max: the largest n and nt among them.
-hipError_t launch_dump_batch(const DumpDesc *d_jobs, int n_jobs, int n_max, int nt_max, hipStream_t stream)
+// `d_jobs`: descriptors in device memory, `total_tiles` tiles in all (at most
+// DUMP_MAX_TILES); d_job_of: the job of each tile, or null where every job
+// has `tiles`.
+hipError_t launch_dump_batch(const DumpDesc *d_jobs, const int32_t *d_job_of, int tiles, int64_t total_tiles,
+                             hipStream_t stream)
 {
-    if (n_jobs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(diag_im_batch, dim3((n_max + 255) / 256, n_jobs), dim3(256), 0, stream, d_jobs);
-    hipLaunchKernelGGL(vis_dump_batch, dim3(DUMP_PARTS_PER_TILE * nt_max, nt_max, n_jobs), dim3(256), 0, stream,
-                       d_jobs);
+    static_assert(DUMP_MAX_TILES * DUMP_PARTS < (INT64_C(1) << 31), "a launch's workgroups fit its grid");
+    if (total_tiles <= 0) return hipSuccess;
+    hipLaunchKernelGGL(vis_dump_batch, dim3((unsigned)(total_tiles * DUMP_PARTS)), dim3(64 * DUMP_WAVES), 0, stream,
+                       d_jobs, d_job_of, tiles);
     return hipGetLastError();
 }
 
@@ -936,6 +952,17 @@ hipError_t launch_zero(int32_t *p, int64_t n_i32, hipStream_t stream)
     if (blocks > 4096) blocks = 4096;
     hipLaunchKernelGGL(fill_zero, dim3((unsigned)blocks), dim3(256), 0, stream,
                        reinterpret_cast<int4 *>(p), n4);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear_slot(int32_t *acc, int64_t n_i32, int32_t *bias, int32_t *base, int64_t n_bias, int64_t *count,
+                             hipStream_t stream)
+{
+    const int64_t n4 = n_i32 / 4;
+    int64_t blocks = (n4 + 255) / 256;
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(clear_slot, dim3((unsigned)blocks), dim3(256), 0, stream, reinterpret_cast<int4 *>(acc), n4,
+                       reinterpret_cast<int4 *>(bias), reinterpret_cast<int4 *>(base), (int)(n_bias / 4), count);
     return hipGetLastError();
 }
 

@@ -229,6 +229,14 @@ __device__ __forceinline__ void flush_rows(const JobDesc &jd, const int32_t *sum
         w[i] = (gw64 *)jd.acc + (blk_a(k) * BLKS + blk_b(k)) * BLOCK_W + r * 64 + lane;   // tile (0, 0)
         v[i] = pack_pair(sum[((2 * k) * 16 + r) * 64 + lane] >> 8, sum[((2 * k + 1) * 16 + r) * 64 + lane] >> 8);
     }
+    // the diagonal's imaginary sums are the slot's biases: waves 0 and 1
+    // take blocks (0, 0) and (1, 1), one lane per input
+    if (wave < 2 && jd.bias != nullptr) {
+        const int k = 2 * wave, r = diag_reg(lane), j = BLK * wave + (lane & 31);
+        if (r >= 0 && j < jd.n)
+            __hip_atomic_fetch_add(jd.bias + j, sum[((2 * k + 1) * 16 + r) * 64 + lane] >> 8, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (atomic) {
 #pragma unroll
         for (int i = 0; i < ROWS_PER_WAVE; ++i)
@@ -273,6 +281,7 @@ __global__ __launch_bounds__(64 * WAVES) void xcorr_narrow(KernelArgs args)
         JobDesc jd = args.jobs ? args.jobs[__builtin_amdgcn_readfirstlane(pce.job)] : args.job0;
         jd.samples = uniform(jd.samples);
         jd.acc = uniform(jd.acc);
+        jd.bias = uniform(jd.bias);
         jd.stride = uniform(jd.stride);
         jd.n = __builtin_amdgcn_readfirstlane(jd.n);
         jd.flags = (uint32_t)__builtin_amdgcn_readfirstlane((int)jd.flags);

@@ -9,8 +9,7 @@
 // correlation kernels add into the slot.  presum_cols (presum_cols16 for
 // aligned rows) forms SR and SI; the
 // correction kernel then adds, to every pair i <= j < N of the slot, the
-// terms above -- in the slot's stored form, whose imaginary part is
-// Im V_ij - S_j with S_j = sum_t Im x_j = SI_j - 8 T.  The slot words are
+// terms above (these samples add Im V itself, with no bias).  The slot words are
 // 64-bit (Im 2^32 + Re) sums, exact in modular arithmetic, so the unsigned
 // sums may pass the int32 range before the correction brings every pair
 // back to its exact value.
@@ -59,7 +58,7 @@ __global__ __launch_bounds__(256) void presum_correct(uint64_t *__restrict__ acc
     const int64_t t = n_samples;
     const int64_t ri = sr[i], ii = si[i], rj = sr[j], ij = si[j];
     const int64_t d_re = -8 * (ri + ii + rj + ij) + 128 * t;
-    const int64_t d_im = 8 * (ri - ii) - 8 * (rj - ij) - (ij - 8 * t);
+    const int64_t d_im = 8 * (ri - ii) - 8 * (rj - ij);
     acc[tile * TILE_W + w] += ((uint64_t)d_im << 32) + (uint64_t)d_re;
 }
 
