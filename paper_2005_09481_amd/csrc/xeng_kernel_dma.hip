@@ -36,221 +36,113 @@
 // instructions holds the issuing wave for tens of cycles per instruction.
 // Regions and blocks wholly below the diagonal are not computed.
 //
-// LDS stage layout ("chunk-major" in 8-row groups): the A region holds 8
-// groups of 8 time rows x 8 chunks of 16 inputs, chunk c of row r at byte
-// 128 c + 16 r of its group; the B region the same with 16 chunks.  The 8
-// rows a transposed read touches are then 128 contiguous bytes, and every
-// read of a stage is a per-lane base plus a compile-time offset.
+// LDS stage layout: the A side, then the B side, each row-major by time row
+// with the 16-byte chunks of a row permuted (swizzle, xeng_dma_ops.h).  Every
+// DMA instruction then reads whole rows of its side, 128 or 256 contiguous
+// bytes each, where the chunk-major layout used before (8 rows x 16 bytes
+// contiguous in LDS) made neighbouring lanes read 16 bytes of different rows:
+// a quarter as many cache accesses for the same bytes, and no bank conflict
+// in either.  N = 2048, T = 32768: 213.5 -> 209.3 us a correlate + export
+// step in alternating runs, N = 2048, T = 2048: 60.2 -> 57.1 us.
 #include <hip/hip_runtime.h>
 
-#include "xeng_internal.h"
+#include "xeng_dma_ops.h"
 
 namespace xeng {
 namespace dma {
 
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) v2i lds_v2i;
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
-typedef __attribute__((address_space(1))) uint64_t gw64;
-
 constexpr int WA_ROWS = 128;            // A rows per workgroup tile
-constexpr int WB_COLS = 256;            // B columns per workgroup tile
-constexpr int GRP_A = 8 * WA_ROWS;      // bytes of an 8-row group, A region: 1 KB
-constexpr int GRP_B = 8 * WB_COLS;      // 2 KB
 constexpr int A_STAGE = STAGE * WA_ROWS;    // 8 KB of packed samples
-constexpr int B_STAGE = STAGE * WB_COLS;    // 16 KB
-constexpr int SLOT = A_STAGE + B_STAGE;     // 24 KB
-constexpr int NSLOT = 6;                    // ring: 144 KB of LDS
-constexpr int AHEAD = NSLOT - 1;            // stages issued ahead
 constexpr int DMA_A = A_STAGE / 1024;       // 1 KB DMA instructions per stage: 8
-constexpr int DMA_B = B_STAGE / 1024;       // 16
 
-// With eight waves, the DMA is left to one wave per SIMD (the other wave's
-// MFMAs then run while the issuing wave waits to issue); 0 spreads it over
-// all eight.
-#ifndef XENG_DMA_SPLIT
-#define XENG_DMA_SPLIT 1
-#endif
-
-template <int NW> struct Layout {
-    static constexpr int WB_WAVES = NW / 2;                  // waves across the 256 columns
-    static constexpr int BW = 8 / WB_WAVES;                  // B blocks per wave
-    static constexpr int DMA_WAVES = (NW == 8 && XENG_DMA_SPLIT) ? 4 : NW;   // waves that issue DMA
-    static constexpr int DMA_PER_WAVE = (DMA_A + DMA_B) / DMA_WAVES;
+// The kernels' shapes: NWAVES waves in TIMES time groups over 128 x COLS
+// inputs, a ring of SLOTS slots of a 64-sample stage per time group, DMA
+// waves per time group issuing its loads.
+template <int NWAVES, int TIMES, int COLS, int SLOTS, int DMA> struct Shape {
+    static constexpr int NW = NWAVES;
+    static constexpr int TG = TIMES;
+    static constexpr int PITCH_A = WA_ROWS, PITCH_B = COLS;   // bytes per time row of a side in LDS
+    static constexpr int WB_COLS = COLS;                     // B columns per workgroup tile
+    static constexpr int TILES = COLS / TILE;                // accumulator tiles side by side
+    static constexpr int B_STAGE = STAGE * COLS;
+    static constexpr int GROUP = A_STAGE + B_STAGE;          // one time group's stage
+    static constexpr int SLOT = TG * GROUP;
+    static constexpr int ROWS = TG * STAGE;                  // samples per slot
+    static constexpr int NSLOT = SLOTS;
+    static constexpr int AHEAD = SLOTS - 1;                  // stages issued ahead
+    static constexpr int LDS_BYTES = SLOTS * SLOT;
+    static constexpr int DMA_B = B_STAGE / 1024;
+    static constexpr int WB_WAVES = NWAVES / TG / 2;         // waves across the columns
+    static constexpr int BW = COLS / BLK / WB_WAVES;         // B blocks per wave
+    static constexpr int DMA_WAVES = DMA;
+    static constexpr int DMA_PER_WAVE = (DMA_A + DMA_B) / DMA;
     static constexpr int MFMA_PER_K = 4 * BW;                // MFMAs per k-step
     static constexpr int READS_PER_K = 2 + BW;               // transposed reads per k-step
-    static constexpr int VALU_PER_MFMA = NW == 4 ? 3 : 4;    // unpack share between MFMAs
+    static constexpr int VALU_PER_MFMA = BW == 4 ? 3 : 4;    // unpack share between MFMAs
 };
 
-// s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, expcnt 6:4 and
-// lgkmcnt 11:8 at their maxima (no wait on those); and lgkmcnt(0) alone.
-#define XENG_VMCNT(n) (((n) & 0xF) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
-#define XENG_LGKMCNT0 (0xF | (0x3 << 14) | (0x7 << 4))
-
-// A wave-uniform 64-bit value moved to scalar registers.
-template <typename T> __device__ __forceinline__ T uniform(T v)
-{
-    static_assert(sizeof(T) == 8, "64-bit values only");
-    uint64_t u;
-    __builtin_memcpy(&u, &v, 8);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)u);
-    u = ((uint64_t)hi << 32) | lo;
-    __builtin_memcpy(&v, &u, 8);
-    return v;
-}
-
+// The wide kernel: 128 x 256, six 24 KB stages.  With eight waves, the DMA
+// is left to one wave per SIMD (the other wave's MFMAs then run while the
+// issuing wave waits to issue).
+template <int NW> using Layout = Shape<NW, 1, 256, 6, 4>;
 struct Tile {
     const uint8_t *samples;
     const uint8_t *zeros;   // 16 bytes of zero samples (0x88)
     int64_t stride;
     int n;                  // inputs (a multiple of 16)
     int row0, col0;         // first A input, first B input
-    int t0, t1;
+    int t0, t1;             // samples, t0 that of the wave's time group
+    int ns;                 // ring slots of the piece
 };
 
-// 16-byte-per-lane DMAs into LDS at byte address `lds_addr` + 16 * lane,
-// written as inline assembly so that the compiler, which cannot tell that
-// reads of other ring slots never alias the slot being filled, does not
-// drain every load in flight before each LDS read; the ring's own vmcnt
-// waits order the accesses.  The instructions have no register result; M0
-// (their LDS base) is saved and restored around them.  Wait states: one
-// between an SALU write of M0 and the DMA; five between a VALU write of an
-// SGPR (readfirstlane) and a memory instruction that reads it as its base.
-// (readfirstlane is a no-op on values already in scalar registers; it
-// returns a signed int, so each half of a pointer is widened as unsigned.)
-//
-// Vector-address form: a 64-bit address per lane.
-__device__ __forceinline__ void dma16_v(const uint8_t *addr, uint32_t lds_addr)
-{
-    const uint32_t sl = (uint32_t)__builtin_amdgcn_readfirstlane(lds_addr);
-    uint32_t saved;
-    asm volatile("s_mov_b32 %0, m0\n\t"
-                 "s_mov_b32 m0, %2\n\t"
-                 "s_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, off\n\t"
-                 "s_mov_b32 m0, %0"
-                 : "=&s"(saved)
-                 : "v"(addr), "s"(sl)
-                 : "memory");
-}
-
-// Scalar-base form, wave-uniform 64-bit base + per-lane 32-bit offsets: a
-// whole stage's share of DMAs (K = 6 or 3) in one statement:
-// M0 saved once, one s_nop 4 ahead of the first instruction (covering a
-// VALU write of any SGPR operand, which the statement's own instructions
-// never make), and between instructions only the one wait state an SALU
-// write of M0 needs before an LDS DMA.
-template <int K>
-__device__ __forceinline__ void dma16_s_stage(const uint8_t *base, const uint32_t (&lane_off)[K],
-                                              const uint32_t (&lds_addr)[K])
-{
-    static_assert(K == 6 || K == 3, "6 or 3 instructions per wave");
-    const uint64_t b = (uint64_t)(uintptr_t)base;
-    const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-    const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b);
-    const uint64_t sb = ((uint64_t)b_hi << 32) | (uint64_t)b_lo;
-    uint32_t sl[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) sl[k] = (uint32_t)__builtin_amdgcn_readfirstlane(lds_addr[k]);
-    uint32_t saved;
-    if constexpr (K == 6) {
-        asm volatile("s_mov_b32 %0, m0\n\t"
-                     "s_mov_b32 m0, %8\n\t"
-                     "s_nop 4\n\t"
-                     "global_load_lds_dwordx4 %1, %7\n\t"
-                     "s_mov_b32 m0, %9\n\t"
-                     "s_nop 0\n\t"
-                     "global_load_lds_dwordx4 %2, %7\n\t"
-                     "s_mov_b32 m0, %10\n\t"
-                     "s_nop 0\n\t"
-                     "global_load_lds_dwordx4 %3, %7\n\t"
-                     "s_mov_b32 m0, %11\n\t"
-                     "s_nop 0\n\t"
-                     "global_load_lds_dwordx4 %4, %7\n\t"
-                     "s_mov_b32 m0, %12\n\t"
-                     "s_nop 0\n\t"
-                     "global_load_lds_dwordx4 %5, %7\n\t"
-                     "s_mov_b32 m0, %13\n\t"
-                     "s_nop 0\n\t"
-                     "global_load_lds_dwordx4 %6, %7\n\t"
-                     "s_mov_b32 m0, %0"
-                     : "=&s"(saved)
-                     : "v"(lane_off[0]), "v"(lane_off[1]), "v"(lane_off[2]), "v"(lane_off[3]),
-                       "v"(lane_off[4]), "v"(lane_off[5]), "s"(sb), "s"(sl[0]), "s"(sl[1]), "s"(sl[2]),
-                       "s"(sl[3]), "s"(sl[4]), "s"(sl[5])
-                     : "memory");
-    } else {
-        asm volatile("s_mov_b32 %0, m0\n\t"
-                     "s_mov_b32 m0, %5\n\t"
-                     "s_nop 4\n\t"
-                     "global_load_lds_dwordx4 %1, %4\n\t"
-                     "s_mov_b32 m0, %6\n\t"
-                     "s_nop 0\n\t"
-                     "global_load_lds_dwordx4 %2, %4\n\t"
-                     "s_mov_b32 m0, %7\n\t"
-                     "s_nop 0\n\t"
-                     "global_load_lds_dwordx4 %3, %4\n\t"
-                     "s_mov_b32 m0, %0"
-                     : "=&s"(saved)
-                     : "v"(lane_off[0]), "v"(lane_off[1]), "v"(lane_off[2]), "s"(sb), "s"(sl[0]), "s"(sl[1]),
-                       "s"(sl[2])
-                     : "memory");
-    }
-}
-
-// Geometry of DMA instruction `inst` (0..23) of a stage for this lane: its
-// LDS offset in the slot (wave-uniform), the time row in the stage and the
-// first of the 16 inputs the lane fetches.  Instructions 0..7 fill A group
-// `inst`; 8..23 fill half h of B group g.  Lane l fetches chunk l / 8 of
-// the instruction's 8 chunks at time row l % 8 of the group, which lands at
-// byte 16 l = 128 (l / 8) + 16 (l % 8) of the instruction's kilobyte.
+// Geometry of DMA instruction `inst` (0..23, or 0..15 of the tile kernel) of
+// a stage for this lane: its LDS offset in the slot (wave-uniform), the time
+// row in the stage and the first of the 16 inputs the lane fetches.
+// Instructions 0..7 fill 8 rows of the A side each, the others 4 rows (8 in
+// the tile kernel) of the B side.
 // A chunk at or past input n (the edge tiles of an N that is not a multiple
 // of the tile) is fetched from inputs n - 16.. instead: every load stays in
 // its row, and what lands in those rows or columns of the tile only reaches
 // accumulator entries (i, j) with i or j >= n, which are never exported.
+template <typename L>
 __device__ __forceinline__ void dma_geom(int inst, int lane, int n, int row0, int col0, int &lds_off, int &t,
                                          int &in)
 {
-    const int r = lane & 7, c = lane >> 3;
+    lds_off = inst * 1024;   // the B side follows the A side
     if (inst < DMA_A) {
-        lds_off = inst * GRP_A;
-        t = 8 * inst + r;
-        in = row0 + 16 * c;
+        const int first = inst * (1024 / L::PITCH_A);
+        t = first + dma_row<L::PITCH_A>(lane);
+        in = row0 + 16 * dma_chunk<L::PITCH_A>(first, lane);
     } else {
-        const int i = inst - DMA_A, g = i >> 1, h = i & 1;
-        lds_off = A_STAGE + g * GRP_B + h * 1024;
-        t = 8 * g + r;
-        in = col0 + 16 * (8 * h + c);
+        const int first = (inst - DMA_A) * (1024 / L::PITCH_B);
+        t = first + dma_row<L::PITCH_B>(lane);
+        in = col0 + 16 * dma_chunk<L::PITCH_B>(first, lane);
     }
     in = min(in, n - 16);
 }
 
 // Index of this wave among the DMA-issuing waves, or -1.  Waves 0..3 sit on
 // SIMDs 0..3 (waves of a workgroup are placed on the SIMDs in turn).
-template <int NW> __device__ __forceinline__ int dma_wave(int wave)
+template <typename L> __device__ __forceinline__ int dma_wave(int wave)
 {
-    if (Layout<NW>::DMA_WAVES == NW) return wave;
+    if (L::TG > 1) return wave % (L::NW / L::TG);
+    if (L::DMA_WAVES == L::NW) return wave;
     return wave < 4 ? wave : -1;
 }
 
 // Per-lane byte offsets (row * stride + input) of this wave's DMA
 // instructions from a stage's first row, fixed for a piece.
-template <int NW> struct DmaLane {
-    uint32_t off[Layout<NW>::DMA_PER_WAVE];
+template <typename L> struct DmaLane {
+    uint32_t off[L::DMA_PER_WAVE];
 };
 
-template <int NW>
-__device__ __forceinline__ void dma_lane_setup(DmaLane<NW> &dl, const Tile &tl, int wave, int lane)
+template <typename L>
+__device__ __forceinline__ void dma_lane_setup(DmaLane<L> &dl, const Tile &tl, int wave, int lane)
 {
 #pragma unroll
-    for (int k = 0; k < Layout<NW>::DMA_PER_WAVE; ++k) {
+    for (int k = 0; k < L::DMA_PER_WAVE; ++k) {
         int lds_off, t, in;
-        dma_geom(dma_wave<NW>(wave) + Layout<NW>::DMA_WAVES * k, lane, tl.n, tl.row0, tl.col0, lds_off, t, in);
+        dma_geom<L>(dma_wave<L>(wave) + L::DMA_WAVES * k, lane, tl.n, tl.row0, tl.col0, lds_off, t, in);
         dl.off[k] = (uint32_t)((int64_t)t * tl.stride) + (uint32_t)in;
     }
 }
@@ -261,28 +153,28 @@ __device__ __forceinline__ void dma_lane_setup(DmaLane<NW> &dl, const Tile &tl, 
 // past its end, issued so that the count of loads in flight stays
 // constant) are read from the zero-sample buffer, so that every stage the
 // compute loop sees is whole.
-template <int NW>
-__device__ __forceinline__ void issue_stage(uint32_t slot_addr, const Tile &tl, const DmaLane<NW> &dl, int stage,
+template <typename L>
+__device__ __forceinline__ void issue_stage(uint32_t slot_addr, const Tile &tl, const DmaLane<L> &dl, int stage,
                                             int wave, int lane)
 {
-    const int dw = dma_wave<NW>(wave);
+    const int dw = dma_wave<L>(wave);
     if (dw < 0) return;
-    const int ts = tl.t0 + stage * STAGE;
+    const int ts = tl.t0 + stage * L::ROWS;
     if (ts + STAGE <= tl.t1) {
         const uint8_t *row = tl.samples + (int64_t)ts * tl.stride;
-        uint32_t lds[Layout<NW>::DMA_PER_WAVE];
+        uint32_t lds[L::DMA_PER_WAVE];
 #pragma unroll
-        for (int k = 0; k < Layout<NW>::DMA_PER_WAVE; ++k) {
+        for (int k = 0; k < L::DMA_PER_WAVE; ++k) {
             int lds_off, t, in;
-            dma_geom(dw + Layout<NW>::DMA_WAVES * k, lane, tl.n, tl.row0, tl.col0, lds_off, t, in);
+            dma_geom<L>(dw + L::DMA_WAVES * k, lane, tl.n, tl.row0, tl.col0, lds_off, t, in);
             lds[k] = slot_addr + (uint32_t)lds_off;
         }
-        dma16_s_stage<Layout<NW>::DMA_PER_WAVE>(row, dl.off, lds);
+        dma16_s_stage<L::DMA_PER_WAVE>(row, dl.off, lds);
     } else {
 #pragma unroll
-        for (int k = 0; k < Layout<NW>::DMA_PER_WAVE; ++k) {
+        for (int k = 0; k < L::DMA_PER_WAVE; ++k) {
             int lds_off, t, in;
-            dma_geom(dw + Layout<NW>::DMA_WAVES * k, lane, tl.n, tl.row0, tl.col0, lds_off, t, in);
+            dma_geom<L>(dw + L::DMA_WAVES * k, lane, tl.n, tl.row0, tl.col0, lds_off, t, in);
             const uint8_t *src =
                 ts + t < tl.t1 ? tl.samples + (int64_t)(ts + t) * tl.stride + in : tl.zeros;
             dma16_v(src, slot_addr + (uint32_t)lds_off);
@@ -290,223 +182,13 @@ __device__ __forceinline__ void issue_stage(uint32_t slot_addr, const Tile &tl, 
     }
 }
 
-// Packed operand data of one k-step (2 A blocks, BW B blocks) and its
-// unpacked form.
-template <int NW> struct Raw {
-    v2i a[2];
-    v2i b[Layout<NW>::BW];
-};
-template <int NW> struct Ops {
-    v8i a[2];   // {16R, 16R, 16I, 16I, 16~R, 16~R, -, -}: real A = s0123, imaginary A = s2345
-    v4i b[Layout<NW>::BW];   // {16R, 16R, 16I, 16I}
-};
-template <int NW, bool F> struct Acc {
-    v16i re[2][Layout<NW>::BW];
-    v16i im[2][Layout<NW>::BW];
-};
-template <int NW> struct Acc<NW, true> {
-    v16f re[2][Layout<NW>::BW];
-    v16f im[2][Layout<NW>::BW];
-};
-
-// Transposed reads of k-step q: `pa`, `pb` are this lane's bases in the
-// slot's A and B regions (group lane / 32, chunk of the lane's 16-lane
-// group, byte 8 (lane % 16)); k-step q adds 2 groups, block a / b 2 chunks.
-template <int NW>
-__device__ __forceinline__ void read_k(Raw<NW> &r, const lds_u8 *pa, const lds_u8 *pb, int q)
-{
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-        r.a[a] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(pa + 2 * GRP_A * q + 256 * a));
-#pragma unroll
-    for (int b = 0; b < Layout<NW>::BW; ++b)
-        r.b[b] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(pb + 2 * GRP_B * q + 256 * b));
-}
-
-// 16 x (4-bit value) in the high half of each byte: from the high nibbles,
-// (p ^ 0x88) & 0xF0 per byte; from the low nibbles, the same on p << 4.
-// XOR with 0x77 instead of 0x88 gives 16 x the bitwise complement.
-//
-// Unsigned form (U): the stored nibbles u in 0..15 themselves, no offset
-// removed -- A real [uR | uI], A imaginary [uI | -uR] (per byte
-// (0x80 - u) ^ 0x80: no borrows), B [8 uR | 8 uI] (at most 120) -- so the
-// sums are 8 x the exact products of the stored values, with no bias.
-//
-// FP8 form (F, unsigned): a byte holding u in 0..15 is the OCP E4M3 code of
-// u x 2^-9 (codes 0..7 are the subnormals m x 2^-9, codes 8..15 the first
-// binade (8 + m) x 2^-9), and setting its top bit negates it exactly.  So A
-// real [uR | uI], A imaginary [uI | -uR] and B [uR | uI] are the masked
-// nibbles themselves (and the sign bit), and the fp32 sums hold the exact
-// integer sums x 2^-18.
-template <int NW, bool RE_LOW, bool U, bool F>
-__device__ __forceinline__ void unpack_k(Ops<NW> &o, const Raw<NW> &r)
-{
-    if constexpr (F) {
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            const uint32_t x0 = (uint32_t)r.a[a].x, x1 = (uint32_t)r.a[a].y;
-            const uint32_t h0 = (x0 >> 4) & 0x0F0F0F0Fu, h1 = (x1 >> 4) & 0x0F0F0F0Fu;
-            const uint32_t l0 = x0 & 0x0F0F0F0Fu, l1 = x1 & 0x0F0F0F0Fu;
-            const uint32_t re0 = RE_LOW ? l0 : h0, re1 = RE_LOW ? l1 : h1;
-            const uint32_t im0 = RE_LOW ? h0 : l0, im1 = RE_LOW ? h1 : l1;
-            o.a[a] = v8i{(int)re0, (int)re1, (int)im0, (int)im1, (int)(re0 | 0x80808080u), (int)(re1 | 0x80808080u),
-                         0, 0};
-        }
-#pragma unroll
-        for (int b = 0; b < Layout<NW>::BW; ++b) {
-            const uint32_t x0 = (uint32_t)r.b[b].x, x1 = (uint32_t)r.b[b].y;
-            const uint32_t h0 = (x0 >> 4) & 0x0F0F0F0Fu, h1 = (x1 >> 4) & 0x0F0F0F0Fu;
-            const uint32_t l0 = x0 & 0x0F0F0F0Fu, l1 = x1 & 0x0F0F0F0Fu;
-            o.b[b] = RE_LOW ? v4i{(int)l0, (int)l1, (int)h0, (int)h1} : v4i{(int)h0, (int)h1, (int)l0, (int)l1};
-        }
-        return;
-    }
-    if constexpr (U) {
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            const uint32_t x0 = (uint32_t)r.a[a].x, x1 = (uint32_t)r.a[a].y;
-            const uint32_t h0 = (x0 >> 4) & 0x0F0F0F0Fu, h1 = (x1 >> 4) & 0x0F0F0F0Fu;
-            const uint32_t l0 = x0 & 0x0F0F0F0Fu, l1 = x1 & 0x0F0F0F0Fu;
-            const uint32_t re0 = RE_LOW ? l0 : h0, re1 = RE_LOW ? l1 : h1;
-            const uint32_t im0 = RE_LOW ? h0 : l0, im1 = RE_LOW ? h1 : l1;
-            const uint32_t n0 = (0x80808080u - re0) ^ 0x80808080u, n1 = (0x80808080u - re1) ^ 0x80808080u;
-            o.a[a] = v8i{(int)re0, (int)re1, (int)im0, (int)im1, (int)n0, (int)n1, 0, 0};
-        }
-#pragma unroll
-        for (int b = 0; b < Layout<NW>::BW; ++b) {
-            const uint32_t x0 = (uint32_t)r.b[b].x, x1 = (uint32_t)r.b[b].y;
-            const uint32_t h0 = (x0 >> 1) & 0x78787878u, h1 = (x1 >> 1) & 0x78787878u;   // 8 x high nibble
-            const uint32_t l0 = (x0 << 3) & 0x78787878u, l1 = (x1 << 3) & 0x78787878u;   // 8 x low nibble
-            o.b[b] = RE_LOW ? v4i{(int)l0, (int)l1, (int)h0, (int)h1} : v4i{(int)h0, (int)h1, (int)l0, (int)l1};
-        }
-        return;
-    }
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const uint32_t x0 = (uint32_t)r.a[a].x, x1 = (uint32_t)r.a[a].y;
-        const uint32_t s0 = x0 << 4, s1 = x1 << 4;
-        const uint32_t h0 = (x0 ^ 0x88888888u) & 0xF0F0F0F0u, h1 = (x1 ^ 0x88888888u) & 0xF0F0F0F0u;
-        const uint32_t l0 = (s0 ^ 0x80808080u) & 0xF0F0F0F0u, l1 = (s1 ^ 0x80808080u) & 0xF0F0F0F0u;
-        if (RE_LOW) {
-            const uint32_t n0 = (s0 ^ 0x70707070u) & 0xF0F0F0F0u, n1 = (s1 ^ 0x70707070u) & 0xF0F0F0F0u;
-            o.a[a] = v8i{(int)l0, (int)l1, (int)h0, (int)h1, (int)n0, (int)n1, 0, 0};
-        } else {
-            const uint32_t n0 = (x0 ^ 0x77777777u) & 0xF0F0F0F0u, n1 = (x1 ^ 0x77777777u) & 0xF0F0F0F0u;
-            o.a[a] = v8i{(int)h0, (int)h1, (int)l0, (int)l1, (int)n0, (int)n1, 0, 0};
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < Layout<NW>::BW; ++b) {
-        const uint32_t x0 = (uint32_t)r.b[b].x, x1 = (uint32_t)r.b[b].y;
-        const uint32_t h0 = (x0 ^ 0x88888888u) & 0xF0F0F0F0u, h1 = (x1 ^ 0x88888888u) & 0xF0F0F0F0u;
-        const uint32_t l0 = ((x0 << 4) ^ 0x80808080u) & 0xF0F0F0F0u;
-        const uint32_t l1 = ((x1 << 4) ^ 0x80808080u) & 0xF0F0F0F0u;
-        o.b[b] = RE_LOW ? v4i{(int)l0, (int)l1, (int)h0, (int)h1} : v4i{(int)h0, (int)h1, (int)l0, (int)l1};
-    }
-}
-
-// Pre-sums of the unsigned form from the operands a wave multiplies: per A
-// block, this lane's row (lane % 32) over the k-step's samples it holds,
-// real nibbles (words 0, 1) and imaginary ones (words 2, 3), each a byte
-// sum by v_dot4_u32_u8 against ones.
-struct PreSum {
-    uint32_t r[2], i[2];
-};
-template <int NW> __device__ __forceinline__ void presum_k(PreSum &ps, const Ops<NW> &o)
-{
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        ps.r[a] = __builtin_amdgcn_udot4((uint32_t)o.a[a][0], 0x01010101u, ps.r[a], false);
-        ps.r[a] = __builtin_amdgcn_udot4((uint32_t)o.a[a][1], 0x01010101u, ps.r[a], false);
-        ps.i[a] = __builtin_amdgcn_udot4((uint32_t)o.a[a][2], 0x01010101u, ps.i[a], false);
-        ps.i[a] = __builtin_amdgcn_udot4((uint32_t)o.a[a][3], 0x01010101u, ps.i[a], false);
-    }
-}
-
-// DIAG: the wave's 2 x 2 blocks sit on the diagonal (eight waves, rows
-// 64 wa.. against columns 64 wa.. of a diagonal tile); block (1, 0) lies
-// strictly below it and is skipped.
-template <int NW, bool DIAG> __device__ __forceinline__ constexpr bool skip_block(int a, int b)
-{
-    return DIAG && a == 1 && b == 0;
-}
-
-// The real products of a k-step first, then the imaginary ones: measured a
-// little faster than alternating them (the chip runs at its power limit, and
-// this order drew less).
-//
-// FP8 form: the products of two k-steps at once on
-// v_mfma_f32_32x32x64_f8f6f4 (E4M3 on both sides, no block scale), whose
-// 32-byte operands are the two k-steps' unpacked words side by side: real
-// [R | I | R' | I'] . [R | I | R' | I'], imaginary [I | -R | I' | -R'] .
-// [R | I | R' | I'].  All real products of the pair first, then the
-// imaginary ones, so that no product waits for the one before it.
-template <int NW, bool DIAG>
-__device__ __forceinline__ void mfma_pair(Acc<NW, true> &acc, const Ops<NW> &o0, const Ops<NW> &o1)
-{
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int b = 0; b < Layout<NW>::BW; ++b)
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                if (skip_block<NW, DIAG>(a, b)) continue;
-                const int w = 2 * p;   // real: words 0..3, imaginary: words 2..5
-                const v8i av = {o0.a[a][w], o0.a[a][w + 1], o0.a[a][w + 2], o0.a[a][w + 3],
-                                o1.a[a][w], o1.a[a][w + 1], o1.a[a][w + 2], o1.a[a][w + 3]};
-                const v8i bv = {o0.b[b][0], o0.b[b][1], o0.b[b][2], o0.b[b][3],
-                                o1.b[b][0], o1.b[b][1], o1.b[b][2], o1.b[b][3]};
-                v16f &c = p == 0 ? acc.re[a][b] : acc.im[a][b];
-                c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 0, 0, 0, 0, 0, 0);
-            }
-}
-
-template <int NW, bool DIAG>
-__device__ __forceinline__ void mfma_k(Acc<NW, false> &acc, const Ops<NW> &o)
-{
-#pragma unroll
-    for (int b = 0; b < Layout<NW>::BW; ++b)
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            if (skip_block<NW, DIAG>(a, b)) continue;
-            const v4i re_a = __builtin_shufflevector(o.a[a], o.a[a], 0, 1, 2, 3);
-            acc.re[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(re_a, o.b[b], acc.re[a][b], 0, 0, 0);
-        }
-#pragma unroll
-    for (int b = 0; b < Layout<NW>::BW; ++b)
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            if (skip_block<NW, DIAG>(a, b)) continue;
-            const v4i im_a = __builtin_shufflevector(o.a[a], o.a[a], 2, 3, 4, 5);
-            acc.im[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(im_a, o.b[b], acc.im[a][b], 0, 0, 0);
-        }
-}
-
-// Instruction order of a k-step: the MFMAs, each followed by a share of the
-// unpack of the next k-step (which the matrix core's 32-cycle MFMAs hide)
-// and, after the first few, one of the LDS reads of a later k-step -- spread
-// out rather than issued as a burst that would stall the wave at issue.
-template <int NW, bool DIAG>
-__device__ __forceinline__ void kstep_schedule()
-{
-    using L = Layout<NW>;
-    constexpr int MFMAS = L::MFMA_PER_K - (DIAG ? 2 : 0);
-    constexpr int VALU = DIAG ? (L::VALU_PER_MFMA * L::MFMA_PER_K + MFMAS - 1) / MFMAS : L::VALU_PER_MFMA;
-#pragma unroll
-    for (int m = 0; m < MFMAS; ++m) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-        if (m < L::READS_PER_K) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // DS read
-        __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);   // VALU
-    }
-}
-
-template <int NW>
+template <typename L>
 __device__ __forceinline__ void wait_stage_and_sync()
 {
-    // this wave's loads of the next stage have landed (AHEAD - 1 newer
+    // this wave's loads of the next stage have landed (L::AHEAD - 1 newer
     // stages in flight) and its LDS reads are done; the barrier extends both
     // to the workgroup
-    __builtin_amdgcn_s_waitcnt(XENG_VMCNT((AHEAD - 1) * Layout<NW>::DMA_PER_WAVE));
+    __builtin_amdgcn_s_waitcnt(XENG_VMCNT((L::AHEAD - 1) * L::DMA_PER_WAVE));
     __builtin_amdgcn_s_waitcnt(XENG_LGKMCNT0);
     __syncthreads();
 }
@@ -514,7 +196,7 @@ __device__ __forceinline__ void wait_stage_and_sync()
 // One piece, software-pipelined over its stages.  Entering iteration s, the
 // unpacked operands of (s, k-step 0) and the raw data of (s, 1) are in
 // registers; the iteration reads (s, 2), (s, 3), (s+1, 0), (s+1, 1) and
-// unpacks one k-step ahead of its MFMAs.  The DMA of stage s + AHEAD goes
+// unpacks one k-step ahead of its MFMAs.  The DMA of stage s + L::AHEAD goes
 // into the slot stage s - 1 used, which every wave finished reading before
 // the barrier of iteration s - 1; that barrier sits before the first read of
 // stage s.  The last iteration's reads of "stage ns" touch a slot whose
@@ -523,63 +205,57 @@ __device__ __forceinline__ void wait_stage_and_sync()
 // In the unsigned form the waves on the diagonal (DIAG) also add up the
 // nibbles of their A rows into `ps`, at the k-steps they multiply (the
 // reads of "stage ns" never count).
-template <int NW, bool RE_LOW, bool DIAG, bool U, bool F>
-__device__ __forceinline__ void run_piece(Acc<NW, F> &acc, PreSum &ps, uint32_t ring, const Tile &tl, int wave,
-                                          int lane, uint32_t a_lane, uint32_t b_lane)
+template <typename L, bool RE_LOW, bool DIAG, bool U, bool F>
+__device__ __forceinline__ void run_piece(Acc<L, F> &acc, PreSum &ps, uint32_t ring, const Tile &tl, int wave,
+                                          int lane, const ReadLane<L> &rl)
 {
     constexpr bool SUMS = U && DIAG;
-    const int ns = (tl.t1 - tl.t0 + STAGE - 1) / STAGE;
-    DmaLane<NW> dl;
-    dma_lane_setup<NW>(dl, tl, wave, lane);
+    const int ns = L::TG == 1 ? (tl.t1 - tl.t0 + STAGE - 1) / STAGE : tl.ns;
+    DmaLane<L> dl;
+    dma_lane_setup<L>(dl, tl, wave, lane);
     // nothing else in flight: the ring's vmcnt waits then count DMA only
     __builtin_amdgcn_s_waitcnt(XENG_VMCNT(0));
 #pragma unroll
-    for (int d = 0; d < AHEAD; ++d) issue_stage<NW>(ring + d * SLOT, tl, dl, d, wave, lane);
-    wait_stage_and_sync<NW>();
+    for (int d = 0; d < L::AHEAD; ++d) issue_stage<L>(ring + d * L::SLOT, tl, dl, d, wave, lane);
+    wait_stage_and_sync<L>();
 
-    Raw<NW> r0, r1;
-    Ops<NW> u0, u1;
+    Raw<L> r0, r1;
+    Ops<L> u0, u1;
     if constexpr (F) {
         // FP8: a k-step pair at a time.  Entering each half stage, the raw
         // data of its two k-steps is in r0, r1; both are unpacked, the next
         // pair's reads are issued, then the pair's products.
         {
-            const lds_u8 *pa = (const lds_u8 *)(uintptr_t)(ring + a_lane);
-            const lds_u8 *pb = (const lds_u8 *)(uintptr_t)(ring + b_lane);
-            read_k<NW>(r0, pa, pb, 0);
-            read_k<NW>(r1, pa, pb, 1);
+            read_k<L>(r0, ring, rl, 0);
+            read_k<L>(r1, ring, rl, 1);
         }
         int cur = 0;
         for (int s = 0; s < ns; ++s) {
-            const int nxt = cur == NSLOT - 1 ? 0 : cur + 1;
-            const int iss = cur == 0 ? NSLOT - 1 : cur - 1;
-            issue_stage<NW>(ring + iss * SLOT, tl, dl, s + AHEAD, wave, lane);
-            const lds_u8 *pa = (const lds_u8 *)(uintptr_t)(ring + cur * SLOT + a_lane);
-            const lds_u8 *pb = (const lds_u8 *)(uintptr_t)(ring + cur * SLOT + b_lane);
-            const lds_u8 *qa = (const lds_u8 *)(uintptr_t)(ring + nxt * SLOT + a_lane);
-            const lds_u8 *qb = (const lds_u8 *)(uintptr_t)(ring + nxt * SLOT + b_lane);
+            const int nxt = cur == L::NSLOT - 1 ? 0 : cur + 1;
+            const int iss = cur == 0 ? L::NSLOT - 1 : cur - 1;
+            issue_stage<L>(ring + iss * L::SLOT, tl, dl, s + L::AHEAD, wave, lane);
             __builtin_amdgcn_sched_barrier(0);
             // k-steps 0, 1
-            unpack_k<NW, RE_LOW, U, F>(u0, r0);
-            unpack_k<NW, RE_LOW, U, F>(u1, r1);
-            read_k<NW>(r0, pa, pb, 2);
-            read_k<NW>(r1, pa, pb, 3);
-            mfma_pair<NW, DIAG>(acc, u0, u1);
+            unpack_k<L, RE_LOW, U, F>(u0, r0);
+            unpack_k<L, RE_LOW, U, F>(u1, r1);
+            read_k<L>(r0, ring + cur * L::SLOT, rl, 2);
+            read_k<L>(r1, ring + cur * L::SLOT, rl, 3);
+            mfma_pair<L, DIAG>(acc, u0, u1);
             if constexpr (SUMS) {
-                presum_k<NW>(ps, u0);
-                presum_k<NW>(ps, u1);
+                presum_k<L>(ps, u0);
+                presum_k<L>(ps, u1);
             }
             __builtin_amdgcn_sched_barrier(0);
             // k-steps 2, 3; stage s + 1 must be in LDS before its first read
-            unpack_k<NW, RE_LOW, U, F>(u0, r0);
-            unpack_k<NW, RE_LOW, U, F>(u1, r1);
-            wait_stage_and_sync<NW>();
-            read_k<NW>(r0, qa, qb, 0);
-            read_k<NW>(r1, qa, qb, 1);
-            mfma_pair<NW, DIAG>(acc, u0, u1);
+            unpack_k<L, RE_LOW, U, F>(u0, r0);
+            unpack_k<L, RE_LOW, U, F>(u1, r1);
+            wait_stage_and_sync<L>();
+            read_k<L>(r0, ring + nxt * L::SLOT, rl, 0);
+            read_k<L>(r1, ring + nxt * L::SLOT, rl, 1);
+            mfma_pair<L, DIAG>(acc, u0, u1);
             if constexpr (SUMS) {
-                presum_k<NW>(ps, u0);
-                presum_k<NW>(ps, u1);
+                presum_k<L>(ps, u0);
+                presum_k<L>(ps, u1);
             }
             __builtin_amdgcn_sched_barrier(0);
             cur = nxt;
@@ -588,50 +264,44 @@ __device__ __forceinline__ void run_piece(Acc<NW, F> &acc, PreSum &ps, uint32_t 
         __syncthreads();       // the next piece's DMA reuses the slots
     } else {
         {
-            const lds_u8 *pa = (const lds_u8 *)(uintptr_t)(ring + a_lane);
-            const lds_u8 *pb = (const lds_u8 *)(uintptr_t)(ring + b_lane);
-            read_k<NW>(r0, pa, pb, 0);
-            read_k<NW>(r1, pa, pb, 1);
-            unpack_k<NW, RE_LOW, U, F>(u0, r0);
+            read_k<L>(r0, ring, rl, 0);
+            read_k<L>(r1, ring, rl, 1);
+            unpack_k<L, RE_LOW, U, F>(u0, r0);
         }
         int cur = 0;    // slot of stage s
         for (int s = 0; s < ns; ++s) {
-            const int nxt = cur == NSLOT - 1 ? 0 : cur + 1;
-            const int iss = cur == 0 ? NSLOT - 1 : cur - 1;   // slot of stage s - 1 = s + AHEAD
-            issue_stage<NW>(ring + iss * SLOT, tl, dl, s + AHEAD, wave, lane);
-            const lds_u8 *pa = (const lds_u8 *)(uintptr_t)(ring + cur * SLOT + a_lane);
-            const lds_u8 *pb = (const lds_u8 *)(uintptr_t)(ring + cur * SLOT + b_lane);
-            const lds_u8 *qa = (const lds_u8 *)(uintptr_t)(ring + nxt * SLOT + a_lane);
-            const lds_u8 *qb = (const lds_u8 *)(uintptr_t)(ring + nxt * SLOT + b_lane);
+            const int nxt = cur == L::NSLOT - 1 ? 0 : cur + 1;
+            const int iss = cur == 0 ? L::NSLOT - 1 : cur - 1;   // slot of stage s - 1 = s + L::AHEAD
+            issue_stage<L>(ring + iss * L::SLOT, tl, dl, s + L::AHEAD, wave, lane);
             __builtin_amdgcn_sched_barrier(0);
             // k-step 0
-            read_k<NW>(r0, pa, pb, 2);
-            unpack_k<NW, RE_LOW, U, F>(u1, r1);
-            mfma_k<NW, DIAG>(acc, u0);
-            if constexpr (SUMS) presum_k<NW>(ps, u0);
-            kstep_schedule<NW, DIAG>();
+            read_k<L>(r0, ring + cur * L::SLOT, rl, 2);
+            unpack_k<L, RE_LOW, U, F>(u1, r1);
+            mfma_k<L, DIAG>(acc, u0);
+            if constexpr (SUMS) presum_k<L>(ps, u0);
+            kstep_schedule<L, DIAG>();
             __builtin_amdgcn_sched_barrier(0);
             // k-step 1
-            read_k<NW>(r1, pa, pb, 3);
-            unpack_k<NW, RE_LOW, U, F>(u0, r0);
-            mfma_k<NW, DIAG>(acc, u1);
-            if constexpr (SUMS) presum_k<NW>(ps, u1);
-            kstep_schedule<NW, DIAG>();
+            read_k<L>(r1, ring + cur * L::SLOT, rl, 3);
+            unpack_k<L, RE_LOW, U, F>(u0, r0);
+            mfma_k<L, DIAG>(acc, u1);
+            if constexpr (SUMS) presum_k<L>(ps, u1);
+            kstep_schedule<L, DIAG>();
             __builtin_amdgcn_sched_barrier(0);
             // k-step 2: stage s + 1 must be in LDS before its first read
-            wait_stage_and_sync<NW>();
-            read_k<NW>(r0, qa, qb, 0);
-            unpack_k<NW, RE_LOW, U, F>(u1, r1);
-            mfma_k<NW, DIAG>(acc, u0);
-            if constexpr (SUMS) presum_k<NW>(ps, u0);
-            kstep_schedule<NW, DIAG>();
+            wait_stage_and_sync<L>();
+            read_k<L>(r0, ring + nxt * L::SLOT, rl, 0);
+            unpack_k<L, RE_LOW, U, F>(u1, r1);
+            mfma_k<L, DIAG>(acc, u0);
+            if constexpr (SUMS) presum_k<L>(ps, u0);
+            kstep_schedule<L, DIAG>();
             __builtin_amdgcn_sched_barrier(0);
             // k-step 3
-            read_k<NW>(r1, qa, qb, 1);
-            unpack_k<NW, RE_LOW, U, F>(u0, r0);
-            mfma_k<NW, DIAG>(acc, u1);
-            if constexpr (SUMS) presum_k<NW>(ps, u1);
-            kstep_schedule<NW, DIAG>();
+            read_k<L>(r1, ring + nxt * L::SLOT, rl, 1);
+            unpack_k<L, RE_LOW, U, F>(u0, r0);
+            mfma_k<L, DIAG>(acc, u1);
+            if constexpr (SUMS) presum_k<L>(ps, u1);
+            kstep_schedule<L, DIAG>();
             __builtin_amdgcn_sched_barrier(0);
             cur = nxt;
         }
@@ -644,22 +314,22 @@ __device__ __forceinline__ void run_piece(Acc<NW, F> &acc, PreSum &ps, uint32_t 
 // products would never be stored, so it computes nothing (which also spares
 // the power that work would draw), but it keeps its share of the
 // workgroup's DMA and passes the same barriers as run_piece.
-template <int NW>
+template <typename L>
 __device__ __forceinline__ void idle_piece(uint32_t ring, const Tile &tl, int wave, int lane)
 {
-    const int ns = (tl.t1 - tl.t0 + STAGE - 1) / STAGE;
-    DmaLane<NW> dl;
-    dma_lane_setup<NW>(dl, tl, wave, lane);
+    const int ns = L::TG == 1 ? (tl.t1 - tl.t0 + STAGE - 1) / STAGE : tl.ns;
+    DmaLane<L> dl;
+    dma_lane_setup<L>(dl, tl, wave, lane);
     __builtin_amdgcn_s_waitcnt(XENG_VMCNT(0));
 #pragma unroll
-    for (int d = 0; d < AHEAD; ++d) issue_stage<NW>(ring + d * SLOT, tl, dl, d, wave, lane);
-    wait_stage_and_sync<NW>();
+    for (int d = 0; d < L::AHEAD; ++d) issue_stage<L>(ring + d * L::SLOT, tl, dl, d, wave, lane);
+    wait_stage_and_sync<L>();
     int cur = 0;
     for (int s = 0; s < ns; ++s) {
-        const int iss = cur == 0 ? NSLOT - 1 : cur - 1;
-        issue_stage<NW>(ring + iss * SLOT, tl, dl, s + AHEAD, wave, lane);
-        wait_stage_and_sync<NW>();
-        cur = cur == NSLOT - 1 ? 0 : cur + 1;
+        const int iss = cur == 0 ? L::NSLOT - 1 : cur - 1;
+        issue_stage<L>(ring + iss * L::SLOT, tl, dl, s + L::AHEAD, wave, lane);
+        wait_stage_and_sync<L>();
+        cur = cur == L::NSLOT - 1 ? 0 : cur + 1;
     }
     __builtin_amdgcn_s_waitcnt(XENG_VMCNT(0));
     __syncthreads();
@@ -676,6 +346,15 @@ __device__ __forceinline__ void idle_piece(uint32_t ring, const Tile &tl, int wa
 template <int SHIFT> __device__ __forceinline__ int32_t acc_val(int32_t v) { return v >> SHIFT; }
 template <int SHIFT> __device__ __forceinline__ int32_t acc_val(float v) { return (int32_t)(v * 262144.0f); }
 
+// An accumulator register's bits, and back.
+__device__ __forceinline__ int as_int(int32_t v) { return v; }
+__device__ __forceinline__ int as_int(float v) { return __float_as_int(v); }
+template <bool F> __device__ __forceinline__ auto as_acc(int v)
+{
+    if constexpr (F) return __int_as_float(v);
+    else return v;
+}
+
 template <int SHIFT, typename V>
 __device__ __forceinline__ void flush_atomic(gw64 *blk, const V &re, const V &im)
 {
@@ -688,21 +367,22 @@ __device__ __forceinline__ void flush_atomic(gw64 *blk, const V &re, const V &im
 // The diagonal's stored imaginary parts (-S_j, see the top) of one wave's
 // blocks on the diagonal of tile (ti, ti) into the slot's biases: one lane
 // per input, whichever register holds its pair (j, j).
-template <int NW, int SHIFT>
-__device__ __forceinline__ void add_bias(int32_t *bias, const Acc<NW, false> &acc, int n, int ti, int wa, int cb0,
-                                         int lane)
+template <typename L, int SHIFT>
+__device__ __forceinline__ void add_bias(int32_t *bias, const Acc<L, false> &acc, int n, int ti, int wa, int cb0,
+                                         int lane, int a0, int a1)
 {
     const int dr = diag_reg(lane);
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
+        if (L::TG == 2 && (a < a0 || a >= a1)) continue;
         int32_t v = 0;
-        if constexpr (Layout<NW>::BW == 2) {
+        if constexpr (L::BW == 2) {
             // a 64 x 64 region: its diagonal blocks are (0, 0) and (1, 1)
 #pragma unroll
             for (int r = 0; r < 16; ++r) v = dr == r ? acc.im[a][a][r] : v;
         } else {
 #pragma unroll
-            for (int b = 0; b < Layout<NW>::BW; ++b)
+            for (int b = 0; b < L::BW; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) v = (cb0 + b == 2 * wa + a && dr == r) ? acc.im[a][b][r] : v;
         }
@@ -715,12 +395,14 @@ __device__ __forceinline__ void add_bias(int32_t *bias, const Acc<NW, false> &ac
 // Whole-tile flush of one wave's 2 x BW blocks (column blocks cb0..): stores
 // if the slot holds zeros, else read-modify-write with the loads of a row of
 // blocks issued together (one memory latency per row, not one per value).
-template <int NW, int SHIFT, bool F>
-__device__ __forceinline__ void flush_owned(gw64 *tb, const Acc<NW, F> &acc, int wa, int cb0, bool fresh)
+template <typename L, int SHIFT, bool F>
+__device__ __forceinline__ void flush_owned(gw64 *tb, const Acc<L, F> &acc, int wa, int cb0, bool fresh, int a0 = 0,
+                                            int a1 = 2)
 {
-    constexpr int BW = Layout<NW>::BW;
+    constexpr int BW = L::BW;
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
+        if (L::TG == 2 && (a < a0 || a >= a1)) continue;
         gw64 *blk[BW];
 #pragma unroll
         for (int b = 0; b < BW; ++b) blk[b] = tb + ((2 * wa + a) * BLKS + cb0 + b) * BLOCK_W;
@@ -739,31 +421,59 @@ __device__ __forceinline__ void flush_owned(gw64 *tb, const Acc<NW, F> &acc, int
     }
 }
 
-// Persistent kernel: workgroup w runs pieces [wg_off[w], wg_off[w+1]).  A
-// piece's tile field holds (I, J2): A rows 128 I.., B columns 256 J2.., i.e.
-// accumulator tiles (I, 2 J2) and (I, 2 J2 + 1) where they are in the upper
+// Two time groups: the two waves of a region exchange half of their sums
+// through LDS (`mine`, `other`: 16 KiB each of the ring, which the end of a
+// piece has left free), wave KEEP of the pair ending with the sums of both
+// over row block KEEP of the region.
+template <typename L, int KEEP, bool F> __device__ __forceinline__ void give_half(uint8_t *mine, const Acc<L, F> &acc, int lane)
+{
+#pragma unroll
+    for (int b = 0; b < L::BW; ++b)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const auto &v = q < 4 ? acc.re[1 - KEEP][b] : acc.im[1 - KEEP][b];
+            const int r = 4 * (q & 3);
+            *reinterpret_cast<v4i *>(mine + ((b * 8 + q) * 64 + lane) * 16) =
+                v4i{as_int(v[r]), as_int(v[r + 1]), as_int(v[r + 2]), as_int(v[r + 3])};
+        }
+}
+template <typename L, int KEEP, bool F> __device__ __forceinline__ void take_half(const uint8_t *other, Acc<L, F> &acc, int lane)
+{
+#pragma unroll
+    for (int b = 0; b < L::BW; ++b)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const v4i w = *reinterpret_cast<const v4i *>(other + ((b * 8 + q) * 64 + lane) * 16);
+            auto &v = q < 4 ? acc.re[KEEP][b] : acc.im[KEEP][b];
+            const int r = 4 * (q & 3);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[r + k] += as_acc<F>(w[k]);
+        }
+}
+
+// Persistent kernels: workgroup w runs pieces [wg_off[w], wg_off[w+1]).  A
+// piece's tile field holds (I, J): A rows 128 I.., B columns from 128 L::TILES J,
+// i.e. accumulator tiles (I, L::TILES J ..) where they are in the upper
 // triangle.  U: the unsigned form; F (with U): its FP8 products.
-template <int NW, bool U = false, bool F = false>
-__global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
+template <typename L, bool U, bool F>
+__device__ __forceinline__ void run_workgroup(const KernelArgs &args)
 {
     static_assert(U || !F, "the FP8 form multiplies the unsigned nibbles");
-    using L = Layout<NW>;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     // a prepared batch's device guard refused this launch
     if (args.skip != nullptr && *args.skip != 0) return;
-    // LDS byte address of the ring, wave-uniform (scalar register)
-    const uint32_t ring = (uint32_t)__builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     // wave-uniform, so that everything derived from it stays scalar
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // per-lane parts of the transposed-read addresses (see read_k); the
-    // wave's region adds to them per piece
-    const int grp = lane >> 4, jl = lane & 15;
-    const uint32_t a_lane0 = GRP_A * (grp >> 1) + 128 * (grp & 1) + 8 * jl;
-    const uint32_t b_lane0 = A_STAGE + GRP_B * (grp >> 1) + 128 * (grp & 1) + 8 * jl;
-
+    // the wave's time group, and its place among the group's waves
+    constexpr int GW = L::NW / L::TG;
+    const int tg = L::TG == 1 ? 0 : wave / GW, gw = L::TG == 1 ? wave : wave % GW;
+    // LDS byte address of the time group's part of the ring, wave-uniform
+    // (scalar register)
+    const uint32_t ring = (uint32_t)__builtin_amdgcn_readfirstlane(
+                              (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds) +
+                          tg * L::GROUP;
     // clock probe (measurement only): workgroup 0's start and end
     const bool stamp = args.clock != nullptr && blockIdx.x == 0 && tid == 0;
     if (stamp) {
@@ -782,7 +492,7 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
         jd.nt = __builtin_amdgcn_readfirstlane(jd.nt);
         jd.flags = (uint32_t)__builtin_amdgcn_readfirstlane((int)jd.flags);
         const int tile = __builtin_amdgcn_readfirstlane(pce.tile);
-        const int ti = tile & 0xFFFF, tj2 = (tile >> 16) & 0xFFFF;
+        const int ti = tile & 0xFFFF, tj0 = L::TILES * ((tile >> 16) & 0xFFFF);
         const bool atomic = __builtin_amdgcn_readfirstlane(pce.t1_atomic) < 0;
         Tile tl;
         tl.samples = uniform(jd.samples);
@@ -790,9 +500,11 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
         tl.stride = uniform(jd.stride);
         tl.n = jd.n;
         tl.row0 = __builtin_amdgcn_readfirstlane(ti * WA_ROWS);
-        tl.col0 = __builtin_amdgcn_readfirstlane(tj2 * WB_COLS);
-        tl.t0 = __builtin_amdgcn_readfirstlane(pce.t0);
+        tl.col0 = __builtin_amdgcn_readfirstlane(tj0 * TILE);
+        const int t0 = __builtin_amdgcn_readfirstlane(pce.t0);
+        tl.t0 = t0 + STAGE * tg;
         tl.t1 = __builtin_amdgcn_readfirstlane(pce.t1_atomic & 0x7FFFFFFF);
+        tl.ns = (tl.t1 - t0 + L::ROWS - 1) / L::ROWS;
         // this wave's region: rows 64 wa.. of the A block against column
         // blocks of the B block.  The waves of a workgroup run on SIMD
         // wave % 4.  Where one tile of the window is not in the triangle
@@ -801,19 +513,20 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
         // regions have no work; the region map then puts the other four on
         // four different SIMDs instead of two waves each on two of them,
         // halving the matrix time of such a window's stages.
-        int wa = wave / L::WB_WAVES, wb = wave % L::WB_WAVES;
-        if constexpr (NW == 8) {
-            const int tjl = 2 * tj2, tjr = tjl + 1;
-            const bool vl = tjl >= ti && tjl < jd.nt, vr = tjr >= ti && tjr < jd.nt;
+        int wa = gw / L::WB_WAVES, wb = gw % L::WB_WAVES;
+        if constexpr (L::NW == 8 && L::TILES == 2) {
+            const bool vl = tj0 >= ti && tj0 < jd.nt, vr = tj0 + 1 >= ti && tj0 + 1 < jd.nt;
             if (vr && !vl && wa == 0) wb ^= 2;
             if (vl && !vr && wa == 1) wb ^= 2;
         }
-        const uint32_t a_lane = a_lane0 + 512 * wa, b_lane = b_lane0 + 256 * L::BW * wb;
+        ReadLane<L> rl;
+        read_lane_setup<L>(rl, 4 * wa, 2 * L::BW * wb, A_STAGE, lane);
         // this wave's accumulator tile; a region wholly below the diagonal
         // is neither computed nor stored (the wave stays in step for the
         // workgroup's DMA and barriers)
-        const int tj = 2 * tj2 + wb / (L::WB_WAVES / 2);
-        const int cb0 = (wb % (L::WB_WAVES / 2)) * L::BW;   // first column block in the tile
+        constexpr int PER_TILE = L::WB_WAVES / L::TILES;   // waves across a tile
+        const int tj = tj0 + wb / PER_TILE;
+        const int cb0 = (wb % PER_TILE) * L::BW;   // first column block in the tile
         const bool valid = tj >= ti && tj < jd.nt;
         // rows 64 wa.. of tile ti against columns 32 cb0 .. 32 (cb0 + BW) - 1
         // of tile tj: wholly below the diagonal?
@@ -822,7 +535,7 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
         // exported; small N and the edge tiles of N not a multiple of 256)
         const bool outside = WA_ROWS * ti + 64 * wa >= jd.n || WA_ROWS * tj + BLK * cb0 >= jd.n;
 
-        Acc<NW, F> acc;
+        Acc<L, F> acc;
         PreSum ps = {{0u, 0u}, {0u, 0u}};
 #pragma unroll
         for (int a = 0; a < 2; ++a)
@@ -833,22 +546,22 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
                     acc.re[a][b][r] = 0;
                     acc.im[a][b][r] = 0;
                 }
-        // eight waves: a 64 x 64 region on the diagonal skips its block below it
-        const bool diag = NW == 8 && tj == ti && cb0 == 2 * wa;
+        // a 64 x 64 region on the diagonal skips its block below it
+        const bool diag = L::BW == 2 && tj == ti && cb0 == 2 * wa;
         // a wave whose tile lies past the last tile column (odd tile count)
         // has nothing to compute either
         if (below || outside || tj >= jd.nt)
-            idle_piece<NW>(ring, tl, wave, lane);
+            idle_piece<L>(ring, tl, wave, lane);
         else if (jd.flags & JOB_RE_LOW) {
             if (diag)
-                run_piece<NW, true, true, U, F>(acc, ps, ring, tl, wave, lane, a_lane, b_lane);
+                run_piece<L, true, true, U, F>(acc, ps, ring, tl, wave, lane, rl);
             else
-                run_piece<NW, true, false, U, F>(acc, ps, ring, tl, wave, lane, a_lane, b_lane);
+                run_piece<L, true, false, U, F>(acc, ps, ring, tl, wave, lane, rl);
         } else {
             if (diag)
-                run_piece<NW, false, true, U, F>(acc, ps, ring, tl, wave, lane, a_lane, b_lane);
+                run_piece<L, false, true, U, F>(acc, ps, ring, tl, wave, lane, rl);
             else
-                run_piece<NW, false, false, U, F>(acc, ps, ring, tl, wave, lane, a_lane, b_lane);
+                run_piece<L, false, false, U, F>(acc, ps, ring, tl, wave, lane, rl);
         }
 
         // unsigned form: the diagonal waves of a job's tiles see every A
@@ -875,14 +588,32 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
             }
         }
 
-        if (valid && !below && !outside) {
+        const bool work = valid && !below && !outside;
+        int a0 = 0, a1 = 2;   // row blocks of the region this wave flushes
+        if constexpr (L::TG == 2) {
+            uint8_t *mine = lds + wave * 16384;
+            const uint8_t *other = lds + ((wave + GW) % L::NW) * 16384;
+            if (work) {
+                if (tg == 0) give_half<L, 0, F>(mine, acc, lane);
+                else give_half<L, 1, F>(mine, acc, lane);
+            }
+            __syncthreads();
+            if (work) {
+                if (tg == 0) take_half<L, 0, F>(other, acc, lane);
+                else take_half<L, 1, F>(other, acc, lane);
+            }
+            __syncthreads();   // the next piece's DMA reuses the ring
+            a0 = tg;
+            a1 = tg + 1;
+        }
+        if (work) {
             // the sums carry 256x the values (both operands 16x), or 8x in
             // the unsigned form (the FP8 form's scale is undone in acc_val)
             constexpr int SHIFT = U ? 3 : 8;
             // the unsigned form carries no bias
             if constexpr (!U)
                 if (tj == ti && (L::BW == 4 || diag) && jd.bias != nullptr)
-                    add_bias<NW, SHIFT>(jd.bias, acc, jd.n, ti, wa, cb0, lane);
+                    add_bias<L, SHIFT>(jd.bias, acc, jd.n, ti, wa, cb0, lane, a0, a1);
             const int64_t tile_idx = (int64_t)ti * jd.nt - (int64_t)ti * (ti - 1) / 2 + (tj - ti);
             gw64 *tb = (gw64 *)(jd.acc + tile_idx * TILE_I32) + lane;
             if (atomic) {
@@ -890,6 +621,7 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
                 for (int a = 0; a < 2; ++a)
 #pragma unroll
                     for (int b = 0; b < L::BW; ++b) {
+                        if (L::TG == 2 && (a < a0 || a >= a1)) continue;
                         if (diag && a == 1 && b == 0) continue;   // below the diagonal, never computed
                         flush_atomic<SHIFT>(tb + ((2 * wa + a) * BLKS + cb0 + b) * BLOCK_W, acc.re[a][b],
                                             acc.im[a][b]);
@@ -897,9 +629,9 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
                         __builtin_amdgcn_sched_barrier(0);
                     }
             } else if (jd.flags & JOB_FRESH) {
-                flush_owned<NW, SHIFT, F>(tb, acc, wa, cb0, true);
+                flush_owned<L, SHIFT, F>(tb, acc, wa, cb0, true, a0, a1);
             } else {
-                flush_owned<NW, SHIFT, F>(tb, acc, wa, cb0, false);
+                flush_owned<L, SHIFT, F>(tb, acc, wa, cb0, false, a0, a1);
             }
         }
     }
@@ -909,9 +641,15 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
     }
 }
 
+template <int NW, bool U = false, bool F = false>
+__global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
+{
+    run_workgroup<Layout<NW>, U, F>(args);
+}
+
 }  // namespace dma
 
-constexpr int DMA_LDS_BYTES = dma::NSLOT * dma::SLOT;
+constexpr int DMA_LDS_BYTES = dma::Layout<8>::LDS_BYTES;
 
 // Both instances are built: eight waves (two per SIMD, so one wave's
 // unpack overlaps the other's matrix work) and four (one per SIMD, four
