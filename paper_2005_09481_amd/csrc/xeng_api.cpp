@@ -100,10 +100,9 @@ std::atomic<int> g_plan_order{XENG_PLAN_XCD};
 Plan build_plan(const PlanJob *jobs, int n_jobs, int max_wgs, int min_stages, TileShape shape, int order,
                 int64_t cap = 0)
 {
-    if (cap > 0) return make_plan(jobs, n_jobs, max_wgs, min_stages, shape, cap);
     Plan p;
-    if (order == XENG_PLAN_XCD && n_jobs == 1 && make_plan_xcd(jobs[0], max_wgs, shape, &p)) return p;
-    return make_plan(jobs, n_jobs, max_wgs, min_stages, shape);
+    if (order == XENG_PLAN_XCD && n_jobs == 1 && make_plan_xcd(jobs[0], max_wgs, shape, &p, cap)) return p;
+    return make_plan(jobs, n_jobs, max_wgs, min_stages, shape, cap);
 }
 
 // Launch configuration of one call: the global settings, or what the

@@ -97,7 +97,8 @@ Plan make_plan(const PlanJob *jobs, int n_jobs, int max_wgs, int min_stages, Til
         return plan;
     }
     const int64_t grid = std::max<int64_t>(
-        1, std::min<int64_t>({(int64_t)max_wgs, (total + min_stages - 1) / min_stages,
+        1, std::min<int64_t>({(int64_t)max_wgs,
+                              std::max<int64_t>((total + min_stages - 1) / min_stages, (int64_t)units.size()),
                               (int64_t)units.size() * MAX_UNIT_SPLIT}));
 
     // Smallest per-workgroup budget with which the greedy fill fits in
@@ -236,7 +237,7 @@ int64_t xcd_candidate(const std::vector<int64_t> &wc, int64_t ns, int64_t G, int
 
 }  // namespace
 
-bool make_plan_xcd(const PlanJob &job, int max_wgs, TileShape shape, Plan *out)
+bool make_plan_xcd(const PlanJob &job, int max_wgs, TileShape shape, Plan *out, int64_t cap_override)
 {
     const int64_t G = max_wgs;
     if (G < XCDS || G % XCDS != 0 || job.n <= 0 || job.t <= 0 || shape == TileShape::Narrow) return false;
@@ -244,7 +245,7 @@ bool make_plan_xcd(const PlanJob &job, int max_wgs, TileShape shape, Plan *out)
     const int64_t U = (int64_t)units.size();
     const int64_t ns = (job.t + STAGE - 1) / STAGE;
     const int64_t ovh_st = piece_overhead(shape);
-    const int64_t cap = shape == TileShape::Wide ? MAX_PIECE_STAGES_WIDE : MAX_PIECE_STAGES;
+    const int64_t cap = cap_override > 0 ? cap_override : piece_cap(shape);
     const int col_scale = shape == TileShape::Wide ? 2 : 1;
     std::stable_sort(units.begin(), units.end(), [col_scale](const std::pair<int, int> &a, const std::pair<int, int> &b) {
         return morton((uint32_t)a.first, (uint32_t)(col_scale * a.second)) <
@@ -320,7 +321,8 @@ SinglePlanArgs single_plan(int32_t n, int64_t t, TileShape shape, int max_wgs, i
     const int64_t units = single_units(a);
     const int64_t total = units * single_stages(a);
     a.grid = std::max<int64_t>(
-        1, std::min<int64_t>({(int64_t)max_wgs, (total + min_stages - 1) / min_stages, units * MAX_UNIT_SPLIT}));
+        1, std::min<int64_t>({(int64_t)max_wgs, std::max<int64_t>((total + min_stages - 1) / min_stages, units),
+                              units * MAX_UNIT_SPLIT}));
     auto none = [](int64_t, int32_t, int32_t, int64_t, int64_t, int64_t) {};
     // the budget search of make_plan, over the same unit order (total
     // stages at full cost bound the total cost from above)

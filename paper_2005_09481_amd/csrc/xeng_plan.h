@@ -34,6 +34,10 @@ struct Plan {
 // (I, 2 J2) and (I, 2 J2 + 1), for every I <= 2 J2 + 1 (for I = 2 J2 + 1
 // the left tile lies below the diagonal: the DMA kernel leaves it out).
 // `cap` (stages), when positive, replaces the shape's longest piece.
+// `min_stages` limits how far units are cut, never their number: a unit of
+// fewer stages is still a workgroup's own where there are workgroups left
+// (N = 2048, T = 64: 72 windows of one stage on 72 workgroups 14.5 us, on the
+// 18 that pieces of four stages would make 44).
 Plan make_plan(const PlanJob *jobs, int n_jobs, int max_wgs, int min_stages,
                TileShape shape = TileShape::Square, int64_t cap = 0);
 
@@ -53,10 +57,11 @@ std::vector<std::pair<int, int>> plan_units(int n, TileShape shape);
 // units and share those input rows and columns in its L2.  Every workgroup
 // has one piece, or a few for the tails, as in the linear plan.  Returns
 // false (nothing written) for a grid that is not a multiple of 8 or a job
-// too short for one segment of XCD_MIN_SEGMENT stages per workgroup.
+// too short for one segment of XCD_MIN_SEGMENT stages per workgroup.  `cap`
+// as in make_plan.
 constexpr int XCDS = 8;
 constexpr int64_t XCD_MIN_SEGMENT = 32;
-bool make_plan_xcd(const PlanJob &job, int max_wgs, TileShape shape, Plan *out);
+bool make_plan_xcd(const PlanJob &job, int max_wgs, TileShape shape, Plan *out, int64_t cap = 0);
 
 // Stage-equivalents charged per piece (prologue and flush) by the planners.
 int64_t piece_overhead(TileShape shape);
