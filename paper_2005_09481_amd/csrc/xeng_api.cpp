@@ -27,10 +27,10 @@
 
 namespace xeng {
 // The correlation kernels: general (128 x 128 tiles, any layout), wide
-// (DMA, 128 x 256), narrow (N <= 64, time split over the waves), the
+// (DMA, 128 x 256), tile (DMA, 128 x 128), region (DMA, 64 x 64), narrow (N <= 64, time split over the waves), the
 // general kernel's exact FP8 instance and the wide kernel's (the unsigned
 // form, for batch jobs whose slot pre-sums are set up).
-enum class Kind { General, Wide, Narrow, Fp8, WideFp8 };
+enum class Kind { General, Wide, Narrow, Fp8, WideFp8, Tile, Region };
 
 hipError_t launch_correlate(const KernelArgs &a, int grid, bool aligned, hipStream_t stream);
 hipError_t launch_correlate_unsigned(const KernelArgs &a, int grid, bool aligned, hipStream_t stream);
@@ -41,6 +41,9 @@ hipError_t launch_presum_correct(int32_t *acc, int n, int nt, int64_t n_samples,
                                  const int32_t *si, hipStream_t stream);
 hipError_t launch_correlate_dma(const KernelArgs &a, int grid, int waves, hipStream_t stream);
 hipError_t launch_correlate_dma_unsigned(const KernelArgs &a, int grid, bool fp8, hipStream_t stream);
+hipError_t launch_correlate_region(const KernelArgs &a, int grid, hipStream_t stream);
+hipError_t init_region_kernel();
+hipError_t launch_correlate_tile(const KernelArgs &a, int grid, hipStream_t stream);
 hipError_t launch_correlate_narrow(const KernelArgs &a, int grid, hipStream_t stream);
 hipError_t init_dma_kernel();
 hipError_t launch_dump(const DumpDesc &jd, hipStream_t stream);
@@ -368,7 +371,7 @@ DeviceState *device_state(int device)
     void *scr = nullptr;
     if (hipMemset(st->d_zeros, 0x88, ZERO_BYTES) != hipSuccess ||
         hipMemset(st->d_zeros + ZERO_BYTES, 0x00, ZERO_BYTES) != hipSuccess || hipDeviceSynchronize() != hipSuccess ||
-        init_dma_kernel() != hipSuccess || init_beam_kernel() != hipSuccess ||
+        init_dma_kernel() != hipSuccess || init_region_kernel() != hipSuccess || init_beam_kernel() != hipSuccess ||
         static_scratch_address(&scr) != hipSuccess || !scr) {
         (void)hipFree(st->d_zeros);
         return nullptr;
@@ -386,7 +389,7 @@ std::string plan_key(const PlanJob *jobs, int n_jobs, int max_wgs, int min_stage
     std::string k;
     k.reserve(40 + 16 * (size_t)n_jobs);
     k.append(reinterpret_cast<const char *>(&cap), sizeof cap);
-    k.push_back(shape == TileShape::Wide ? 'w' : 's');
+    k.push_back((char)('0' + (int)shape));
     k.push_back((char)('0' + order));
     k.append(reinterpret_cast<const char *>(&max_wgs), sizeof max_wgs);
     k.append(reinterpret_cast<const char *>(&min_stages), sizeof min_stages);
@@ -469,12 +472,14 @@ int cache_plan(DeviceState *st, const std::string &key, const Plan &plan, Device
 }
 
 // Look up (or build, upload and cache) the plan for these job sizes.
+// `wgs`, when positive, replaces the workgroups of the shape.
 // Called with st->mu held and the device current.
 int get_plan(DeviceState *st, const PlanJob *jobs, int n_jobs, TileShape shape, const Tuning &tu,
-             DevicePlan *out, int64_t cap = 0)
+             DevicePlan *out, int64_t cap = 0, int wgs = 0)
 {
     int max_wgs, min_stages;
     plan_limits(st, shape, tu, &max_wgs, &min_stages);
+    if (wgs > 0) max_wgs = wgs;
     const std::string key = plan_key(jobs, n_jobs, max_wgs, min_stages, shape, tu.order, cap);
     if (find_plan(st, key, out)) return XENG_OK;
     return cache_plan(st, key, build_plan(jobs, n_jobs, max_wgs, min_stages, shape, tu.order, cap), out);
@@ -690,7 +695,23 @@ TileShape shape_of(Kind k)
 {
     return k == Kind::Wide || k == Kind::WideFp8 ? TileShape::Wide
            : k == Kind::Narrow                   ? TileShape::Narrow
+           : k == Kind::Tile                     ? TileShape::Tile
+           : k == Kind::Region                   ? TileShape::Region
                                                  : TileShape::Square;
+}
+
+// The kernel of one job read by DMA, and the workgroups to plan it for (0:
+// the shape's).  The four-wave instance is the wide kernel's.
+struct Choice {
+    Kind kind;
+    int wgs;
+};
+Choice dma_choice(const DeviceState *st, const PlanJob &pj, const Tuning &tu)
+{
+    if (tu.kernel != XENG_KERNEL_AUTO) return Choice{Kind::Wide, 0};
+    const DmaChoice c = choose_dma(pj.n, pj.t, st->cu_count, std::max(1, tu.min_stages));
+    return Choice{c.shape == TileShape::Region ? Kind::Region : c.shape == TileShape::Tile ? Kind::Tile : Kind::Wide,
+                  c.wgs};
 }
 
 // Longest piece of a kernel, in stages (0: its shape's default).  The FP8
@@ -706,6 +727,8 @@ hipError_t launch(const KernelArgs &a, int32_t grid, Kind kind, int waves, uint3
 {
     if (kind == Kind::Wide) return launch_correlate_dma(a, grid, waves, stream);
     if (kind == Kind::Narrow) return launch_correlate_narrow(a, grid, stream);
+    if (kind == Kind::Region) return launch_correlate_region(a, grid, stream);
+    if (kind == Kind::Tile) return launch_correlate_tile(a, grid, stream);
     if (kind == Kind::Fp8) return launch_correlate_fp8(a, grid, (flags_and & JOB_ALIGNED8) != 0, stream);
     if (kind == Kind::WideFp8) return launch_correlate_dma_unsigned(a, grid, true, stream);
     return launch_correlate(a, grid, (flags_and & JOB_ALIGNED8) != 0, stream);
@@ -777,15 +800,15 @@ int correlate_padded(xeng_ctx *ctx, int32_t slot, const uint8_t *samples, int64_
         a.jobs = nullptr;
         a.zeros = ctx->st->d_zeros;
         a.clock = ctx->st->clock.load();
-        // the wide kernel, unless the tuning asks for the general one
+        // a DMA kernel, unless the tuning asks for the general one
         const bool dma = tu.kernel != XENG_KERNEL_GENERAL;
         PlanJob pj{ctx->n, tc};
         DevicePlan dp;
-        if ((rc = get_plan(ctx->st, &pj, 1, dma ? TileShape::Wide : TileShape::Square, tu, &dp)) != XENG_OK) break;
+        const Choice ch = dma ? dma_choice(ctx->st, pj, tu) : Choice{Kind::General, 0};
+        if ((rc = get_plan(ctx->st, &pj, 1, shape_of(ch.kind), tu, &dp, 0, ch.wgs)) != XENG_OK) break;
         a.pieces = dp.d_pieces;
         a.wg_off = dp.d_off;
-        if ((e = launch(a, dp.grid, dma ? Kind::Wide : Kind::General, dma_waves(tu), a.job0.flags, stream)) !=
-            hipSuccess) {
+        if ((e = launch(a, dp.grid, ch.kind, dma_waves(tu), a.job0.flags, stream)) != hipSuccess) {
             rc = map_err(e);
             break;
         }
@@ -843,6 +866,7 @@ int validate_jobs(const xeng_job *jobs, int32_t n_jobs, int64_t launches, bool m
 struct Part {
     Kind kind = Kind::General;
     uint32_t flags_and = ~0u;
+    int wgs = 0;   // workgroups to plan for (0: the shape's)
     std::vector<PlanJob> pj;
     std::vector<JobDesc> descs;
 };
@@ -900,21 +924,34 @@ bool any_dma_job(const JobList &jl)
     return false;
 }
 
+// (A batch of one job takes the kernel a single call would: several wide
+// jobs share the wide kernel's launch, whose owned tiles flush without
+// atomics.)
 std::vector<Part> split_by_kernel(const JobList &jl, const Tuning &tu)
 {
-    Part by_kind[5];
+    Part by_kind[7];
     by_kind[(int)Kind::Wide].kind = Kind::Wide;
     by_kind[(int)Kind::Narrow].kind = Kind::Narrow;
+    by_kind[(int)Kind::Tile].kind = Kind::Tile;
+    by_kind[(int)Kind::Region].kind = Kind::Region;
     by_kind[(int)Kind::Fp8].kind = Kind::Fp8;
     by_kind[(int)Kind::WideFp8].kind = Kind::WideFp8;
     for (size_t k = 0; k < jl.descs.size(); ++k) {
-        Part &p = by_kind[(int)kind_of(jl.descs[k], tu)];
+        Kind kind = kind_of(jl.descs[k], tu);
+        int wgs = 0;
+        if (kind == Kind::Wide && jl.descs.size() == 1) {
+            const Choice ch = dma_choice(jl.st, jl.pj[k], tu);
+            kind = ch.kind;
+            wgs = ch.wgs;
+        }
+        Part &p = by_kind[(int)kind];
+        p.wgs = wgs;
         p.pj.push_back(jl.pj[k]);
         p.descs.push_back(jl.descs[k]);
         p.flags_and &= jl.descs[k].flags;
     }
     std::vector<Part> parts;
-    for (Kind k : {Kind::Wide, Kind::Narrow, Kind::General, Kind::Fp8, Kind::WideFp8})
+    for (Kind k : {Kind::Wide, Kind::Tile, Kind::Region, Kind::Narrow, Kind::General, Kind::Fp8, Kind::WideFp8})
         if (!by_kind[(int)k].descs.empty()) parts.push_back(std::move(by_kind[(int)k]));
     return parts;
 }
@@ -974,6 +1011,7 @@ int run_parts(DeviceState *st, const std::vector<Part> &parts, const Tuning &tu,
         const TileShape shape = shape_of(part.kind);
         int max_wgs, min_stages;
         plan_limits(st, shape, tu, &max_wgs, &min_stages);
+        if (part.wgs > 0) max_wgs = part.wgs;
         const std::string key =
             plan_key(part.pj.data(), (int)part.pj.size(), max_wgs, min_stages, shape, tu.order, cap_of(part.kind));
         std::shared_ptr<const Plan> plan;
@@ -1242,11 +1280,12 @@ int xeng_correlate(xeng_ctx *ctx, int32_t slot, const uint8_t *d_samples, int64_
     const Kind kind = kind_of(a.job0, tu);
     if (kind == Kind::General && tu.kernel != XENG_KERNEL_GENERAL && ctx->n >= PAD_MIN_N)
         return correlate_padded(ctx, slot, d_samples, n_samples, row_stride, tu, stream);
-    rc = get_plan(ctx->st, &pj, 1, shape_of(kind), tu, &dp, cap_of(kind));
+    const Choice ch = kind == Kind::Wide ? dma_choice(ctx->st, pj, tu) : Choice{kind, 0};
+    rc = get_plan(ctx->st, &pj, 1, shape_of(ch.kind), tu, &dp, cap_of(ch.kind), ch.wgs);
     if (rc != XENG_OK) return rc;
     a.pieces = dp.d_pieces;
     a.wg_off = dp.d_off;
-    hipError_t e = launch(a, dp.grid, kind, dma_waves(tu), a.job0.flags, stream);
+    hipError_t e = launch(a, dp.grid, ch.kind, dma_waves(tu), a.job0.flags, stream);
     if (e != hipSuccess) return map_err(e);
     ctx->acc_t[(size_t)slot] += n_samples;
     return map_err(publish_count(ctx, slot, stream));
@@ -1741,11 +1780,11 @@ int xeng_batch_create(const xeng_job *jobs, int32_t n_jobs, xeng_batch **out)
     }
     for (const Part &part : split_by_kernel(jl, tu)) {
         const TileShape shape = shape_of(part.kind);
-        const int per_cu = shape == TileShape::Square   ? std::max(1, tu.wgs_per_cu)
-                           : part.kind == Kind::Narrow ? NARROW_WGS_PER_CU
-                                                       : 1;
-        const Plan plan = build_plan(part.pj.data(), (int)part.pj.size(), jl.st->cu_count * per_cu,
-                                     std::max(1, tu.min_stages), shape, tu.order, cap_of(part.kind));
+        int max_wgs, min_stages;
+        plan_limits(jl.st, shape, tu, &max_wgs, &min_stages);
+        if (part.wgs > 0) max_wgs = part.wgs;
+        const Plan plan = build_plan(part.pj.data(), (int)part.pj.size(), max_wgs, min_stages, shape, tu.order,
+                                     cap_of(part.kind));
         xeng_batch::Launch l{part.kind, dma_waves(tu), part.flags_and, plan.grid, nullptr, nullptr, nullptr};
         b->launches.push_back(l);
         xeng_batch::Launch &lb = b->launches.back();

@@ -36,6 +36,17 @@
 // instructions holds the issuing wave for tens of cycles per instruction.
 // Regions and blocks wholly below the diagonal are not computed.
 //
+// The tile kernel (xcorr_tile) is the same code on 128 x 128 tiles: the wave
+// of a 64 x 64 quarter is a pair, each taking every other 64 samples, whose
+// sums meet in LDS at the end of a piece.  A workgroup then flushes half as
+// much as the wide kernel's, no window has idle quarters left of the
+// diagonal, and jobs of few tiles cut into fewer pieces; its operands cost a
+// third more LDS DMA per product.  Correlation alone, wide kernel / tile
+// kernel: N = 2048, T = 1024 42 / 20 us, T = 8192 79 / 67, T = 16384 121 /
+// 112, T = 32768 202 / 204; N = 1008, T = 32768 79 / 69.  Bound at these
+// sizes by its shared pieces' atomic flushes (N = 1024, T = 16384 46 us, 26
+// with the flush left out), past T = 32768 by power, like the wide kernel.
+//
 // LDS stage layout: the A side, then the B side, each row-major by time row
 // with the 16-byte chunks of a row permuted (swizzle, xeng_dma_ops.h).  Every
 // DMA instruction then reads whole rows of its side, 128 or 256 contiguous
@@ -85,6 +96,10 @@ template <int NWAVES, int TIMES, int COLS, int SLOTS, int DMA> struct Shape {
 // is left to one wave per SIMD (the other wave's MFMAs then run while the
 // issuing wave waits to issue).
 template <int NW> using Layout = Shape<NW, 1, 256, 6, 4>;
+// The tile kernel: 128 x 128, four waves for each half of a 128-sample slot,
+// five 32 KB slots (four measured the same).
+using TileLayout = Shape<8, 2, 128, 5, 4>;
+
 struct Tile {
     const uint8_t *samples;
     const uint8_t *zeros;   // 16 bytes of zero samples (0x88)
@@ -647,6 +662,13 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
     run_workgroup<Layout<NW>, U, F>(args);
 }
 
+// The tile kernel: 128 x 128 tiles, each quarter's time split over two waves.
+template <bool U = false, bool F = false>
+__global__ __launch_bounds__(64 * TileLayout::NW, 1) void xcorr_tile(KernelArgs args)
+{
+    run_workgroup<TileLayout, U, F>(args);
+}
+
 }  // namespace dma
 
 constexpr int DMA_LDS_BYTES = dma::Layout<8>::LDS_BYTES;
@@ -671,7 +693,17 @@ hipError_t init_dma_kernel()
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void *)dma::xcorr_dma<8, true, true>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, DMA_LDS_BYTES);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)dma::xcorr_tile<>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                dma::TileLayout::LDS_BYTES);
     return e;
+}
+
+hipError_t launch_correlate_tile(const KernelArgs &a, int grid, hipStream_t stream)
+{
+    if (grid <= 0) return hipSuccess;
+    hipLaunchKernelGGL(dma::xcorr_tile<>, dim3(grid), dim3(64 * dma::TileLayout::NW), dma::TileLayout::LDS_BYTES, stream, a);
+    return hipGetLastError();
 }
 
 // The unsigned form (pre-sum path): eight waves, int8 or (fp8) FP8

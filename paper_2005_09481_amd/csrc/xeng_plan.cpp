@@ -14,7 +14,11 @@ std::vector<std::pair<int, int>> plan_units(int n, TileShape shape)
     const int nt = n_tiles_side(n);
     if (shape == TileShape::Narrow) {
         u.emplace_back(0, 0);
-    } else if (shape == TileShape::Square) {
+    } else if (shape == TileShape::Region) {
+        const int nr = (n + REGION - 1) / REGION;
+        for (int ri = 0; ri < nr; ++ri)
+            for (int rj = ri; rj < nr; ++rj) u.emplace_back(ri, rj);
+    } else if (shape != TileShape::Wide) {
         for (int ti = 0; ti < nt; ++ti)
             for (int tj = ti; tj < nt; ++tj) u.emplace_back(ti, tj);
     } else {
@@ -28,8 +32,18 @@ std::vector<std::pair<int, int>> plan_units(int n, TileShape shape)
 // Cost of a piece beyond its stages, in stage units: its prologue (the
 // first stages' loads are not yet overlapped) and its flush of the tile's
 // accumulators to memory.  Measured on the DMA kernel's 128 x 256 tiles at
-// about 16 stage times; a 128 x 128 tile flushes half as much.
-int64_t piece_overhead(TileShape shape) { return shape == TileShape::Wide ? 16 : 8; }
+// about 16 stage times; a 128 x 128 tile of the general kernel flushes half
+// as much.  The tile kernel's stages take half as long (24 measured best of
+// 8 to 40), the region kernel's a fifth (40 best of 24 to 64).
+int64_t piece_overhead(TileShape shape)
+{
+    switch (shape) {
+    case TileShape::Wide: return 16;
+    case TileShape::Tile: return 24;
+    case TileShape::Region: return 40;
+    default: return 8;
+    }
+}
 
 int64_t piece_cap(TileShape shape) { return shape == TileShape::Square ? MAX_PIECE_STAGES : MAX_PIECE_STAGES_WIDE; }
 
@@ -305,6 +319,69 @@ bool make_plan_xcd(const PlanJob &job, int max_wgs, TileShape shape, Plan *out, 
     plan.grid = (int32_t)G;
     *out = std::move(plan);
     return true;
+}
+
+namespace {
+
+// Time model of a shape's kernel on one job (microseconds): per stage,
+// prologue and flush of a piece that owns its unit, prologue of a shared
+// one, and the share of one shared piece in the atomic flushes, which all
+// workgroups' together move at about 2 TB/s.
+struct ShapeCost {
+    TileShape shape;
+    double stage, owned, prologue, shared;
+};
+constexpr double LAUNCH_US = 4.0;
+
+// Stage times rise with the length of the work: the clock settles under the
+// load, and the region kernel's operands outgrow what the L2s hold.
+double stage_us(const ShapeCost &c, double stages_per_wg, int64_t units)
+{
+    if (c.shape == TileShape::Tile && stages_per_wg > 100) return 0.66;
+    if (c.shape == TileShape::Region && stages_per_wg > 100 && units > 210) return 0.35;
+    if (c.shape == TileShape::Region && stages_per_wg > 160) return 0.22;
+    return c.stage;
+}
+
+}  // namespace
+
+DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages)
+{
+    static const ShapeCost costs[] = {{TileShape::Wide, 1.1, 13.0, 5.0, 0.13},
+                                      {TileShape::Tile, 0.62, 8.0, 3.0, 0.065},
+                                      {TileShape::Region, 0.20, 4.3, 3.0, 0.016}};
+    const int64_t ns = std::max<int64_t>(1, (t + STAGE - 1) / STAGE);
+    const int64_t nt = n_tiles_side(n), nr = (n + REGION - 1) / REGION;
+    DmaChoice best{TileShape::Wide, 0};
+    double best_us = -1.0;
+    auto consider = [&](TileShape shape, int64_t wgs, double us) {
+        if (best_us < 0.0 || us < best_us) {
+            best_us = us;
+            best = DmaChoice{shape, (int)wgs};
+        }
+    };
+    for (const ShapeCost &c : costs) {
+        int64_t units = tri64(nr);
+        if (c.shape == TileShape::Tile) units = tri64(nt);
+        if (c.shape == TileShape::Wide) {
+            units = 0;
+            for (int64_t i = 0; i < nt; ++i) units += (nt + 1) / 2 - i / 2;
+        }
+        // every unit whole, or in k equal pieces
+        for (int64_t k = 1; k * units <= cus && k <= MAX_UNIT_SPLIT && (k == 1 || k * min_stages <= ns); ++k) {
+            const int64_t s = (ns + k - 1) / k;
+            const double st = (double)s * stage_us(c, (double)s, units);
+            consider(c.shape, k * units,
+                     LAUNCH_US + st + (k == 1 ? c.owned : c.prologue + (double)(k * units) * c.shared));
+        }
+        // the work in equal shares of every workgroup; a job of fewer units
+        // than compute units has been seen above unless it is long enough
+        const double s = (double)units * (double)ns / cus;
+        if (units * MAX_UNIT_SPLIT >= cus && units * ns >= (int64_t)cus * min_stages)
+            consider(c.shape, 0,
+                     LAUNCH_US + s * stage_us(c, s, units) + c.owned * (double)units / cus + cus * c.shared);
+    }
+    return best;
 }
 
 SinglePlanArgs single_plan(int32_t n, int64_t t, TileShape shape, int max_wgs, int min_stages, int64_t *n_pieces,

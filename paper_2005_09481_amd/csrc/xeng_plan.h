@@ -29,7 +29,8 @@ struct Plan {
 // A tile cut into several pieces is marked atomic.  Every (i <= j, t) of
 // every job is covered by exactly one piece.
 //
-// Square: units are the tiles (ti <= tj) of 128 x 128.  Wide: units are
+// Square and Tile: units are the tiles (ti <= tj) of 128 x 128.  Region: the
+// 64 x 64 regions.  Wide: units are
 // workgroup tiles (I, J2) of 128 rows x 256 columns, i.e. accumulator tiles
 // (I, 2 J2) and (I, 2 J2 + 1), for every I <= 2 J2 + 1 (for I = 2 J2 + 1
 // the left tile lies below the diagonal: the DMA kernel leaves it out).
@@ -69,6 +70,26 @@ int64_t piece_overhead(TileShape shape);
 // stay exact (the general kernel's B operands carry 16x the samples, the
 // DMA and narrow kernels' A and B operands both do).
 int64_t piece_cap(TileShape shape);
+
+// The shape of one job that the DMA kernels read (N > NARROW_MAX_N), and the
+// workgroups to plan it for (0: one per compute unit): the smallest of the
+// modelled times of the wide, tile and region kernels, each with its units
+// whole, in equal pieces, or in equal shares of every workgroup.  The model's
+// constants come from a sweep of N from 80 to 4096 and T from 64 to 65536.
+// Where it draws the lines, with both sides measured (correlation alone):
+// N = 1024, T = 16384 region 41, tile 48, wide 61 us; T = 32768 region 75,
+// tile 69, wide 81; N = 2048, T = 512 region 25, tile 16 (whole tiles), wide
+// 30; T = 16384 tile 112, wide 121; T = 32768 tile 204, wide 202; T = 65536
+// tile 404, wide 368; N = 3072, T = 512 tile 44, wide 25 (whole windows).
+// What decides between whole units and shares is the flush: shares of a tile
+// meet on the same words, and all atomic flushes together ran at some 2 TB/s
+// whatever their order and placement (N = 2048, T = 2048: 28 us in 136 whole
+// tiles, 36 in 256 shares).
+struct DmaChoice {
+    TileShape shape;
+    int wgs;
+};
+DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages);
 
 // Plan parameters of one job as make_plan would choose them (grid and
 // budget), for the container-free planner of xeng_plan_single.h; also the

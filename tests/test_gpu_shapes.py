@@ -1,0 +1,56 @@
+"""The DMA kernels' shapes on the GPU at sizes where each is chosen: the
+region kernel (64 x 64 regions, time split over eight waves), the tile kernel
+(128 x 128 tiles, two time groups), the wide kernel, each with whole units
+and with shared ones, at the edges of half stages, stages, regions and tiles.
+Small cases against the oracle, larger ones against the scalar reference
+kernel; repeated integrations and both nibble orders."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from paper_2005_09481_amd import xeng
+
+pytestmark = pytest.mark.gpu
+
+
+def host(t):
+    return t.cpu().numpy().astype(np.int64)
+
+
+@pytest.mark.parametrize("n", [80, 112, 128, 144, 192, 208, 320])
+@pytest.mark.parametrize("t", [1, 31, 32, 33, 64, 65, 127, 129, 255, 257, 700])
+def test_small_jobs_match_oracle(n, t):
+    x = synth.uniform_bytes(n, t, seed=[n, t])
+    d = torch.from_numpy(x).cuda()
+    ref = oracle.correlate(x)
+    for re_low in (False, True):
+        c = xeng.Correlator(n, 1, re_low=re_low)
+        want = oracle.correlate(x, re_low=re_low) if re_low else ref
+        c.correlate(0, d)
+        assert np.array_equal(host(c.dump(0, reset=False)), want)
+        c.correlate(0, d)              # into a slot that no longer holds zeros
+        xeng.correlate_batch([(c, 0, d)])
+        assert np.array_equal(host(c.dump(0)), 3 * want)
+        c.close()
+
+
+@pytest.mark.parametrize("n,t", [(512, 8192), (768, 3000), (1008, 4100), (1024, 20000), (1024, 33000), (1280, 1500),
+                                 (1536, 5000), (1536, 9000), (2048, 100), (2048, 512), (2048, 1025), (2048, 3000),
+                                 (2064, 9000), (3072, 700), (1000, 33000), (777, 6000)])
+def test_larger_jobs_match_reference(n, t):
+    g = torch.Generator(device="cuda").manual_seed(n * 7 + t)
+    x = torch.randint(0, 256, (t, n), dtype=torch.uint8, device="cuda", generator=g)
+    for re_low in (False, True):
+        ref = xeng.correlate_reference(x, re_low=re_low)
+        c = xeng.Correlator(n, 1, re_low=re_low)
+        c.correlate(0, x)
+        assert torch.equal(c.dump(0, reset=False), ref)
+        c.correlate(0, x)
+        assert torch.equal(c.dump(0), 2 * ref)
+        b = xeng.Batch([(c, 0, x)])
+        b.launch()
+        assert torch.equal(c.dump(0), ref)
+        b.close()
+        c.close()
