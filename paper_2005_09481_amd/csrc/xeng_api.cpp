@@ -62,15 +62,15 @@ hipError_t launch_batch_guard(const GuardJob *d_jobs, int n_jobs, int32_t *d_ski
                               hipStream_t stream);
 hipError_t launch_set_count(int64_t *p, int64_t v, hipStream_t stream);
 hipError_t static_scratch_address(void **ptr);
-hipError_t init_beam_kernel();
 double ceiling_macs(int grid, int iters);
 int ceiling_threads();
 hipError_t launch_mfma_ceiling(int grid, int iters, int32_t *out, int64_t *clk, bool stamp_start, bool stamp_end,
                                hipStream_t stream);
+hipError_t init_beam_kernel();
 int64_t beam_image_bytes(int n);
 void beam_image(const int8_t *w, int n, int n_beams, uint8_t *img);
 hipError_t launch_beamform(const uint8_t *s, int64_t n_samples, int n, int64_t stride, uint32_t re_low,
-                           const int8_t *d_w, int n_beams, int shift, void *out, int grid, hipStream_t stream);
+                           const int8_t *d_w, int n_beams, int shift, void *out, int cus, hipStream_t stream);
 hipError_t launch_sk_flags(const uint8_t *s, int64_t n_samples, int n, int64_t stride, uint32_t re_low,
                            int block_len, int64_t lo_num, int64_t hi_num, int64_t den, uint8_t *flags,
                            hipStream_t stream);
@@ -371,7 +371,8 @@ DeviceState *device_state(int device)
     void *scr = nullptr;
     if (hipMemset(st->d_zeros, 0x88, ZERO_BYTES) != hipSuccess ||
         hipMemset(st->d_zeros + ZERO_BYTES, 0x00, ZERO_BYTES) != hipSuccess || hipDeviceSynchronize() != hipSuccess ||
-        init_dma_kernel() != hipSuccess || init_region_kernel() != hipSuccess || init_beam_kernel() != hipSuccess ||
+        init_dma_kernel() != hipSuccess || init_region_kernel() != hipSuccess ||
+        init_beam_kernel() != hipSuccess ||
         static_scratch_address(&scr) != hipSuccess || !scr) {
         (void)hipFree(st->d_zeros);
         return nullptr;
@@ -2155,10 +2156,8 @@ int xeng_beamform(xeng_beams *bm, const uint8_t *d_samples, int64_t n_samples, i
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int rc = refuse_capture(stream);
     if (rc != XENG_OK) return rc;
-    const int64_t blocks = (n_samples + 127) / 128;      // row blocks of the kernel
-    const int grid = (int)std::min<int64_t>(blocks, bm->cu_count);
     return map_err(launch_beamform(d_samples, n_samples, bm->n, row_stride, (bm->flags & XENG_NIBBLE_RE_LOW) ? 1u : 0u,
-                                   reinterpret_cast<const int8_t *>(bm->d_w), bm->n_beams, shift, d_out, grid,
+                                   reinterpret_cast<const int8_t *>(bm->d_w), bm->n_beams, shift, d_out, bm->cu_count,
                                    stream));
 }
 
