@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 
 #include "xeng_internal.h"
+#include "xeng_rows.h"
 
 namespace xeng {
 
@@ -56,46 +57,17 @@ __device__ __forceinline__ void unpack4(uint32_t w, bool re_low, uint32_t (&a_re
     a_im[1] = __builtin_amdgcn_perm(re, im, 0x07030602u);
 }
 
-typedef unsigned int bu4 __attribute__((ext_vector_type(4)));
-typedef unsigned int bu4_u __attribute__((ext_vector_type(4), aligned(1)));
+typedef row16 bu4;
 
-// 16 inputs i0 .. of a row of which inputs below `end` exist (zero samples
-// or anything past it: the weights there are zero).  The last lane of a row
-// whose end is no multiple of 16 reads the 16 bytes that end there and
-// shifts its own down, so no load passes the row's inputs; `before`: inputs
-// of the row that lie before `row` (earlier chunks).
+// 16 inputs i0 .. of a row of which inputs below `end` exist (anything past
+// it: the weights there are zero); `before`: inputs of the row that lie
+// before `row` (earlier chunks).
 template <bool VEC>
 __device__ __forceinline__ bu4 load16(const uint8_t *row, int i0, int end, int before)
 {
-    bu4 v = {0x88888888u, 0x88888888u, 0x88888888u, 0x88888888u};
-    if (i0 >= end) return v;
-    if (VEC) return *reinterpret_cast<const bu4 *>(row + i0);
-    const int past = i0 + 16 - end;   // bytes of the 16 that do not exist
-    if (past <= 0) return *reinterpret_cast<const bu4_u *>(row + i0);
-    if (i0 + before >= past) {
-        const bu4 x = *reinterpret_cast<const bu4_u *>(row + i0 - past);
-        const uint32_t d[8] = {x.x, x.y, x.z, x.w, 0u, 0u, 0u, 0u};
-        const int q = past >> 2, sh = past & 3;
-        uint32_t o[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            // dwords k + q and k + q + 1 of d, without dynamic indexing
-            uint32_t lo = d[k], hi = d[k + 1];
-#pragma unroll
-            for (int u = 1; u < 4; ++u) {
-                lo = q == u ? d[k + u] : lo;
-                hi = q == u ? d[k + u + 1] : hi;
-            }
-            o[k] = (uint32_t)((((uint64_t)hi << 32) | lo) >> (8 * sh));
-        }
-        return bu4{o[0], o[1], o[2], o[3]};
-    }
-    // fewer than 16 inputs in all
-    uint32_t x[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-        if (i0 + k < end) x[k >> 2] = (x[k >> 2] & ~(0xFFu << (8 * (k & 3)))) | ((uint32_t)row[i0 + k] << (8 * (k & 3)));
-    return bu4{x[0], x[1], x[2], x[3]};
+    if (!VEC) return load_row16(row, i0, end, before);
+    if (i0 >= end) return bu4{0x88888888u, 0x88888888u, 0x88888888u, 0x88888888u};
+    return *reinterpret_cast<const bu4 *>(row + i0);
 }
 
 // Two k-steps (16 inputs of the lane's row) into both accumulators.

@@ -22,7 +22,10 @@
 // both sides stay below 2^58 for thresholds up to 16.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "xeng_internal.h"
+#include "xeng_rows.h"
 
 namespace xeng {
 
@@ -46,62 +49,112 @@ __device__ __forceinline__ uint8_t sk_decide(int32_t s1, int32_t s2, int m, int6
     return (num * den < lo_num * dd || num * den > hi_num * dd) ? 1 : 0;
 }
 
-// Vector form: 16-byte-aligned rows with N % 16 == 0.  A workgroup takes
-// 1024 inputs x one block: lane l of wave w loads the 16 inputs 16 l .. of
-// rows w, w + 4, ... of the block (16-byte loads, a wave reading 1 KB
-// contiguous per row), sums them, and the four waves' sums meet in LDS.
-__global__ __launch_bounds__(256) void sk_flags_vec(const uint8_t *__restrict__ s, int64_t n_samples, int n,
-                                                    int64_t stride, uint32_t re_low, int block_len, int64_t lo_num,
-                                                    int64_t hi_num, int64_t den, uint8_t *__restrict__ flags)
+// Squares of the offset-decoded nibbles u - 8 of four bytes each holding one
+// nibble's low three bits in `idx` (0..7) and, in `top`, 0xFF where its bit 3
+// is set: (idx)^2 there, else (idx - 8)^2, by byte permutes of two 8-entry
+// tables.
+__device__ __forceinline__ uint32_t nib_squares(uint32_t idx, uint32_t top)
 {
-    __shared__ int32_t red[4][1024][2];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i0 = 1024 * (int)blockIdx.x + 16 * lane;
+    const uint32_t pos = __builtin_amdgcn_perm(0x31241910u, 0x09040100u, idx);   // 0 1 4 9 16 25 36 49
+    const uint32_t neg = __builtin_amdgcn_perm(0x01040910u, 0x19243140u, idx);   // 64 49 36 25 16 9 4 1
+    return (pos & top) | (neg & ~top);
+}
+
+// Four samples of one input (a byte each): their powers' sums into s1, s2.
+// A byte permute with selectors 8..11 replicates the sign bits of bytes 1, 3,
+// 5 and 7 of its two sources; with the word and the word shifted up a byte
+// those are the four bytes' top bits.
+__device__ __forceinline__ void power_sums4(uint32_t x, uint32_t &s1, uint32_t &s2)
+{
+    constexpr uint32_t TOP = 0x0B090A08u;
+    const uint32_t hi = nib_squares((x >> 4) & 0x07070707u, __builtin_amdgcn_perm(x, x << 8, TOP));
+    const uint32_t lo = nib_squares(x & 0x07070707u, __builtin_amdgcn_perm(x << 4, x << 12, TOP));
+    const uint32_t p = hi + lo;   // at most 128 in a byte
+    s1 = __builtin_amdgcn_udot4(p, 0x01010101u, s1, false);
+    s2 = __builtin_amdgcn_udot4(p, p, s2, false);
+}
+
+// A workgroup takes 16 CW inputs x one block of rows, any alignment and N >=
+// 16: a lane holds a chunk of 16 inputs (the row's last 16 for a chunk that
+// would pass its end: those inputs' sums are then formed twice, alike) and
+// takes four rows at a time, one 16-byte load each, transposed by byte
+// permutes so that a register holds four samples of one input.  The 64 / CW
+// row groups of every wave take the block's row quads in turn; their sums
+// meet in LDS by atomic adds, and one thread per input takes the exact
+// decision.
+//
+// Bound by HBM: every sample byte is read once, at 4.8 integer operations a
+// sample (one sample per operation and input before: some ten).  N = 2048, T =
+// 32768, 256-sample blocks (67 MB): 27.3 -> 18.3 us = 3.7 TB/s (eight waves a
+// workgroup 18.3, four 21.1, two 32.6: one workgroup per CU there, whose first
+// loads and last sums nothing overlaps); N = 500 (unaligned rows, byte loads
+// before), T = 8192: 41 -> 8.8 us.
+template <int CW>
+__global__ __launch_bounds__(1024) void sk_flags_vec(const uint8_t *__restrict__ s, int64_t n_samples, int n,
+                                                     int64_t stride, int block_len, int64_t lo_num, int64_t hi_num,
+                                                     int64_t den, uint8_t *__restrict__ flags)
+{
+    constexpr int GROUPS = 64 / CW;
+    __shared__ uint32_t sum[32 * CW];   // [S1, S2][input of a chunk][chunk]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const int c = lane % CW, c0 = CW * (int)blockIdx.x;
     const int64_t b = blockIdx.y;
     const int64_t t0 = b * block_len;
-    const int64_t t1 = t0 + block_len < n_samples ? t0 + block_len : n_samples;
-    const int sh_re = re_low ? 0 : 4, sh_im = re_low ? 4 : 0;
-    int32_t s1[16], s2[16];
+    const int m = (int)(t0 + block_len < n_samples ? block_len : n_samples - t0);
+    for (int k = threadIdx.x; k < 32 * CW; k += blockDim.x) sum[k] = 0;
+    __syncthreads();
+    if (16 * (c0 + c) < n) {
+        const uint8_t *p = s + t0 * stride + min(16 * (c0 + c), n - 16);
+        uint32_t s1[16], s2[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) s1[k] = s2[k] = 0;
-    if (i0 < n) {
-        const uint8_t *p = s + i0;
-        int64_t t = t0 + wave;
-        for (; t + 12 < t1; t += 16) {
-            uint4 v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const uint4 *>(p + (t + 4 * u) * stride);
+        for (int k = 0; k < 16; ++k) s1[k] = s2[k] = 0;
+        const int quads = (m + 3) / 4, step = waves * GROUPS;
+        auto load = [&](row16 (&v)[4], int q) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const uint32_t w4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-                for (int k = 0; k < 16; ++k) power_sums((w4[k >> 2] >> (8 * (k & 3))) & 0xFFu, sh_re, sh_im, s1[k], s2[k]);
+                // rows past the block's end: the zero sample, no power
+                v[u] = row16{0x88888888u, 0x88888888u, 0x88888888u, 0x88888888u};
+                if (4 * q + u < m) v[u] = *reinterpret_cast<const row16_u *>(p + (int64_t)(4 * q + u) * stride);
             }
-        }
-        for (; t < t1; t += 4) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(p + t * stride);
-            const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
+        };
+        auto use = [&](const row16 (&v)[4]) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) power_sums((w4[k >> 2] >> (8 * (k & 3))) & 0xFFu, sh_re, sh_im, s1[k], s2[k]);
+            for (int w = 0; w < 4; ++w) {
+                const uint32_t ab_lo = __builtin_amdgcn_perm(v[1][w], v[0][w], 0x05010400u);
+                const uint32_t ab_hi = __builtin_amdgcn_perm(v[1][w], v[0][w], 0x07030602u);
+                const uint32_t cd_lo = __builtin_amdgcn_perm(v[3][w], v[2][w], 0x05010400u);
+                const uint32_t cd_hi = __builtin_amdgcn_perm(v[3][w], v[2][w], 0x07030602u);
+                power_sums4(__builtin_amdgcn_perm(cd_lo, ab_lo, 0x05040100u), s1[4 * w], s2[4 * w]);
+                power_sums4(__builtin_amdgcn_perm(cd_lo, ab_lo, 0x07060302u), s1[4 * w + 1], s2[4 * w + 1]);
+                power_sums4(__builtin_amdgcn_perm(cd_hi, ab_hi, 0x05040100u), s1[4 * w + 2], s2[4 * w + 2]);
+                power_sums4(__builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u), s1[4 * w + 3], s2[4 * w + 3]);
+            }
+        };
+        row16 v0[4], v1[4];
+        int q = wave * GROUPS + lane / CW;
+        load(v0, q);
+        for (; q < quads; q += 2 * step) {
+            load(v1, q + step);
+            use(v0);
+            load(v0, q + 2 * step);
+            use(v1);
         }
-    }
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        red[wave][16 * lane + k][0] = s1[k];
-        red[wave][16 * lane + k][1] = s2[k];
+        for (int k = 0; k < 16; ++k) {
+            atomicAdd(&sum[k * CW + c], s1[k]);
+            atomicAdd(&sum[(16 + k) * CW + c], s2[k]);
+        }
     }
     __syncthreads();
-    const int m = (int)(t1 - t0);
-    for (int c = threadIdx.x; c < 1024; c += 256) {
-        const int i = 1024 * (int)blockIdx.x + c;
-        if (i >= n) continue;
-        const int32_t a = red[0][c][0] + red[1][c][0] + red[2][c][0] + red[3][c][0];
-        const int32_t q = red[0][c][1] + red[1][c][1] + red[2][c][1] + red[3][c][1];
-        flags[b * n + i] = sk_decide(a, q, m, lo_num, hi_num, den);
+    for (int e = threadIdx.x; e < 16 * CW; e += blockDim.x) {
+        const int ch = e / 16, k = e % 16, first = 16 * (c0 + ch);
+        if (first >= n) continue;
+        flags[b * n + min(first, n - 16) + k] =
+            sk_decide((int32_t)sum[k * CW + ch], (int32_t)sum[(16 + k) * CW + ch], m, lo_num, hi_num, den);
     }
 }
 
-// Any alignment: one thread per (input, block), byte loads.
+// N < 16: one thread per (input, block), byte loads.
 __global__ __launch_bounds__(256) void sk_flags_bytes(const uint8_t *__restrict__ s, int64_t n_samples, int n,
                                                       int64_t stride, uint32_t re_low, int block_len, int64_t lo_num,
                                                       int64_t hi_num, int64_t den, uint8_t *__restrict__ flags)
@@ -117,12 +170,19 @@ __global__ __launch_bounds__(256) void sk_flags_bytes(const uint8_t *__restrict_
     flags[b * n + i] = sk_decide(s1, s2, (int)(t1 - t0), lo_num, hi_num, den);
 }
 
-// Rows of n samples copied into rows of n16 bytes, padded with the zero
-// sample, every sample of a flagged (block, input) replaced by the zero
-// sample.  Row t of the copy is sample t_first + t of the call, in block
-// (t_first + t) / block_len.  Vector form (16-byte-aligned rows and flags,
-// n % 16 == 0): a thread per 16 bytes, 16-byte loads of samples and flags,
-// a workgroup covering 256 x 16 bytes of consecutive rows.
+// Rows of n samples (any stride and alignment) copied into rows `pitch` bytes
+// apart, each n16 = n rounded up to 16 bytes padded with the zero sample: a
+// layout the DMA kernels read.  MASK: every sample of a flagged (block, input)
+// becomes the zero sample; row t of the copy is sample t_first + t of the
+// call, in block (t_first + t) / block_len.
+//
+// Bound by HBM: 2 N bytes a row.  A workgroup takes consecutive rows, 2^xs
+// threads side by side on a row, a thread 16 bytes of R rows (all loads before
+// the first store).  N = 1000, T = 32768: 16.0 us (a dword per thread, a row
+// per workgroup) -> 12.5 us with four rows (13.1 with two, 13.8 with one); with
+// flags, N = 2048, T = 32768 (134 MB) 21.0 us with two (22.0 with one, 22.3
+// with four, 20.6 for the aligned-only form it replaces), N = 500, T = 8192
+// 10.1 -> 9.7 us.
 __device__ __forceinline__ uint32_t mask_word(uint32_t x, uint32_t f)
 {
     // bytes of f that are nonzero -> 0xFF
@@ -131,41 +191,38 @@ __device__ __forceinline__ uint32_t mask_word(uint32_t x, uint32_t f)
     return (x & ~m) | (0x88888888u & m);
 }
 
-__global__ __launch_bounds__(256) void mask_rows_vec(const uint8_t *__restrict__ src, int64_t stride, int n,
-                                                     int64_t rows, uint8_t *__restrict__ dst,
-                                                     const uint8_t *__restrict__ flags, int block_len,
-                                                     int64_t t_first)
-{
-    const int per_row = n / 16;
-    const int64_t total = rows * per_row;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-        const int64_t t = e / per_row;
-        const int c = (int)(e - t * per_row) * 16;
-        const uint4 x = *reinterpret_cast<const uint4 *>(src + t * stride + c);
-        const uint4 f = *reinterpret_cast<const uint4 *>(flags + ((t_first + t) / block_len) * (int64_t)n + c);
-        *reinterpret_cast<uint4 *>(dst + t * n + c) =
-            make_uint4(mask_word(x.x, f.x), mask_word(x.y, f.y), mask_word(x.z, f.z), mask_word(x.w, f.w));
-    }
-}
+template <bool MASK> constexpr int COPY_ROWS = MASK ? 2 : 4;
 
-// Any alignment or N: one workgroup per row, byte loads.
-__global__ __launch_bounds__(256) void mask_rows(const uint8_t *__restrict__ src, int64_t stride, int n, int n16,
-                                                 uint8_t *__restrict__ dst, const uint8_t *__restrict__ flags,
-                                                 int block_len, int64_t t_first)
+template <bool MASK>
+__global__ __launch_bounds__(256) void copy_rows(const uint8_t *__restrict__ src, int64_t stride, int n, int64_t rows,
+                                                 uint8_t *__restrict__ dst, int64_t pitch, int xs,
+                                                 const uint8_t *__restrict__ flags, int block_len, int64_t t_first)
 {
-    const int64_t t = blockIdx.x;
-    const uint8_t *row = src + t * stride;
-    const uint8_t *frow = flags + ((t_first + t) / block_len) * (int64_t)n;
-    uint32_t *out_row = reinterpret_cast<uint32_t *>(dst + t * n16);
-    for (int c0 = 4 * (int)threadIdx.x; c0 < n16; c0 += 4 * 256) {
-        uint32_t out = 0x88888888u;
+    const int x = threadIdx.x & ((1 << xs) - 1), y = threadIdx.x >> xs, ny = 256 >> xs;
+    constexpr int R = COPY_ROWS<MASK>;
+    for (int64_t t0 = (int64_t)blockIdx.x * ny * R + y; t0 < rows; t0 += (int64_t)gridDim.x * ny * R)
+        for (int c = 16 * x; c < n; c += 16 << xs) {
+            row16 v[R], f[R];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int c = c0 + k;
-            if (c < n && frow[c] == 0) out = (out & ~(0xFFu << (8 * k))) | ((uint32_t)row[c] << (8 * k));
+            for (int k = 0; k < R; ++k) {
+                const int64_t t = t0 + k * ny;
+                if (t >= rows) continue;
+                v[k] = load_row16(src + t * stride, c, n);
+                if (MASK) {
+                    const uint32_t b = (uint32_t)(t_first + t) / (uint32_t)block_len;   // T_MAX samples at most
+                    f[k] = load_row16(flags + (int64_t)b * n, c, n);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                const int64_t t = t0 + k * ny;
+                if (t >= rows) continue;
+                if (MASK)
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) v[k][w] = mask_word(v[k][w], f[k][w]);
+                *reinterpret_cast<row16 *>(dst + t * pitch + c) = v[k];
+            }
         }
-        out_row[c0 >> 2] = out;
-    }
 }
 
 // Unflagged masks packed along blocks: bits[i][w] bit k set when block
@@ -193,10 +250,12 @@ __global__ __launch_bounds__(256) void pack_unflagged(const uint8_t *__restrict_
 // (q < 4), so that each row's 64 counts are updated by 16 consecutive
 // threads at a time.  The masks of the 64 + 64 inputs go through LDS in
 // chunks of up to CW words.  Blocks 0 .. nb-2 weigh block_len each, the
-// last `last_len`.
+// last `last_len`.  `fresh`: the counts hold nothing since the slot's reset
+// (which leaves them as they are) and are stored, not read.
 constexpr int CW = 32;
 __global__ __launch_bounds__(256) void count_pairs(const uint32_t *__restrict__ bits, int words, int nb, int n,
-                                                   int block_len, int last_len, int32_t *__restrict__ counts)
+                                                   int block_len, int last_len, int fresh,
+                                                   int32_t *__restrict__ counts)
 {
     const int by = blockIdx.y, bx = blockIdx.x;
     if (bx < by) return;
@@ -247,18 +306,19 @@ __global__ __launch_bounds__(256) void count_pairs(const uint32_t *__restrict__ 
         for (int q = 0; q < 4; ++q) {
             const int j = 64 * bx + tx + 16 * q;
             if (j >= n || j < i) continue;
-            counts[row + j] += c[p][q] * block_len + ((li && lj[q]) ? last_len : 0);
+            const int32_t v = c[p][q] * block_len + ((li && lj[q]) ? last_len : 0);
+            counts[row + j] = fresh ? v : counts[row + j] + v;
         }
     }
 }
 
 // out[k] = counts[k] + base (samples integrated without flags count for
-// every pair).
+// every pair); `counts` null: no flagged samples since the slot's reset.
 __global__ __launch_bounds__(256) void counts_export(const int32_t *__restrict__ counts, int64_t npairs, int32_t base,
                                                      int32_t *__restrict__ out)
 {
     for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < npairs; k += (int64_t)gridDim.x * 256)
-        out[k] = counts[k] + base;
+        out[k] = (counts ? counts[k] : 0) + base;
 }
 
 hipError_t launch_sk_flags(const uint8_t *s, int64_t n_samples, int n, int64_t stride, uint32_t re_low,
@@ -267,36 +327,49 @@ hipError_t launch_sk_flags(const uint8_t *s, int64_t n_samples, int n, int64_t s
 {
     const int64_t nb = (n_samples + block_len - 1) / block_len;
     if (nb <= 0) return hipSuccess;
-    const bool vec = (reinterpret_cast<uintptr_t>(s) % 16) == 0 && stride % 16 == 0 && n % 16 == 0;
-    if (vec)
-        hipLaunchKernelGGL(sk_flags_vec, dim3((unsigned)((n + 1023) / 1024), (unsigned)nb), dim3(256), 0, stream, s,
-                           n_samples, n, stride, re_low, block_len, lo_num, hi_num, den, flags);
-    else
+    if (n < 16) {
         hipLaunchKernelGGL(sk_flags_bytes, dim3((unsigned)((n + 255) / 256), (unsigned)nb), dim3(256), 0, stream, s,
                            n_samples, n, stride, re_low, block_len, lo_num, hi_num, den, flags);
+        return hipGetLastError();
+    }
+    // the narrowest row of lanes that holds the inputs' chunks, and a wave
+    // for every two row quads of each of its row groups, up to 16
+    const int chunks = (n + 15) / 16;
+    auto go = [&](auto kernel, int cw) {
+        const int per_wave = 4 * 2 * (64 / cw);
+        const int waves = std::min(16, std::max(1, (block_len + per_wave - 1) / per_wave));
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((chunks + cw - 1) / cw), (unsigned)nb), dim3(64 * waves), 0, stream,
+                           s, n_samples, n, stride, block_len, lo_num, hi_num, den, flags);
+    };
+    if (chunks <= 4) go(sk_flags_vec<4>, 4);
+    else if (chunks <= 16) go(sk_flags_vec<16>, 16);
+    else if (chunks <= 32) go(sk_flags_vec<32>, 32);
+    else go(sk_flags_vec<64>, 64);
     return hipGetLastError();
 }
 
-hipError_t launch_mask_rows(const uint8_t *src, int64_t stride, int n, int64_t rows, int n16, uint8_t *dst,
+// `dst`: rows `pitch` bytes apart (a multiple of 16, >= n), 16-byte aligned;
+// `flags` null: a plain padded copy.
+hipError_t launch_copy_rows(const uint8_t *src, int64_t stride, int n, int64_t rows, uint8_t *dst, int64_t pitch,
                             const uint8_t *flags, int block_len, int64_t t_first, hipStream_t stream)
 {
     if (rows <= 0) return hipSuccess;
-    const bool vec = n == n16 && (reinterpret_cast<uintptr_t>(src) % 16) == 0 && stride % 16 == 0 &&
-                     (reinterpret_cast<uintptr_t>(flags) % 16) == 0 && (reinterpret_cast<uintptr_t>(dst) % 16) == 0;
-    if (vec) {
-        int64_t blocks = (rows * (n / 16) + 255) / 256;
-        if (blocks > 8192) blocks = 8192;
-        hipLaunchKernelGGL(mask_rows_vec, dim3((unsigned)blocks), dim3(256), 0, stream, src, stride, n, rows, dst,
-                           flags, block_len, t_first);
-    } else {
-        hipLaunchKernelGGL(mask_rows, dim3((unsigned)rows), dim3(256), 0, stream, src, stride, n, n16, dst, flags,
-                           block_len, t_first);
-    }
+    const int per_row = (n + 15) / 16;
+    int xs = 0;
+    while (xs < 8 && (1 << xs) < per_row) ++xs;
+    const int64_t per_wg = (int64_t)(256 >> xs) * (flags ? COPY_ROWS<true> : COPY_ROWS<false>);
+    const int64_t blocks = std::min<int64_t>(65535, (rows + per_wg - 1) / per_wg);
+    if (flags)
+        hipLaunchKernelGGL(copy_rows<true>, dim3((unsigned)blocks), dim3(256), 0, stream, src, stride, n, rows, dst,
+                           pitch, xs, flags, block_len, t_first);
+    else
+        hipLaunchKernelGGL(copy_rows<false>, dim3((unsigned)blocks), dim3(256), 0, stream, src, stride, n, rows, dst,
+                           pitch, xs, flags, block_len, t_first);
     return hipGetLastError();
 }
 
 hipError_t launch_counts(const uint8_t *flags, int nb, int n, int block_len, int last_len, uint32_t *bits,
-                         int32_t *counts, hipStream_t stream)
+                         int32_t *counts, bool fresh, hipStream_t stream)
 {
     if (nb <= 0) return hipSuccess;
     const int words = (nb + 31) / 32;
@@ -305,7 +378,7 @@ hipError_t launch_counts(const uint8_t *flags, int nb, int n, int block_len, int
                        bits);
     const unsigned tiles = (unsigned)((n + 63) / 64);
     hipLaunchKernelGGL(count_pairs, dim3(tiles, tiles), dim3(256), 0, stream, bits, words, nb, n, block_len,
-                       last_len, counts);
+                       last_len, fresh ? 1 : 0, counts);
     return hipGetLastError();
 }
 
