@@ -639,6 +639,7 @@ JobDesc make_job(const xeng_ctx *c, int32_t slot, const uint8_t *d_samples, int6
     if ((stride % 8) == 0 && (addr % 8) == 0 && c->n % 8 == 0) jd.flags |= JOB_ALIGNED8;
     if ((stride % 16) == 0 && (addr % 16) == 0 && c->n % 16 == 0) jd.flags |= JOB_DMA;
     if (may_store && c->acc_t[(size_t)slot] == 0 && c->bound[(size_t)slot] == 0) jd.flags |= JOB_FRESH;
+    if (c->slot_i32 * (int64_t)sizeof(int32_t) >= STREAM_BYTES) jd.flags |= JOB_STREAM;
     jd.pad = 0;
     jd.presum = nullptr;
     jd.bias = c->d_bias + (int64_t)slot * bias_i32(c->n);
@@ -949,6 +950,12 @@ std::vector<Part> split_by_kernel(const JobList &jl, const Tuning &tu)
         p.pj.push_back(jl.pj[k]);
         p.descs.push_back(jl.descs[k]);
         p.flags_and &= jl.descs[k].flags;
+    }
+    for (Part &p : by_kind) {
+        int64_t bytes = 0;
+        for (const JobDesc &d : p.descs) bytes += (int64_t)d.nt * (d.nt + 1) / 2 * TILE_I32 * (int64_t)sizeof(int32_t);
+        if (bytes >= STREAM_BYTES)
+            for (JobDesc &d : p.descs) d.flags |= JOB_STREAM;
     }
     std::vector<Part> parts;
     for (Kind k : {Kind::Wide, Kind::Tile, Kind::Region, Kind::Narrow, Kind::General, Kind::Fp8, Kind::WideFp8})

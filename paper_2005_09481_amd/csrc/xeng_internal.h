@@ -104,6 +104,15 @@ constexpr uint32_t JOB_RE_LOW = 1u;    // real part in the low nibble
 constexpr uint32_t JOB_ALIGNED8 = 2u;   // samples, stride and N are multiples of 8 bytes
 constexpr uint32_t JOB_DMA = 4u;        // samples and stride multiples of 16 bytes, N of 16: DMA kernel
 constexpr uint32_t JOB_FRESH = 8u;      // the slot holds zeros: whole-tile flushes store instead of add
+constexpr uint32_t JOB_STREAM = 16u;    // the launch's accumulators pass the caches: see STREAM_BYTES
+// Accumulators of one launch from which whole-tile flushes go past the
+// caches: what the Infinity Cache (256 MiB) keeps of them until the next
+// launch or export no longer pays for allocating them.  Batches of N = 2048
+// (17.0 MiB a slot), four launches of 1024 samples and an export,
+// us cached / past the caches: 8 slots 481 / 502, 12 slots 684 / 677,
+// 16 slots 900 / 876, 24 slots 1225 / 1175, 48 slots 2423 / 2321; N = 1024,
+// 120 slots (540 MiB) 1659 / 1575.
+constexpr int64_t STREAM_BYTES = (int64_t)192 << 20;
 
 // Work decomposition shapes: 128 x 128 tiles (general kernel; Tile: the tile
 // kernel, which reads by DMA), 128 x 256 workgroup tiles covering two

@@ -407,10 +407,24 @@ __device__ __forceinline__ void add_bias(int32_t *bias, const Acc<L, false> &acc
     }
 }
 
+// A slot word, through the caches or past them (NT).
+template <bool NT> __device__ __forceinline__ uint64_t load_word(const gw64 *p)
+{
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <bool NT> __device__ __forceinline__ void store_word(gw64 *p, uint64_t v)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 // Whole-tile flush of one wave's 2 x BW blocks (column blocks cb0..): stores
 // if the slot holds zeros, else read-modify-write with the loads of a row of
 // blocks issued together (one memory latency per row, not one per value).
-template <typename L, int SHIFT, bool F>
+// NT: past the caches (JOB_STREAM; the four-wave kernel has no registers for
+// a second form).
+template <typename L, int SHIFT, bool F, bool NT>
 __device__ __forceinline__ void flush_owned(gw64 *tb, const Acc<L, F> &acc, int wa, int cb0, bool fresh, int a0 = 0,
                                             int a1 = 2)
 {
@@ -425,13 +439,13 @@ __device__ __forceinline__ void flush_owned(gw64 *tb, const Acc<L, F> &acc, int 
 #pragma unroll
         for (int b = 0; b < BW; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) old[b][r] = fresh ? 0 : blk[b][r * 64];
+            for (int r = 0; r < 16; ++r) old[b][r] = fresh ? 0 : load_word<NT>(blk[b] + r * 64);
 #pragma unroll
         for (int b = 0; b < BW; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                blk[b][r * 64] =
-                    old[b][r] + pack_pair(acc_val<SHIFT>(acc.re[a][b][r]), acc_val<SHIFT>(acc.im[a][b][r]));
+                store_word<NT>(blk[b] + r * 64, old[b][r] + pack_pair(acc_val<SHIFT>(acc.re[a][b][r]),
+                                                                      acc_val<SHIFT>(acc.im[a][b][r])));
         __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -643,10 +657,13 @@ __device__ __forceinline__ void run_workgroup(const KernelArgs &args)
                         // one block at a time: keeps the register file for the main loop
                         __builtin_amdgcn_sched_barrier(0);
                     }
+            } else if (L::NW == 8 && (jd.flags & JOB_STREAM)) {
+                if (jd.flags & JOB_FRESH) flush_owned<L, SHIFT, F, true>(tb, acc, wa, cb0, true, a0, a1);
+                else flush_owned<L, SHIFT, F, true>(tb, acc, wa, cb0, false, a0, a1);
             } else if (jd.flags & JOB_FRESH) {
-                flush_owned<L, SHIFT, F>(tb, acc, wa, cb0, true, a0, a1);
+                flush_owned<L, SHIFT, F, false>(tb, acc, wa, cb0, true, a0, a1);
             } else {
-                flush_owned<L, SHIFT, F>(tb, acc, wa, cb0, false, a0, a1);
+                flush_owned<L, SHIFT, F, false>(tb, acc, wa, cb0, false, a0, a1);
             }
         }
     }

@@ -54,3 +54,24 @@ def test_larger_jobs_match_reference(n, t):
         assert torch.equal(c.dump(0), ref)
         b.close()
         c.close()
+
+
+@pytest.mark.parametrize("n,slots,t", [(2048, 11, 96), (2048, 12, 200), (1000, 46, 64), (8192, 1, 64)])
+def test_launches_past_the_caches(n, slots, t):
+    """Launches whose accumulators stay just under, and pass, what goes past
+    the caches: fresh slots, slots that hold sums, a resetting export between."""
+    g = torch.Generator(device="cuda").manual_seed(n + slots + t)
+    x = torch.randint(0, 256, (slots, t, n), dtype=torch.uint8, device="cuda", generator=g)
+    c = xeng.Correlator(n, slots)
+    jobs = [(c, k, x[k]) for k in range(slots)]
+    for launches in (2, 1):
+        for _ in range(launches):
+            xeng.correlate_batch(jobs)
+        outs = xeng.dump_batch([(c, k) for k in range(slots)])
+        for k in range(slots):
+            assert torch.equal(outs[k], launches * xeng.correlate_reference(x[k]))
+    for k in range(slots):
+        c.correlate(k, x[k])
+        c.correlate_presum(k, x[k])
+        assert torch.equal(c.dump(k), 2 * xeng.correlate_reference(x[k]))
+    c.close()
