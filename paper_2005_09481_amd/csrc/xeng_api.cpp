@@ -697,6 +697,11 @@ TileShape shape_of(Kind k)
                                                  : TileShape::Square;
 }
 
+Kind kind_of_shape(TileShape s)
+{
+    return s == TileShape::Region ? Kind::Region : s == TileShape::Tile ? Kind::Tile : Kind::Wide;
+}
+
 // The kernel of one job read by DMA, and the workgroups to plan it for (0:
 // the shape's).  The four-wave instance is the wide kernel's.
 struct Choice {
@@ -707,8 +712,7 @@ Choice dma_choice(const DeviceState *st, const PlanJob &pj, const Tuning &tu)
 {
     if (tu.kernel != XENG_KERNEL_AUTO) return Choice{Kind::Wide, 0};
     const DmaChoice c = choose_dma(pj.n, pj.t, st->cu_count, std::max(1, tu.min_stages));
-    return Choice{c.shape == TileShape::Region ? Kind::Region : c.shape == TileShape::Tile ? Kind::Tile : Kind::Wide,
-                  c.wgs};
+    return Choice{kind_of_shape(c.shape), c.wgs};
 }
 
 // Longest piece of a kernel, in stages (0: its shape's default).  The FP8
@@ -925,31 +929,28 @@ bool any_dma_job(const JobList &jl)
     return false;
 }
 
-// (A batch of one job takes the kernel a single call would: several wide
-// jobs share the wide kernel's launch, whose owned tiles flush without
-// atomics.)
+// (Jobs read by DMA share one launch, of the kernel that a model of the
+// launch's time chooses; one such job takes the kernel a single call would.)
 std::vector<Part> split_by_kernel(const JobList &jl, const Tuning &tu)
 {
     Part by_kind[7];
     by_kind[(int)Kind::Wide].kind = Kind::Wide;
     by_kind[(int)Kind::Narrow].kind = Kind::Narrow;
-    by_kind[(int)Kind::Tile].kind = Kind::Tile;
-    by_kind[(int)Kind::Region].kind = Kind::Region;
     by_kind[(int)Kind::Fp8].kind = Kind::Fp8;
     by_kind[(int)Kind::WideFp8].kind = Kind::WideFp8;
     for (size_t k = 0; k < jl.descs.size(); ++k) {
-        Kind kind = kind_of(jl.descs[k], tu);
-        int wgs = 0;
-        if (kind == Kind::Wide && jl.descs.size() == 1) {
-            const Choice ch = dma_choice(jl.st, jl.pj[k], tu);
-            kind = ch.kind;
-            wgs = ch.wgs;
-        }
-        Part &p = by_kind[(int)kind];
-        p.wgs = wgs;
+        Part &p = by_kind[(int)kind_of(jl.descs[k], tu)];
         p.pj.push_back(jl.pj[k]);
         p.descs.push_back(jl.descs[k]);
         p.flags_and &= jl.descs[k].flags;
+    }
+    Part &dma = by_kind[(int)Kind::Wide];
+    if (dma.pj.size() == 1) {
+        const Choice ch = dma_choice(jl.st, dma.pj[0], tu);
+        dma.kind = ch.kind;
+        dma.wgs = ch.wgs;
+    } else if (!dma.pj.empty() && tu.kernel == XENG_KERNEL_AUTO) {
+        dma.kind = kind_of_shape(choose_dma_batch(dma.pj.data(), (int)dma.pj.size(), jl.st->cu_count));
     }
     for (Part &p : by_kind) {
         int64_t bytes = 0;
@@ -958,7 +959,7 @@ std::vector<Part> split_by_kernel(const JobList &jl, const Tuning &tu)
             for (JobDesc &d : p.descs) d.flags |= JOB_STREAM;
     }
     std::vector<Part> parts;
-    for (Kind k : {Kind::Wide, Kind::Tile, Kind::Region, Kind::Narrow, Kind::General, Kind::Fp8, Kind::WideFp8})
+    for (Kind k : {Kind::Wide, Kind::Narrow, Kind::General, Kind::Fp8, Kind::WideFp8})
         if (!by_kind[(int)k].descs.empty()) parts.push_back(std::move(by_kind[(int)k]));
     return parts;
 }

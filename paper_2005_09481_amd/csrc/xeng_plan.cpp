@@ -332,6 +332,20 @@ struct ShapeCost {
     double stage, owned, prologue, shared;
 };
 constexpr double LAUNCH_US = 4.0;
+constexpr ShapeCost SHAPE_COSTS[] = {{TileShape::Wide, 1.1, 13.0, 5.0, 0.13},
+                                     {TileShape::Tile, 0.62, 8.0, 3.0, 0.065},
+                                     {TileShape::Region, 0.20, 4.3, 3.0, 0.016}};
+
+// Units of one job (the length of plan_units).
+int64_t shape_units(int32_t n, TileShape shape)
+{
+    const int64_t nt = n_tiles_side(n);
+    if (shape == TileShape::Region) return tri64((n + REGION - 1) / REGION);
+    if (shape == TileShape::Tile) return tri64(nt);
+    int64_t units = 0;
+    for (int64_t i = 0; i < nt; ++i) units += (nt + 1) / 2 - i / 2;
+    return units;
+}
 
 // Stage times rise with the length of the work: the clock settles under the
 // load, and the region kernel's operands outgrow what the L2s hold.
@@ -347,11 +361,7 @@ double stage_us(const ShapeCost &c, double stages_per_wg, int64_t units)
 
 DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages)
 {
-    static const ShapeCost costs[] = {{TileShape::Wide, 1.1, 13.0, 5.0, 0.13},
-                                      {TileShape::Tile, 0.62, 8.0, 3.0, 0.065},
-                                      {TileShape::Region, 0.20, 4.3, 3.0, 0.016}};
     const int64_t ns = std::max<int64_t>(1, (t + STAGE - 1) / STAGE);
-    const int64_t nt = n_tiles_side(n), nr = (n + REGION - 1) / REGION;
     DmaChoice best{TileShape::Wide, 0};
     double best_us = -1.0;
     auto consider = [&](TileShape shape, int64_t wgs, double us) {
@@ -360,13 +370,8 @@ DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages)
             best = DmaChoice{shape, (int)wgs};
         }
     };
-    for (const ShapeCost &c : costs) {
-        int64_t units = tri64(nr);
-        if (c.shape == TileShape::Tile) units = tri64(nt);
-        if (c.shape == TileShape::Wide) {
-            units = 0;
-            for (int64_t i = 0; i < nt; ++i) units += (nt + 1) / 2 - i / 2;
-        }
+    for (const ShapeCost &c : SHAPE_COSTS) {
+        const int64_t units = shape_units(n, c.shape);
         // every unit whole, or in k equal pieces
         for (int64_t k = 1; k * units <= cus && k <= MAX_UNIT_SPLIT && (k == 1 || k * min_stages <= ns); ++k) {
             const int64_t s = (ns + k - 1) / k;
@@ -380,6 +385,42 @@ DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages)
         if (units * MAX_UNIT_SPLIT >= cus && units * ns >= (int64_t)cus * min_stages)
             consider(c.shape, 0,
                      LAUNCH_US + s * stage_us(c, s, units) + c.owned * (double)units / cus + cus * c.shared);
+    }
+    return best;
+}
+
+TileShape choose_dma_batch(const PlanJob *jobs, int n_jobs, int cus)
+{
+    TileShape best = TileShape::Wide;
+    double best_us = -1.0;
+    for (const ShapeCost &c : SHAPE_COSTS) {
+        int64_t units = 0, stages = 0, longest = 0;
+        for (int k = 0; k < n_jobs; ++k) {
+            const int64_t ns = (jobs[k].t + STAGE - 1) / STAGE, u = shape_units(jobs[k].n, c.shape);
+            units += u;
+            stages += u * ns;
+            longest = std::max(longest, ns);
+        }
+        // (Wide comes first: its count decides for the others)
+        if (c.shape == TileShape::Wide && units > cus) return TileShape::Wide;
+        if (c.shape == TileShape::Region && 4 * units > 5 * (int64_t)cus) continue;
+        // which regime the planner's costs (in stages) lead it to
+        const int64_t k = (units + cus - 1) / cus, ovh = piece_overhead(c.shape);
+        double us;
+        if (k * (longest + ovh) * cus <= stages + ovh * (units + cus)) {
+            // a second region's flush also waits for the first one's stores
+            const double owned = c.shape == TileShape::Region && k > 1 ? 1.5 * c.owned : c.owned;
+            us = (double)k * ((double)longest * stage_us(c, (double)(k * longest), units) + owned);
+        } else {
+            const double s = (double)stages / cus;
+            us = s * stage_us(c, s, units) + c.prologue + c.owned * (double)units / cus + cus * c.shared;
+        }
+        // the wide kernel unless another is clearly ahead
+        if (c.shape != TileShape::Wide) us *= 1.05;
+        if (best_us < 0.0 || us < best_us) {
+            best_us = us;
+            best = c.shape;
+        }
     }
     return best;
 }

@@ -91,6 +91,17 @@ struct DmaChoice {
 };
 DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages);
 
+// The same choice for the jobs of a batch that one DMA launch takes, planned
+// over every compute unit: the modelled time of the planner's two regimes,
+// every unit whole or all work in equal shares.  From more wide windows than
+// compute units on, the wide kernel flushes them whole and reads least; the
+// region kernel reads most, and is left out past a quarter more regions than
+// compute units.  Correlations of T samples with the launch and the exports,
+// wide / tile / region, us: 4 jobs of N = 512, T to 4096 51 / 45 / 33; 16 of
+// N = 512, T to 1024 60 / 46 / 51; 8 of N = 1024, T to 4096 87 / 70 / 127; 8 of
+// N = 2048, T to 4096 (576 windows) 198 / 222 / 433.
+TileShape choose_dma_batch(const PlanJob *jobs, int n_jobs, int cus);
+
 // Plan parameters of one job as make_plan would choose them (grid and
 // budget), for the container-free planner of xeng_plan_single.h; also the
 // number of pieces and of workgroups used.  Host only, allocates nothing.

@@ -75,3 +75,34 @@ def test_launches_past_the_caches(n, slots, t):
         c.correlate_presum(k, x[k])
         assert torch.equal(c.dump(k), 2 * xeng.correlate_reference(x[k]))
     c.close()
+
+
+@pytest.mark.parametrize("sizes", [
+    [(128, 64), (320, 700)],                                       # a few regions
+    [(512, 4096), (256, 1), (512, 4097), (80, 65)],                # regions in shares, a tiny job
+    [(512, 1024)] * 7 + [(1000, 333)],                             # about as many regions as compute units
+    [(1024, 2000)] * 6,                                            # tiles
+    [(768, 12000), (1024, 5000), (64, 300), (200, 31), (777, 900)],
+    [(1536, 300)] * 6,                                             # windows just past the compute units
+    [(640, 900), (48, 2000), (17, 64)],                            # one job beside narrow ones
+])
+def test_batches_match_reference(sizes):
+    g = torch.Generator(device="cuda").manual_seed(len(sizes) + sizes[0][0])
+    jobs, want = [], []
+    for k, (n, t) in enumerate(sizes):
+        c = xeng.Correlator(n, 1, re_low=bool(k % 2))
+        x = torch.randint(0, 256, (t, n), dtype=torch.uint8, device="cuda", generator=g)
+        jobs.append((c, 0, x))
+        want.append(xeng.correlate_reference(x, re_low=bool(k % 2)))
+    xeng.correlate_batch(jobs)                 # into fresh slots
+    xeng.correlate_batch(jobs)                 # and slots that hold sums
+    b = xeng.Batch(jobs)
+    b.launch()
+    outs = xeng.dump_batch([(c, 0) for c, _, _ in jobs])
+    for o, w in zip(outs, want):
+        assert torch.equal(o, 3 * w)
+    b.launch()
+    b.close()
+    for (c, _, _), w in zip(jobs, want):
+        assert torch.equal(c.dump(0), w)
+        c.close()
