@@ -33,14 +33,14 @@ def measured_traffic():
     has changed since those counters were taken."""
     import hashlib
     rec = os.path.join(ROOT, "profiles", "xcorr_dma_n2048_t32768_traffic.txt")
-    src = os.path.join(ROOT, "paper_2005_09481_amd", "csrc", "xeng_kernel_dma.hip")
+    srcs = [os.path.join(ROOT, "paper_2005_09481_amd", "csrc", f) for f in ("xeng_dma_ops.h", "xeng_kernel_dma.hip")]
     try:
         fields = {}
         for line in open(rec):
             if ":" in line and not line.startswith("#"):
                 k, v = line.split(":", 1)
                 fields[k.strip()] = v.strip()
-        if hashlib.sha256(open(src, "rb").read()).hexdigest() != fields["kernel_source_sha256"]:
+        if hashlib.sha256(b"".join(open(f, "rb").read() for f in srcs)).hexdigest() != fields["kernel_source_sha256"]:
             return None
         return int(fields["fetch_bytes_per_launch"]) + int(fields["write_bytes_per_launch"])
     except (OSError, KeyError, ValueError):

@@ -181,7 +181,7 @@ int xeng_rfi_flags(const uint8_t *d_samples, int64_t n_samples, int32_t n_inputs
  * that did, so V_ij / n_ij is the mean over them.  The samples are copied
  * into padded rows with flagged samples set to zero (scratch from the
  * library's pool, in chunks as the padded path of xeng_correlate) and
- * correlated by the wide kernel.  Same checks and integration bound as
+ * correlated by a DMA kernel.  Same checks and integration bound as
  * xeng_correlate; XENG_EINVAL without XENG_COUNTS or with block_len < 1.
  */
 int xeng_correlate_flagged(xeng_ctx *ctx, int32_t slot, const uint8_t *d_samples, int64_t n_samples,
@@ -287,8 +287,8 @@ int xeng_correlate_batch(const xeng_job *jobs, int32_t n_jobs, void *hip_stream)
  * out: int32 [N(N+1)/2][2], device memory or host memory from
  *   hipHostMalloc; owned by the caller.  reset != 0 zeroes the slot and its
  *   sample counter after the export.  Asynchronous on hip_stream.  Exports
- *   of one slot must not run concurrently on different streams (they share
- *   the slot's diagonal staging, and a reset export writes the accumulators
+ *   of one slot must not run concurrently on different streams (a reset
+ *   export writes the accumulators and the bias base
  *   the other reads).  A slot integrated by xeng_correlate_presum (or an FP8
  *   call on the wide kernel) since its last export gets the pending O(N)
  *   correction (see xeng_correlate_presum) on hip_stream: inside the export
@@ -310,7 +310,7 @@ typedef struct {
  * Export many slots at once (the exports of Sec. 2.1 for every channel that
  * reaches its cadence together): each job's output equals what xeng_dump
  * would write for it, and reset jobs zero their slot and sample counter.
- * Two launches cover the whole batch (diagonal staging, then the export),
+ * One launch covers the whole batch,
  * where one xeng_dump per slot runs each export as its own small launch.
  * All contexts must be on one device; a (ctx, slot) pair may appear at most
  * once; the outputs must not overlap one another or any accumulator.
@@ -335,7 +335,7 @@ int64_t xeng_samples_integrated(const xeng_ctx *ctx, int32_t slot);
 int64_t xeng_max_integration(void);
 
 /* Device bytes of one slot for N inputs: its int32 accumulators plus the
- * staging the dump uses (admission control); -1 if N < 1.  A context
+ * biases the dump subtracts (admission control); -1 if N < 1.  A context
  * created with XENG_COUNTS holds 4 * N(N+1)/2 bytes more per slot. */
 int64_t xeng_slot_bytes(int32_t n_inputs);
 
@@ -616,7 +616,7 @@ int xeng_server_last_dump(xeng_server *s, int32_t channel, int32_t *out);
 int xeng_server_export_ring(xeng_server *s, int32_t channel, int32_t *ring, int32_t n_entries);
 
 /* Kernel selection for xeng_set_tuning. */
-#define XENG_KERNEL_AUTO 0     /* wide DMA kernel (eight waves) where the job allows it, else general */
+#define XENG_KERNEL_AUTO 0     /* the DMA kernel with the smallest modelled time (wide, tile or region) where the job allows it, else general */
 #define XENG_KERNEL_GENERAL 1  /* always the general kernel */
 #define XENG_KERNEL_DMA4 2     /* wide DMA kernel with four waves where the job allows it, else general */
 /*

@@ -25,7 +25,7 @@
 //     or past the piece's end read the zero-sample buffer instead, so the
 //     count of loads in flight is the same at every point of the loop and
 //     the waits for a stage's data wait for that stage only;
-//   * registers -> LDS in the wide kernel's chunk-major layout (chunk c of
+//   * registers -> LDS in a chunk-major layout (chunk c of
 //     row r at byte 128 c + 16 r of its 8-row group), in a buffer private to
 //     the wave: the main loop needs no barrier;
 //   * LDS -> registers by transposed reads (ds_read_b64_tr_b8); since rows
