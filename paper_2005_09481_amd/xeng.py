@@ -11,6 +11,7 @@ import ctypes
 import os
 from array import array
 from dataclasses import dataclass
+from operator import index
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libxeng.so")
@@ -392,11 +393,12 @@ def _words(words, struct, n):
 
 def _job_array(jobs):
     # the fields of _Job as 64-bit words: ctx, slot (low) and reserved,
-    # samples, n_samples, row_stride
+    # samples, n_samples, row_stride.  A slot is made a Python int before it is
+    # masked: numpy's and torch's narrow integers overflow there
     words = array("q")
     for corr, slot, samples in jobs:
         ptr, t, row_stride = _samples_args(samples, corr.n_inputs, corr.device)
-        words.extend((corr.handle.value, slot & 0xFFFFFFFF, ptr or 0, t, row_stride))
+        words.extend((corr.handle.value, index(slot) & 0xFFFFFFFF, ptr or 0, t, row_stride))
     return _words(words, _Job, len(jobs))
 
 
@@ -427,7 +429,7 @@ def dump_batch(jobs, stream=None):
         if out is None or out.dtype is not i32 or out.numel() != c._vis_numel or not out.is_contiguous():
             out = c._dump_out(out)
         h = c._h
-        words += ((h or c.handle).value, (j[1] & 0xFFFFFFFF) | (0 if len(j) > 3 and not j[3] else 1 << 32),
+        words += ((h or c.handle).value, (index(j[1]) & 0xFFFFFFFF) | (0 if len(j) > 3 and not j[3] else 1 << 32),
                   out.data_ptr(), 0)
         outs.append(out)
     arr = _words(array("q", words), _DumpJob, len(outs))
