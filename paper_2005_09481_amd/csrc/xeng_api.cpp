@@ -997,6 +997,17 @@ int ring_acquire(DeviceState *st, size_t bytes, JobTable **out)
     return XENG_OK;
 }
 
+// Marks a staging buffer as read by what has been queued on `stream`.  If
+// that cannot be recorded, the work is waited for, so that the buffer is
+// never written again under a launch that still reads it.
+hipError_t ring_mark(JobTable &tb, hipStream_t stream)
+{
+    const hipError_t e = hipEventRecord(tb.ev, stream);
+    tb.pending = e == hipSuccess;
+    if (e != hipSuccess) (void)hipStreamSynchronize(stream);
+    return e;
+}
+
 // Launch the parts of a batch, staging each job table through the ring.
 // Every plan and staging buffer is obtained, and every table written into
 // its pinned buffer, before the first copy or launch is queued: a host-side
@@ -1071,10 +1082,12 @@ int run_parts(DeviceState *st, const std::vector<Part> &parts, const Tuning &tu,
     }
     for (Staged &sg : staged) {
         hipError_t e = hipMemcpyAsync(sg.tb->d, sg.tb->h, sg.bytes, hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess) e = launch(sg.a, sg.grid, sg.kind, sg.waves, sg.flags_and, stream);
-        if (e == hipSuccess) e = hipEventRecord(sg.tb->ev, stream);
+        if (e == hipSuccess) {
+            e = launch(sg.a, sg.grid, sg.kind, sg.waves, sg.flags_and, stream);
+            const hipError_t em = ring_mark(*sg.tb, stream);
+            if (e == hipSuccess) e = em;
+        }
         if (e != hipSuccess) return map_err(e);
-        sg.tb->pending = true;
     }
     return XENG_OK;
 }
@@ -1567,16 +1580,19 @@ int xeng_dump_batch(const xeng_dump_job *jobs, int32_t n_jobs, void *hip_stream)
             for (int32_t k = 0; k < m; ++k) tab = std::fill_n(tab, tri64(descs[(size_t)(k0 + k)].nt), k);
         }
         hipError_t e = hipMemcpyAsync(tb->d, tb->h, b_desc + b_tab, hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess)
+        if (e == hipSuccess) {
             e = launch_dump_batch(reinterpret_cast<const DumpDesc *>(tb->d),
                                   same ? nullptr : reinterpret_cast<const int32_t *>(tb->d + b_desc),
                                   (int)tri64(descs[(size_t)k0].nt), total, stream);
-        if (e == hipSuccess) e = hipEventRecord(tb->ev, stream);
+            // a chunk's slots are reset as its launch is queued, whatever
+            // becomes of the calls behind it
+            if (e == hipSuccess)
+                for (int32_t k = k0; k < k0 + m; ++k)
+                    if (jobs[k].reset) after_reset_export(jobs[k].ctx, jobs[k].slot);
+            const hipError_t em = ring_mark(*tb, stream);
+            if (e == hipSuccess) e = em;
+        }
         if (e != hipSuccess) return map_err(e);
-        tb->pending = true;
-        // (a chunk's slots are reset as its launch is queued)
-        for (int32_t k = k0; k < k0 + m; ++k)
-            if (jobs[k].reset) after_reset_export(jobs[k].ctx, jobs[k].slot);
         k0 += m;
     }
     return XENG_OK;

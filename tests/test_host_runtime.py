@@ -1,0 +1,96 @@
+"""The library's host bookkeeping without a GPU: its HIP calls go to a
+stand-in (tests/fake_hip.cpp) that counts allocations and launches and can
+make a call fail.  Every test runs in a process of its own, so that the
+stand-in reaches no other test."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = r"""
+import ctypes, sys
+sys.path.insert(0, sys.argv[1])
+F = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)
+for f in ("fake_device_bytes", "fake_pool_allocs", "fake_pool_bytes", "fake_launches"):
+    getattr(F, f).restype = ctypes.c_int64
+F.fake_pool_bytes.argtypes = [ctypes.c_int64]
+F.fake_launches.argtypes = [ctypes.c_char_p]
+from paper_2005_09481_amd import xeng as X
+L = X.lib()
+P = 1 << 20          # a sample address: never read, kernels do nothing
+
+def create(n, slots=1, flags=0, budget=0):
+    h = ctypes.c_void_p()
+    assert L.xeng_create(ctypes.byref(X._Config(n, slots, 0, flags, budget)), ctypes.byref(h)) == 0
+    return h
+
+def jobs(*js):
+    return (X._Job * len(js))(*[X._Job(c, s, 0, P, t, stride) for c, s, t, stride in js]), len(js), None
+
+def dumps(*js):
+    return (X._DumpJob * len(js))(*[X._DumpJob(c, s, r, P, 0, 0) for c, s, r in js]), len(js), None
+"""
+
+
+@pytest.fixture(scope="module")
+def fake_hip(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I",
+                    "/opt/rocm/include", os.path.join(ROOT, "tests", "fake_hip.cpp"), "-o", out, "-ldl"],
+                   check=True, capture_output=True)
+    return out
+
+
+@pytest.fixture
+def run(fake_hip, tmp_path):
+    def go(body):
+        env = dict(os.environ, XENG_TUNE_DIR=str(tmp_path))
+        r = subprocess.run([sys.executable, "-c", PRELUDE + body, ROOT, fake_hip], env=env, capture_output=True,
+                           text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr[-3000:]
+        return r.stdout
+    return go
+
+
+def test_stand_in_takes_the_calls(run):
+    run(r"""
+c = create(130, 2)
+assert L.xeng_correlate(c, 0, P, 100, 130, None) == 0
+assert L.xeng_samples_integrated(c, 0) == 100
+assert L.xeng_dump(c, 0, P, 1, None) == 0
+assert F.fake_launches(b"xcorr_mfma") == 1 and F.fake_launches(b"vis_dump") == 1
+assert L.xeng_samples_integrated(c, 0) == 0
+assert L.xeng_destroy(c) == 0
+""")
+
+
+def test_failed_event_record_after_a_batched_export(run):
+    # the export is queued when the event behind it cannot be recorded: its
+    # slots are reset on the device, so on the host too, and the staging
+    # buffer it reads is not reused while it may still run
+    run(r"""
+c = create(130, 3)
+assert L.xeng_correlate_batch(*jobs((c, 0, 64, 130), (c, 1, 64, 130), (c, 2, 64, 130))) == 0
+F.fake_clear()
+F.fake_fail_records(1)
+assert L.xeng_dump_batch(*dumps((c, 0, 1), (c, 1, 0))) == X.XENG_EDEVICE
+assert F.fake_launches(b"vis_dump_batch") == 1
+assert [L.xeng_samples_integrated(c, s) for s in range(3)] == [0, 64, 64]
+assert F.fake_stream_syncs() == 1
+assert L.xeng_dump_batch(*dumps((c, 0, 1), (c, 1, 1))) == 0
+assert [L.xeng_samples_integrated(c, s) for s in range(3)] == [0, 0, 64]
+""")
+
+
+def test_failed_event_record_after_a_batched_correlation(run):
+    # the call reports the error, after the launch that reads its staging
+    # buffer has ended
+    run(r"""
+c = create(130, 2)
+F.fake_fail_records(1)
+assert L.xeng_correlate_batch(*jobs((c, 0, 64, 130), (c, 1, 64, 130))) == X.XENG_EDEVICE
+assert F.fake_launches(b"xcorr_mfma") == 1 and F.fake_stream_syncs() == 1
+""")
