@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <numeric>
 #include <unordered_map>
 
 namespace xeng {
@@ -56,6 +57,26 @@ struct UnitRef {
     int64_t wc;   // cost of one stage (unit_stage_cost)
 };
 
+// The smallest budget from `lo` upward that fits, where every larger one then
+// fits too: steps of `step`, twice as long each time, then bisection.
+template <typename Fits> int64_t smallest_budget(int64_t lo, int64_t step, Fits fits)
+{
+    int64_t hi = lo;
+    while (!fits(hi)) {
+        lo = hi + 1;
+        hi += step;
+        step *= 2;
+    }
+    while (lo < hi) {
+        const int64_t mid = lo + (hi - lo) / 2;
+        if (fits(mid))
+            hi = mid;
+        else
+            lo = mid + 1;
+    }
+    return lo;
+}
+
 // Greedy fill: workgroups in order, each taking pieces of the linear (job,
 // unit, stage) order until its cost (stage costs + overhead per piece)
 // would exceed `budget`.  Returns the number of workgroups used (or grid + 1 if
@@ -73,7 +94,11 @@ int64_t fill(const std::vector<UnitRef> &units, int64_t budget, int64_t overhead
                 if (++w >= grid) return grid + 1;
                 left = budget;
             }
-            const int64_t take = std::min({units[u].ns - done, (left - overhead) / wc, cap});
+            // (a whole rest that fits needs no division)
+            const int64_t rest = units[u].ns - done;
+            const int64_t take = rest <= cap && rest * wc <= left - overhead
+                                     ? rest
+                                     : std::min({rest, (left - overhead) / wc, cap});
             emit(w, u, done, done + take);
             done += take;
             left -= take * wc + overhead;
@@ -116,18 +141,13 @@ Plan make_plan(const PlanJob *jobs, int n_jobs, int max_wgs, int min_stages, Til
                               (int64_t)units.size() * MAX_UNIT_SPLIT}));
 
     // Smallest per-workgroup budget with which the greedy fill fits in
-    // `grid` workgroups (the fill is monotone in the budget).
+    // `grid` workgroups (the fill is monotone in the budget), from the mean
+    // cost upward: every unit pays the overhead at least once.
     auto none = [](int64_t, size_t, int64_t, int64_t) {};
-    int64_t lo = ovh + STAGE_COST, hi = ovh + total_cost + 1;
-    hi = std::max(hi, (total_cost + grid - 1) / grid + ovh * ((int64_t)units.size() + 1) + 1);
-    while (fill(units, hi, ovh, cap, grid, none) > grid) hi *= 2;
-    while (lo < hi) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (fill(units, mid, ovh, cap, grid, none) <= grid)
-            hi = mid;
-        else
-            lo = mid + 1;
-    }
+    const int64_t mean = (total_cost + ovh * (int64_t)units.size() + grid - 1) / grid;
+    const int64_t lo = smallest_budget(std::max(ovh + STAGE_COST, mean), ovh, [&](int64_t budget) {
+        return fill(units, budget, ovh, cap, grid, none) <= grid;
+    });
 
     struct Raw { Piece p; int32_t wg; size_t unit; };
     std::vector<Raw> raw;
@@ -165,88 +185,76 @@ namespace {
 // Interleaved bits of (a, b): units close in both coordinates come close
 // together in this order, so a run of consecutive units covers a compact
 // block of the triangle (few distinct row and column blocks).
-uint64_t morton(uint32_t a, uint32_t b)
+uint32_t spread(uint32_t x)   // bit k of the low 16 to bit 2 k
 {
-    uint64_t r = 0;
-    for (int k = 0; k < 16; ++k) r |= (uint64_t)((a >> k) & 1u) << (2 * k + 1) | (uint64_t)((b >> k) & 1u) << (2 * k);
-    return r;
+    x = (x | (x << 8)) & 0x00FF00FFu;
+    x = (x | (x << 4)) & 0x0F0F0F0Fu;
+    x = (x | (x << 2)) & 0x33333333u;
+    return (x | (x << 1)) & 0x55555555u;
 }
+uint32_t morton(uint32_t a, uint32_t b) { return spread(a) << 1 | spread(b); }
 
-}  // namespace
-
-namespace {
-
-// One candidate of make_plan_xcd for segment length L (in stages of a full
-// unit): the pieces of each logical workgroup, and the largest workgroup
-// cost (stage costs + overhead per piece, in sixteenths of a stage).  A
-// unit whose stages cost less (`wc`) takes longer segments of the same
-// cost.  Returns -1 if the work does not fit in G workgroups.
+// One candidate of make_plan_xcd: segments of length L (in stages of a full
+// unit).  A unit whose stages cost less takes longer segments of the same
+// cost, so units of one stage cost are cut alike.
 struct XSeg {
     int64_t u, s0, s1;
 };
 
-int64_t xcd_candidate(const std::vector<int64_t> &wc, int64_t ns, int64_t G, int64_t L, int64_t ovh, int64_t cap,
-                      std::vector<std::vector<XSeg>> *out)
+struct XcdCut {
+    struct Class {
+        int64_t wc, units;   // stage cost, units of that cost
+        int64_t len, full, tail;   // segment length, full segments of a unit, stages left over
+    } cls[2];
+    int64_t main = 0;         // full segments of all units
+    int64_t tails = 0;        // units with a tail
+    int64_t tail_cost = 0;    // of their stages
+    int64_t worst = 0;        // largest cost of a full segment with its overhead
+};
+
+void cut(XcdCut &x, int64_t ns, int64_t L, int64_t ovh, int64_t cap)
 {
-    const int64_t U = (int64_t)wc.size();
-    std::vector<int64_t> Lu((size_t)U), Fu((size_t)U), ru((size_t)U);
-    int64_t main = 0, max_f = 0, worst = 0;
-    bool tails = false;
-    for (int64_t u = 0; u < U; ++u) {
-        Lu[(size_t)u] = std::min({ns, cap, std::max<int64_t>(1, L * STAGE_COST / wc[(size_t)u])});
-        Fu[(size_t)u] = ns / Lu[(size_t)u];                  // full segments of the unit
-        ru[(size_t)u] = ns - Fu[(size_t)u] * Lu[(size_t)u];  // its tail
-        main += Fu[(size_t)u];
-        max_f = std::max(max_f, Fu[(size_t)u]);
-        tails = tails || ru[(size_t)u] > 0;
-        if (Fu[(size_t)u] > 0) worst = std::max(worst, Lu[(size_t)u] * wc[(size_t)u] + ovh);
+    x.main = x.tails = x.tail_cost = x.worst = 0;
+    for (XcdCut::Class &c : x.cls) {
+        if (c.units == 0) continue;
+        c.len = std::min({ns, cap, std::max<int64_t>(1, L * STAGE_COST / c.wc)});
+        c.full = ns / c.len;
+        c.tail = ns - c.full * c.len;
+        x.main += c.units * c.full;
+        if (c.tail > 0) {
+            x.tails += c.units;
+            x.tail_cost += c.units * c.tail * c.wc;
+        }
+        x.worst = std::max(x.worst, c.len * c.wc + ovh);
     }
-    if (main > G || (tails && main == G)) return -1;
-    if (out) {
-        out->assign((size_t)G, {});
-        int64_t k = 0;
-        for (int64_t p = 0; p < max_f; ++p)
-            for (int64_t u = 0; u < U; ++u)
-                if (p < Fu[(size_t)u])
-                    (*out)[(size_t)k++].push_back(XSeg{u, p * Lu[(size_t)u], (p + 1) * Lu[(size_t)u]});
-    }
-    if (!tails) return worst;
-    // the tails: stream-K over the remaining workgroups, smallest budget that fits
-    auto fill = [&](int64_t budget, bool emit) -> bool {
-        int64_t k = main, left = budget, u = 0, done = 0;
-        while (u < U) {
-            const int64_t r = ru[(size_t)u], w = wc[(size_t)u];
-            if (r == 0) {
-                ++u;
-                continue;
-            }
-            if (left - ovh < w) {
+}
+
+// The tails of units of classes cls[..] by the stream-K fill, over workgroups
+// `first` .. G - 1 of `budget` each: emit(workgroup, unit, first stage, end
+// stage).  False if they do not fit.
+template <typename Emit>
+bool fill_tails(const XcdCut &x, const std::vector<uint8_t> &cls, int64_t first, int64_t G, int64_t budget, int64_t ovh,
+                int64_t cap, Emit emit)
+{
+    int64_t k = first, left = budget;
+    for (size_t u = 0; u < cls.size(); ++u) {
+        const XcdCut::Class &c = x.cls[cls[u]];
+        int64_t done = 0;
+        while (done < c.tail) {
+            if (left - ovh < c.wc) {
                 if (++k >= G) return false;
                 left = budget;
             }
-            const int64_t take = std::min({r - done, (left - ovh) / w, cap});
-            const int64_t base = Fu[(size_t)u] * Lu[(size_t)u];
-            if (emit) (*out)[(size_t)k].push_back(XSeg{u, base + done, base + done + take});
+            const int64_t rest = c.tail - done;
+            const int64_t take = rest <= cap && rest * c.wc <= left - ovh
+                                     ? rest
+                                     : std::min({rest, (left - ovh) / c.wc, cap});
+            emit(k, u, c.full * c.len + done, c.full * c.len + done + take);
             done += take;
-            left -= take * w + ovh;
-            if (done == r) {
-                ++u;
-                done = 0;
-            }
+            left -= take * c.wc + ovh;
         }
-        return true;
-    };
-    int64_t lo = ovh + STAGE_COST, hi = ovh + STAGE_COST;
-    while (!fill(hi, false)) hi *= 2;
-    while (lo < hi) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (fill(mid, false))
-            hi = mid;
-        else
-            lo = mid + 1;
     }
-    if (out) fill(lo, true);
-    return std::max(worst, lo);
+    return true;
 }
 
 }  // namespace
@@ -255,42 +263,81 @@ bool make_plan_xcd(const PlanJob &job, int max_wgs, TileShape shape, Plan *out, 
 {
     const int64_t G = max_wgs;
     if (G < XCDS || G % XCDS != 0 || job.n <= 0 || job.t <= 0 || shape == TileShape::Narrow) return false;
-    std::vector<std::pair<int, int>> units = plan_units(job.n, shape);
-    const int64_t U = (int64_t)units.size();
-    const int64_t ns = (job.t + STAGE - 1) / STAGE;
-    const int64_t ovh_st = piece_overhead(shape);
-    const int64_t cap = cap_override > 0 ? cap_override : piece_cap(shape);
-    const int col_scale = shape == TileShape::Wide ? 2 : 1;
-    std::stable_sort(units.begin(), units.end(), [col_scale](const std::pair<int, int> &a, const std::pair<int, int> &b) {
-        return morton((uint32_t)a.first, (uint32_t)(col_scale * a.second)) <
-               morton((uint32_t)b.first, (uint32_t)(col_scale * b.second));
-    });
     const int64_t nt = n_tiles_side(job.n);
-    std::vector<int64_t> wc((size_t)U);
-    int64_t total_cost = 0;
-    for (int64_t u = 0; u < U; ++u) {
-        wc[(size_t)u] = unit_stage_cost(shape == TileShape::Wide, units[(size_t)u].first, units[(size_t)u].second, nt);
-        total_cost += ns * wc[(size_t)u];
-    }
+    const int64_t ns = (job.t + STAGE - 1) / STAGE;
+    const int64_t ovh = piece_overhead(shape) * STAGE_COST;
+    const int64_t cap = cap_override > 0 ? cap_override : piece_cap(shape);
+    const std::vector<std::pair<int, int>> rows = plan_units(job.n, shape);
+    const size_t U = rows.size();
+    XcdCut x;
+    x.cls[0] = {STAGE_COST, 0, 0, 0, 0};
+    x.cls[1] = {HALF_WINDOW_COST, 0, 0, 0, 0};
+    for (const auto &u : rows)
+        x.cls[unit_stage_cost(shape == TileShape::Wide, u.first, u.second, nt) == STAGE_COST ? 0 : 1].units++;
+    const int64_t total_cost = ns * (x.cls[0].units * x.cls[0].wc + x.cls[1].units * x.cls[1].wc);
     // segment lengths around the balanced share (longer ones leave less
     // for the tail workgroups): the candidate with the smallest largest
     // workgroup cost wins
     const int64_t L0 = (total_cost + STAGE_COST * G - 1) / (STAGE_COST * G);
     if (L0 < XCD_MIN_SEGMENT || L0 >= ns) return false;
-    int64_t best_L = -1, best_cost = -1;
-    for (int64_t L = std::min({L0 + 4 * ovh_st, cap, ns - 1}); L >= std::max<int64_t>(XCD_MIN_SEGMENT, L0 - ovh_st);
-         --L) {
-        const int64_t c = xcd_candidate(wc, ns, G, L, ovh_st * STAGE_COST, cap, nullptr);
-        if (c >= 0 && (best_cost < 0 || c < best_cost)) {
-            best_cost = c;
-            best_L = L;
+
+    // the units in Morton order
+    std::vector<std::pair<uint32_t, uint32_t>> order(U);   // (key, index into rows)
+    const int col_scale = shape == TileShape::Wide ? 2 : 1;
+    for (size_t u = 0; u < U; ++u)
+        order[u] = {morton((uint32_t)rows[u].first, (uint32_t)(col_scale * rows[u].second)), (uint32_t)u};
+    std::sort(order.begin(), order.end());
+    std::vector<std::pair<int, int>> units(U);
+    std::vector<uint8_t> cls(U);
+    for (size_t u = 0; u < U; ++u) {
+        units[u] = rows[order[u].second];
+        cls[u] = unit_stage_cost(shape == TileShape::Wide, units[u].first, units[u].second, nt) == STAGE_COST ? 0 : 1;
+    }
+
+    // A candidate is cut in constant time.  The fill of its tails, a pass over
+    // the units, runs where their mean leaves it a chance, and the search for
+    // its smallest budget only if it fits the best cost so far (of equal
+    // candidates the one of the longest segments wins).  Taken in scattered
+    // order, few candidates are better than all before them.  N = 512, T =
+    // 30000 (36 regions): 20 us, 1400 with every candidate's budget searched.
+    auto none = [](int64_t, size_t, int64_t, int64_t) {};
+    auto tails_mean = [&] { return (x.tail_cost + ovh * x.tails + G - x.main - 1) / (G - x.main); };
+    auto fits = [&](int64_t b) { return fill_tails(x, cls, x.main, G, b, ovh, cap, none); };
+    const int64_t L_min = std::max<int64_t>(XCD_MIN_SEGMENT, L0 - piece_overhead(shape));
+    const int64_t L_count = std::min({L0 + 4 * piece_overhead(shape), cap, ns - 1}) - L_min + 1;
+    int64_t best_L = -1, best_cost = INT64_MAX, step = std::max<int64_t>(1, L_count * 5 / 8);
+    while (std::gcd(step, L_count) > 1) ++step;
+    for (int64_t k = 0; k < L_count; ++k) {
+        const int64_t L = L_min + k * step % L_count;
+        cut(x, ns, L, ovh, cap);
+        if (x.main > G || (x.tails > 0 && x.main == G)) continue;
+        const int64_t limit = L > best_L ? best_cost : best_cost - 1;   // what this one may cost
+        int64_t cost = x.worst;
+        if (x.tails > 0) cost = std::max(cost, tails_mean());
+        if (cost > limit) continue;
+        if (x.tails > 0 && !fits(cost)) {
+            if (limit < INT64_MAX - 1 && !fits(limit)) continue;
+            cost = smallest_budget(cost + 1, ovh, fits);
         }
+        best_cost = cost;
+        best_L = L;
     }
     if (best_L < 0) return false;
-    std::vector<std::vector<XSeg>> logical;
-    xcd_candidate(wc, ns, G, best_L, ovh_st * STAGE_COST, cap, &logical);
+    cut(x, ns, best_L, ovh, cap);
+    std::vector<std::vector<XSeg>> logical((size_t)G);
+    size_t next = 0;
+    for (int64_t p = 0; p < std::max(x.cls[0].full, x.cls[1].full); ++p)
+        for (size_t u = 0; u < U; ++u) {
+            const XcdCut::Class &c = x.cls[cls[u]];
+            if (p < c.full) logical[next++].push_back(XSeg{(int64_t)u, p * c.len, (p + 1) * c.len});
+        }
+    if (x.tails > 0)
+        fill_tails(x, cls, x.main, G, smallest_budget(std::max(ovh + STAGE_COST, tails_mean()), ovh, fits), ovh, cap,
+                   [&](int64_t k, size_t u, int64_t s0, int64_t s1) {
+                       logical[(size_t)k].push_back(XSeg{(int64_t)u, s0, s1});
+                   });
     // a unit cut into several pieces is shared: flushed with atomics
-    std::vector<int> pieces_of(units.size(), 0);
+    std::vector<int> pieces_of(U, 0);
     for (const auto &v : logical)
         for (const XSeg &sg : v) pieces_of[(size_t)sg.u]++;
     // logical workgroup k runs on XCD k / (G / XCDS): physical id

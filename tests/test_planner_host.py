@@ -1,0 +1,135 @@
+"""The planner on the CPU, for every unit shape: the XCD-aware search finds
+the cut of least cost, and planning a call's work costs less than the call."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SQUARE, WIDE, NARROW, TILE, REGION = range(5)
+OVERHEAD = {SQUARE: 8, WIDE: 16, NARROW: 8, TILE: 24, REGION: 40}
+
+
+@pytest.fixture(scope="module")
+def P(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("planner") / "libplanner_host.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__",
+                    "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "paper_2005_09481_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "planner_host.cpp"),
+                    os.path.join(ROOT, "paper_2005_09481_amd", "csrc", "xeng_plan.cpp"), "-o", out],
+                   check=True, capture_output=True)
+    L = ctypes.CDLL(out)
+    i32, i64, p32, p64 = ctypes.c_int32, ctypes.c_int64, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int64)
+    L.host_plan.restype = i64
+    L.host_plan.argtypes = [p32, p64, i32, i32, i32, i32, i32, i64, p64, i64]
+    L.host_choose.argtypes = [i32, i64, i32, i32, p32]
+    L.host_choose_batch.argtypes = [p32, p64, i32, i32]
+    L.host_plan_us.restype = ctypes.c_double
+    L.host_plan_us.argtypes = [i32, i64, i32, i32, i32]
+    return L
+
+
+def plan(P, jobs, wgs, shape, min_stages=4, xcd=False, cap=0):
+    """Rows (job, i, j, t0, t1, atomic, workgroup), or None."""
+    n = (ctypes.c_int32 * len(jobs))(*[j[0] for j in jobs])
+    t = (ctypes.c_int64 * len(jobs))(*[j[1] for j in jobs])
+    args = (n, t, len(jobs), wgs, min_stages, shape, int(xcd), cap)
+    count = P.host_plan(*args, None, 0)
+    if count < 0:
+        return None
+    out = np.zeros((max(count, 1), 7), dtype=np.int64)
+    assert P.host_plan(*args, out.ctypes.data_as(ctypes.POINTER(ctypes.c_int64)), count) == count
+    return out[:count]
+
+
+def units_of(n, shape):
+    nt, nr = -(-n // 128), -(-n // 64)
+    if shape == NARROW:
+        return [(0, 0)]
+    if shape == REGION:
+        return [(i, j) for i in range(nr) for j in range(i, nr)]
+    if shape == WIDE:
+        return [(i, j) for i in range(nt) for j in range(i // 2, (nt + 1) // 2)]
+    return [(i, j) for i in range(nt) for j in range(i, nt)]
+
+
+def stage_cost(i, j, n, shape):
+    """Sixteenths of a stage: 13 for a wide window with one tile outside the triangle."""
+    nt = -(-n // 128)
+    return 13 if shape == WIDE and (i <= 2 * j < nt) != (i <= 2 * j + 1 < nt) else 16
+
+
+def workgroup_costs(pieces, n, shape):
+    cost = {}
+    for _, i, j, t0, t1, _, w in pieces.tolist():
+        cost[w] = cost.get(w, 0) + -(-(t1 - t0) // 64) * stage_cost(i, j, n, shape) + 16 * OVERHEAD[shape]
+    return cost
+
+
+def tails_fit(tails, wgs, budget, ovh):
+    """Whether the tails (stage cost, stages) fill at most `wgs` workgroups of `budget`, in order."""
+    k, left = 0, budget
+    for wc, r in tails:
+        while r > 0:
+            if left - ovh < wc:
+                k, left = k + 1, budget
+                if k >= wgs:
+                    return False
+            take = min(r, (left - ovh) // wc)
+            r, left = r - take, left - take * wc - ovh
+    return True
+
+
+def least_cost(n, t, wgs, shape):
+    """The smallest largest workgroup cost of any cut into segments and tails."""
+    ns, ovh = -(-t // 64), OVERHEAD[shape]
+    order = sorted(units_of(n, shape), key=lambda u: sum(((u[0] >> k) & 1) << (2 * k + 1) |
+                                                         (((2 if shape == WIDE else 1) * u[1] >> k) & 1) << (2 * k)
+                                                         for k in range(16)))
+    wc = [stage_cost(i, j, n, shape) for i, j in order]
+    mean = -(-ns * sum(wc) // (16 * wgs))
+    best = None
+    for L in range(max(32, mean - ovh), min(mean + 4 * ovh, 1023, ns - 1) + 1):
+        seg = [min(ns, 1023, max(1, L * 16 // c)) for c in wc]
+        full = [ns // s for s in seg]
+        tails = [(c, ns - f * s) for c, f, s in zip(wc, full, seg) if ns > f * s]
+        rest = wgs - sum(full)
+        if rest < 0 or (tails and rest == 0):
+            continue
+        cost = max(s * c + 16 * ovh for s, c in zip(seg, wc))
+        if tails:
+            lo, hi = 16 * ovh + 16, 16 * ovh * len(tails) + sum(c * r for c, r in tails)
+            while lo < hi:
+                mid = (lo + hi) // 2
+                if tails_fit(tails, rest, mid, 16 * ovh):
+                    hi = mid
+                else:
+                    lo = mid + 1
+            cost = max(cost, lo)
+        best = cost if best is None else min(best, cost)
+    return best
+
+
+@pytest.mark.parametrize("n,t,wgs,shape", [
+    (512, 30000, 256, REGION), (300, 32768, 240, REGION), (768, 12000, 256, REGION), (1024, 5000, 256, REGION),
+    (768, 65536, 256, TILE), (1000, 32768, 256, TILE), (2048, 5000, 256, TILE), (1100, 20000, 128, TILE),
+    (2048, 32768, 256, WIDE), (2000, 9000, 256, WIDE), (1536, 30000, 256, WIDE), (1000, 32768, 512, SQUARE),
+])
+def test_xcd_search_finds_the_least_cost(P, n, t, wgs, shape):
+    pieces = plan(P, [(n, t)], wgs, shape, xcd=True)
+    want = least_cost(n, t, wgs, shape)
+    if want is None:
+        assert pieces is None
+    else:
+        # (a unit's last stage may be partial: it costs a whole one)
+        assert max(workgroup_costs(pieces, n, shape).values()) == want
+
+
+@pytest.mark.parametrize("n,t,shape", [(512, 30000, REGION), (1024, 12000, REGION), (1536, 30000, TILE),
+                                       (2048, 5000, TILE), (2048, 30000, WIDE), (3072, 65536, WIDE)])
+def test_planning_takes_less_than_the_call(P, n, t, shape):
+    # a call with new sizes plans its work on the host first; these take 20 to
+    # 100 us where the calls themselves take 30 us and more
+    assert P.host_plan_us(n, t, 256, shape, 30) < 400
