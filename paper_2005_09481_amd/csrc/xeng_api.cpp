@@ -743,10 +743,29 @@ hipError_t launch(const KernelArgs &a, int32_t grid, Kind kind, int waves, uint3
 // (about twice the general kernel's rate for a copy that moves each sample
 // twice).  Below PAD_MIN_N the general kernel's 128 x 128 tiles waste less.
 constexpr int PAD_MIN_N = 256;
-// Rows of the copy start at whole cache lines, so that the DMA kernels' 64-
-// to 256-byte row pieces do too (N = 1000, T = 32768 correlate + export: 87.3
-// us; rows of 1008 bytes and the dword copy took 92.8).
-int pad_pitch(int n) { return (n + 127) / 128 * 128; }
+// Rows of the copy start at whole cache lines where the scratch has room for
+// that, so that the DMA kernels' 64- to 256-byte row pieces do too (N = 1000,
+// T = 32768 correlate + export: 87.3 us; rows of 1008 bytes and the dword copy
+// took 92.8).  What fits the scratch is decided on rows of N rounded up to 16
+// bytes: whole lines would take up to eight times as much for small N.
+int64_t tight_pitch(int n) { return ((int64_t)n + 15) / 16 * 16; }
+int64_t line_pitch(int n) { return ((int64_t)n + 127) / 128 * 128; }
+
+// Rows of one chunk of a call's copy: whole stages, at least one.
+int64_t pad_rows(int64_t n_samples, int64_t pitch, int64_t limit)
+{
+    return std::min<int64_t>(n_samples, std::max<int64_t>(STAGE, limit / pitch / STAGE * STAGE));
+}
+
+// Whole lines for a call that is then cut into no more chunks.
+int64_t pad_pitch(int n, int64_t n_samples, int64_t limit)
+{
+    auto chunks = [&](int64_t pitch) {
+        const int64_t rows = pad_rows(n_samples, pitch, limit);
+        return (n_samples + rows - 1) / rows;
+    };
+    return chunks(line_pitch(n)) <= chunks(tight_pitch(n)) ? line_pitch(n) : tight_pitch(n);
+}
 
 // The device's scratch pool for padded jobs, created on first use: a pool
 // of the library's own that keeps up to 1 GiB between calls (the default
@@ -780,9 +799,9 @@ int pad_pool(DeviceState *st, hipMemPool_t *out)
 int correlate_padded(xeng_ctx *ctx, int32_t slot, const uint8_t *samples, int64_t n_samples, int64_t stride,
                      const Tuning &tu, hipStream_t stream, const uint8_t *flags = nullptr, int block_len = 0)
 {
-    const int n16 = (ctx->n + 15) / 16 * 16, pitch = pad_pitch(ctx->n);
-    const int64_t rows =
-        std::min<int64_t>(n_samples, std::max<int64_t>(STAGE, g_pad_bytes.load() / pitch / STAGE * STAGE));
+    const int n16 = (int)tight_pitch(ctx->n);
+    const int64_t limit = g_pad_bytes.load();
+    const int64_t pitch = pad_pitch(ctx->n, n_samples, limit), rows = pad_rows(n_samples, pitch, limit);
     hipMemPool_t pool = nullptr;
     int prc = pad_pool(ctx->st, &pool);
     if (prc != XENG_OK) return prc;
@@ -876,7 +895,7 @@ struct Part {
 };
 
 // Batched jobs the DMA kernel cannot read in place, with N >= PAD_MIN_N, are
-// copied into one pooled scratch buffer (as many as fit in PAD_SCRATCH_BYTES,
+// copied into one pooled scratch buffer (as many as fit in the scratch limit,
 // in job order; the rest keep the general kernel) and their descriptors
 // point at the copy.  The caller frees *scratch on the stream after the
 // launches.  Called with st->mu held and the device current.
@@ -886,19 +905,27 @@ int pad_batch_jobs(JobList &jl, const Tuning &tu, hipStream_t stream, uint8_t **
     // (FP8 jobs read in place: the general kernel's instance any array, the
     // wide kernel's the arrays it takes as they are)
     if (tu.kernel == XENG_KERNEL_GENERAL || tu.kernel == XENG_KERNEL_FP8) return XENG_OK;
+    const int64_t limit = g_pad_bytes.load();
+    auto bytes_of = [&](size_t k, int64_t pitch) { return (jl.pj[k].t * pitch + 255) / 256 * 256; };
     std::vector<size_t> pick;
-    std::vector<int64_t> off;
     int64_t total = 0;
     for (size_t k = 0; k < jl.descs.size(); ++k) {
         const JobDesc &d = jl.descs[k];
         if ((d.flags & JOB_DMA) || d.n < PAD_MIN_N || jl.pj[k].t <= 0) continue;
-        const int64_t bytes = jl.pj[k].t * (int64_t)pad_pitch(d.n);
-        if (total + bytes > g_pad_bytes.load()) continue;
+        if (total + jl.pj[k].t * tight_pitch(d.n) > limit) continue;
         pick.push_back(k);
-        off.push_back(total);
-        total += (bytes + 255) / 256 * 256;
+        total += bytes_of(k, tight_pitch(d.n));
     }
     if (pick.empty()) return XENG_OK;
+    // whole lines for the jobs that the room left over takes
+    std::vector<int64_t> pitch;
+    for (size_t k : pick) {
+        const int n = jl.descs[k].n;
+        const int64_t more = bytes_of(k, line_pitch(n)) - bytes_of(k, tight_pitch(n));
+        const bool fits = total + more <= limit;
+        pitch.push_back(fits ? line_pitch(n) : tight_pitch(n));
+        if (fits) total += more;
+    }
     hipMemPool_t pool = nullptr;
     int rc = pad_pool(jl.st, &pool);
     if (rc != XENG_OK) return rc;
@@ -907,16 +934,16 @@ int pad_batch_jobs(JobList &jl, const Tuning &tu, hipStream_t stream, uint8_t **
         *scratch = nullptr;
         return map_err(e);
     }
+    uint8_t *dst = *scratch;
     for (size_t i = 0; i < pick.size(); ++i) {
         JobDesc &d = jl.descs[pick[i]];
-        const int n16 = (d.n + 15) / 16 * 16, pitch = pad_pitch(d.n);
-        uint8_t *dst = *scratch + off[i];
-        if ((e = launch_copy_rows(d.samples, d.stride, d.n, jl.pj[pick[i]].t, dst, pitch, nullptr, 1, 0, stream)) !=
+        if ((e = launch_copy_rows(d.samples, d.stride, d.n, jl.pj[pick[i]].t, dst, pitch[i], nullptr, 1, 0, stream)) !=
             hipSuccess)
             return map_err(e);
         d.samples = dst;
-        d.stride = pitch;
-        d.n = n16;   // the padded inputs hold zero samples
+        d.stride = pitch[i];
+        d.n = (int32_t)tight_pitch(d.n);   // the padded inputs hold zero samples
+        dst += bytes_of(pick[i], pitch[i]);
         d.flags |= JOB_DMA;
     }
     return XENG_OK;

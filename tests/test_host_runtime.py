@@ -94,3 +94,45 @@ F.fake_fail_records(1)
 assert L.xeng_correlate_batch(*jobs((c, 0, 64, 130), (c, 1, 64, 130))) == X.XENG_EDEVICE
 assert F.fake_launches(b"xcorr_mfma") == 1 and F.fake_stream_syncs() == 1
 """)
+
+
+def test_padded_batches_fit_the_scratch_they_need(run):
+    # N = 257 needs rows of 272 bytes; whole cache lines (384) are taken only
+    # where the scratch has room, never instead of the DMA kernel
+    run(r"""
+c = create(257, 2)
+def batch(limit, *ts):
+    assert L.xeng_set_pad_chunk_bytes(limit) == 0
+    F.fake_clear()
+    assert L.xeng_correlate_batch(*jobs(*[(c, k, t, 257) for k, t in enumerate(ts)])) == 0
+    copies, general = F.fake_launches(b"copy_rows"), F.fake_launches(b"xcorr_mfma")
+    return copies, general, F.fake_pool_bytes(0) if F.fake_pool_allocs() else 0
+
+assert batch(272 * 640, 640) == (1, 0, 272 * 640)            # exactly the tight rows
+assert batch(272 * 640 - 1, 640) == (0, 1, 0)
+assert batch(384 * 640, 640) == (1, 0, 384 * 640)            # room for whole lines
+assert batch(272 * 1280, 640, 640) == (2, 0, 272 * 1280)
+assert batch((272 + 384) * 640, 640, 640) == (2, 0, (272 + 384) * 640)
+assert batch(0, 640, 640) == (2, 0, 2 * 384 * 640)
+""")
+
+
+def test_padded_calls_take_no_more_chunks_than_they_need(run):
+    run(r"""
+c, small = create(257), create(7, 1, X.XENG_COUNTS)
+def chunks(call, limit):
+    assert L.xeng_set_pad_chunk_bytes(limit) == 0
+    F.fake_clear()
+    assert call() == 0
+    assert F.fake_launches(b"copy_rows") == F.fake_launches(b"xcorr_region") + F.fake_launches(b"xcorr_tile")
+    return F.fake_launches(b"copy_rows")
+
+one = lambda: L.xeng_correlate(c, 0, P, 640, 257, None)
+assert chunks(one, 0) == 1 and F.fake_pool_bytes(0) == 384 * 640
+assert chunks(one, 272 * 640) == 1 and F.fake_pool_bytes(0) == 272 * 640
+assert chunks(one, 272 * 320) == 2
+flagged = lambda: L.xeng_correlate_flagged(small, 0, P, 2048, 7, P, 64, None)
+assert chunks(flagged, 0) == 1 and F.fake_pool_bytes(1) == 128 * 2048      # (behind the counts' masks)
+assert chunks(flagged, 16 * 2048) == 1 and F.fake_pool_bytes(1) == 16 * 2048
+assert chunks(flagged, 16 * 1024) == 2
+""")
