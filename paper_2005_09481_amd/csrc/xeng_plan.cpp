@@ -323,6 +323,12 @@ bool make_plan_xcd(const PlanJob &job, int max_wgs, TileShape shape, Plan *out, 
         best_L = L;
     }
     if (best_L < 0) return false;
+    // The linear order where this one costs more than a piece's overhead
+    // beyond its mean, a bound that order keeps.  It does where a few
+    // workgroups are left for the tails of many units: N = 3840, T = 4096,
+    // 240 windows, 16 workgroups.
+    const int64_t linear = (total_cost + ovh * (int64_t)U + G - 1) / G + 2 * ovh;
+    if (best_cost > linear) return false;
     cut(x, ns, best_L, ovh, cap);
     std::vector<std::vector<XSeg>> logical((size_t)G);
     size_t next = 0;

@@ -59,7 +59,7 @@ std::vector<std::pair<int, int>> plan_units(int n, TileShape shape);
 // has one piece, or a few for the tails, as in the linear plan.  Returns
 // false (nothing written) for a grid that is not a multiple of 8 or a job
 // too short for one segment of XCD_MIN_SEGMENT stages per workgroup.  `cap`
-// as in make_plan.
+// as in make_plan.  False as well where the linear order is clearly better.
 constexpr int XCDS = 8;
 constexpr int64_t XCD_MIN_SEGMENT = 32;
 bool make_plan_xcd(const PlanJob &job, int max_wgs, TileShape shape, Plan *out, int64_t cap = 0);

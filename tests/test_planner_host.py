@@ -133,3 +133,16 @@ def test_planning_takes_less_than_the_call(P, n, t, shape):
     # a call with new sizes plans its work on the host first; these take 20 to
     # 100 us where the calls themselves take 30 us and more
     assert P.host_plan_us(n, t, 256, shape, 30) < 400
+
+
+@pytest.mark.parametrize("n,t,shape", [(3840, 4096, WIDE), (1408, 8192, REGION), (1408, 49152, REGION),
+                                       (2816, 8192, TILE), (1296, 4096, REGION), (2048, 32768, WIDE),
+                                       (1024, 16384, REGION), (1000, 32768, TILE)])
+def test_xcd_plan_is_never_far_behind_the_linear_one(P, n, t, shape):
+    # with few workgroups left for the tails of many units it would be: the
+    # linear order is then taken
+    pieces, linear = plan(P, [(n, t)], 256, shape, xcd=True), plan(P, [(n, t)], 256, shape)
+    if pieces is not None:
+        cost, want = workgroup_costs(pieces, n, shape), workgroup_costs(linear, n, shape)
+        assert max(cost.values()) <= max(want.values()) + 16 * OVERHEAD[shape]
+
