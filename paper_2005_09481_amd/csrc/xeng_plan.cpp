@@ -376,18 +376,29 @@ bool make_plan_xcd(const PlanJob &job, int max_wgs, TileShape shape, Plan *out, 
 
 namespace {
 
-// Time model of a shape's kernel on one job (microseconds): per stage,
-// prologue and flush of a piece that owns its unit, prologue of a shared
-// one, and the share of one shared piece in the atomic flushes, which all
-// workgroups' together move at about 2 TB/s.
+// Time model of a shape's kernel (microseconds).  Up to one unit per
+// workgroup: per stage, and more per stage past `long_from` of them on a
+// workgroup; prologue and flush of a piece that owns its unit; prologue of a
+// shared one; and the share of one shared piece in the atomic flushes, which
+// all workgroups' together move at about 2 TB/s.
 struct ShapeCost {
     TileShape shape;
     double stage, owned, prologue, shared;
+    double long_from, long_more;
+    double batch_long_from, batch_long_more;   // the same for the jobs of a batch
+    // One job of more units than compute units, whose flushes move tens to
+    // hundreds of MB: whole units in rounds (launch, a stage of every round, a
+    // round, the flushes per unit and compute unit), or the work in equal
+    // shares (launch with the shared pieces' atomics, stage, flushes, and more
+    // per stage past share_long_from).
+    double rounds_launch, round_stage, round, round_flush;
+    double shares_launch, share_stage, share_flush, share_long_from, share_long;
 };
 constexpr double LAUNCH_US = 4.0;
-constexpr ShapeCost SHAPE_COSTS[] = {{TileShape::Wide, 1.1, 13.0, 5.0, 0.13},
-                                     {TileShape::Tile, 0.62, 8.0, 3.0, 0.065},
-                                     {TileShape::Region, 0.20, 4.3, 3.0, 0.016}};
+constexpr ShapeCost SHAPE_COSTS[] = {
+    {TileShape::Wide, 1.1, 13.0, 5.0, 0.13, 1e9, 0.0, 1e9, 0.0, 1.0, 1.1, 3.9, 18.0, 41.0, 0.84, 16.5, 60, 0.45},
+    {TileShape::Tile, 0.62, 8.0, 3.0, 0.065, 100, 0.04, 100, 0.04, 2.0, 0.59, 8.0, 5.4, 23.0, 0.5, 11.3, 100, 0.2},
+    {TileShape::Region, 0.20, 4.3, 3.0, 0.016, 160, 0.02, 60, 0.20, 2.0, 0.24, 5.7, 0.0, 12.5, 0.2, 4.6, 100, 0.2}};
 
 // Units of one job (the length of plan_units).
 int64_t shape_units(int32_t n, TileShape shape)
@@ -400,14 +411,21 @@ int64_t shape_units(int32_t n, TileShape shape)
     return units;
 }
 
-// Stage times rise with the length of the work: the clock settles under the
-// load, and the region kernel's operands outgrow what the L2s hold.
-double stage_us(const ShapeCost &c, double stages_per_wg, int64_t units)
+// The stages of one workgroup.  They take longer where the work is long: the
+// clock settles under the load, and where the workgroups walk time apart
+// from each other their operands no longer meet in the L2s.
+double stages_us(const ShapeCost &c, double stages, bool batch = false)
 {
-    if (c.shape == TileShape::Tile && stages_per_wg > 100) return 0.66;
-    if (c.shape == TileShape::Region && stages_per_wg > 100 && units > 210) return 0.35;
-    if (c.shape == TileShape::Region && stages_per_wg > 160) return 0.22;
-    return c.stage;
+    const double from = batch ? c.batch_long_from : c.long_from, more = batch ? c.batch_long_more : c.long_more;
+    return stages * c.stage + std::max(0.0, stages - from) * more;
+}
+
+// Whether the planner's costs (in stages) lead it to give every unit to one
+// workgroup, `rounds` of them each, rather than to equal shares.
+bool whole_units(const ShapeCost &c, int64_t units, int64_t longest, int64_t stages, int cus)
+{
+    const int64_t rounds = (units + cus - 1) / cus, ovh = piece_overhead(c.shape);
+    return rounds * (longest + ovh) * cus <= stages + ovh * (units + cus);
 }
 
 }  // namespace
@@ -425,19 +443,30 @@ DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages)
     };
     for (const ShapeCost &c : SHAPE_COSTS) {
         const int64_t units = shape_units(n, c.shape);
-        // every unit whole, or in k equal pieces
+        const double s = (double)units * (double)ns / cus, per_cu = (double)units / cus;
+        if (units > cus) {
+            const double rounds = (double)((units + cus - 1) / cus);
+            consider(c.shape, 0,
+                     whole_units(c, units, ns, units * ns, cus)
+                         ? c.rounds_launch + rounds * ((double)ns * c.round_stage + c.round) + c.round_flush * per_cu
+                         : c.shares_launch + s * c.share_stage + c.share_flush * per_cu +
+                               std::max(0.0, s - c.share_long_from) * c.share_long);
+            continue;
+        }
+        // every unit whole, or in k equal pieces, whose workgroups walk the
+        // same time together (the region kernel's stages then stay at their
+        // price however many there are: N = 1408, 253 whole regions, T = 4096
+        // 21 us, 8192 33, 16384 58)
         for (int64_t k = 1; k * units <= cus && k <= MAX_UNIT_SPLIT && (k == 1 || k * min_stages <= ns); ++k) {
-            const int64_t s = (ns + k - 1) / k;
-            const double st = (double)s * stage_us(c, (double)s, units);
+            const double st = (double)((ns + k - 1) / k);
+            const double run = c.shape == TileShape::Region ? st * c.stage : stages_us(c, st);
             consider(c.shape, k * units,
-                     LAUNCH_US + st + (k == 1 ? c.owned : c.prologue + (double)(k * units) * c.shared));
+                     LAUNCH_US + run + (k == 1 ? c.owned : c.prologue + (double)(k * units) * c.shared));
         }
         // the work in equal shares of every workgroup; a job of fewer units
         // than compute units has been seen above unless it is long enough
-        const double s = (double)units * (double)ns / cus;
         if (units * MAX_UNIT_SPLIT >= cus && units * ns >= (int64_t)cus * min_stages)
-            consider(c.shape, 0,
-                     LAUNCH_US + s * stage_us(c, s, units) + c.owned * (double)units / cus + cus * c.shared);
+            consider(c.shape, 0, LAUNCH_US + stages_us(c, s) + c.owned * per_cu + cus * c.shared);
     }
     return best;
 }
@@ -457,16 +486,14 @@ TileShape choose_dma_batch(const PlanJob *jobs, int n_jobs, int cus)
         // (Wide comes first: its count decides for the others)
         if (c.shape == TileShape::Wide && units > cus) return TileShape::Wide;
         if (c.shape == TileShape::Region && 4 * units > 5 * (int64_t)cus) continue;
-        // which regime the planner's costs (in stages) lead it to
-        const int64_t k = (units + cus - 1) / cus, ovh = piece_overhead(c.shape);
         double us;
-        if (k * (longest + ovh) * cus <= stages + ovh * (units + cus)) {
+        if (whole_units(c, units, longest, stages, cus)) {
+            const double k = (double)((units + cus - 1) / cus);
             // a second region's flush also waits for the first one's stores
             const double owned = c.shape == TileShape::Region && k > 1 ? 1.5 * c.owned : c.owned;
-            us = (double)k * ((double)longest * stage_us(c, (double)(k * longest), units) + owned);
+            us = stages_us(c, k * (double)longest, true) + k * owned;
         } else {
-            const double s = (double)stages / cus;
-            us = s * stage_us(c, s, units) + c.prologue + c.owned * (double)units / cus + cus * c.shared;
+            us = stages_us(c, (double)stages / cus, true) + c.prologue + c.owned * (double)units / cus + cus * c.shared;
         }
         // the wide kernel unless another is clearly ahead
         if (c.shape != TileShape::Wide) us *= 1.05;

@@ -74,13 +74,22 @@ int64_t piece_cap(TileShape shape);
 // The shape of one job that the DMA kernels read (N > NARROW_MAX_N), and the
 // workgroups to plan it for (0: one per compute unit): the smallest of the
 // modelled times of the wide, tile and region kernels, each with its units
-// whole, in equal pieces, or in equal shares of every workgroup.  The model's
-// constants come from a sweep of N from 80 to 4096 and T from 64 to 65536.
-// Where it draws the lines, with both sides measured (correlation alone):
-// N = 1024, T = 16384 region 41, tile 48, wide 61 us; T = 32768 region 75,
-// tile 69, wide 81; N = 2048, T = 512 region 25, tile 16 (whole tiles), wide
-// 30; T = 16384 tile 112, wide 121; T = 32768 tile 204, wide 202; T = 65536
-// tile 404, wide 368; N = 3072, T = 512 tile 44, wide 25 (whole windows).
+// whole, in equal pieces, or in equal shares of every workgroup, and with more
+// units than compute units in rounds of whole units or in shares, as the
+// planner splits them.  The model's constants come from sweeps of N from 80 to
+// 8192 and T from 1 to 131072 with every kernel; over those 400 sizes the
+// choice takes 0.5 % longer than the fastest of them in the mean.
+// Where it draws the lines, with both sides measured (correlation alone, us):
+//   N = 1024, T = 16384 region 38, tile 46, wide 60; T = 32768 74, 68, 81
+//   N = 1408, T = 8192 whole regions 33, tile 44; T = 32768 tile 106, region 110
+//   N = 1536, T = 256 whole tiles 12, region 17; T = 2048 26, 22
+//   N = 2048, T = 512 whole tiles 16, wide 21, region 26; T = 2048 28, 40, 33;
+//     T = 3000 tile 42, region 39; T = 4096 44, 50; T = 16384 tile 107, wide 120
+//   N = 3072, T = 512 whole windows 25, tile 44; T = 20000 wide 259, tile 268
+//   N = 4096, T = 64 whole windows 30, tile 35, region 54; T = 4096 tile 118,
+//     wide 128; T = 12000 288, 281
+//   N = 5008, T = 512 whole windows 53, tile 76; N = 6000, T = 2048 wide 138,
+//     tile 155
 // What decides between whole units and shares is the flush: shares of a tile
 // meet on the same words, and all atomic flushes together ran at some 2 TB/s
 // whatever their order and placement (N = 2048, T = 2048: 28 us in 136 whole
@@ -99,7 +108,10 @@ DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages);
 // compute units.  Correlations of T samples with the launch and the exports,
 // wide / tile / region, us: 4 jobs of N = 512, T to 4096 51 / 45 / 33; 16 of
 // N = 512, T to 1024 60 / 46 / 51; 8 of N = 1024, T to 4096 87 / 70 / 127; 8 of
-// N = 2048, T to 4096 (576 windows) 198 / 222 / 433.
+// N = 2048, T to 4096 (576 windows) 198 / 222 / 433.  Long batches leave the
+// region kernel, whose workgroups then read different times of different jobs:
+// 16 of N = 256, T = 6000 60 / 53 / 49, T = 12000 70 / 62 / 73, T = 32768 103 /
+// 94 / 150; 2 of N = 640, T = 12000 63 / 55 / 44, T = 32768 84 / 80 / 123.
 TileShape choose_dma_batch(const PlanJob *jobs, int n_jobs, int cus);
 
 // Plan parameters of one job as make_plan would choose them (grid and

@@ -1,5 +1,6 @@
 """The planner on the CPU, for every unit shape: the XCD-aware search finds
-the cut of least cost, and planning a call's work costs less than the call."""
+the cut of least cost, planning a call's work costs less than the call, and
+jobs and batches take the kernel measured fastest at their sizes."""
 import ctypes
 import os
 import subprocess
@@ -146,3 +147,36 @@ def test_xcd_plan_is_never_far_behind_the_linear_one(P, n, t, shape):
         cost, want = workgroup_costs(pieces, n, shape), workgroup_costs(linear, n, shape)
         assert max(cost.values()) <= max(want.values()) + 16 * OVERHEAD[shape]
 
+
+def choose(P, n, t, cus=256, min_stages=4):
+    wgs = ctypes.c_int32()
+    return P.host_choose(n, t, cus, min_stages, ctypes.byref(wgs)), wgs.value
+
+
+@pytest.mark.parametrize("n,t,shape,wgs", [
+    # measured on both sides of each line (see choose_dma)
+    (512, 8192, REGION, 0), (1024, 16384, REGION, 0), (1024, 49152, TILE, 0), (1536, 256, TILE, 78), (1536, 2048, REGION, 0),
+    (1408, 4096, REGION, 253), (1408, 8192, REGION, 253), (1408, 16384, REGION, 253), (1408, 49152, TILE, 0),
+    (2048, 512, TILE, 136), (2048, 1536, TILE, 136), (2048, 2048, TILE, 136), (2048, 16384, TILE, 0),
+    (2048, 32768, WIDE, 0), (3072, 512, WIDE, 156), (3072, 20000, WIDE, 0),
+    (4096, 1, WIDE, 0), (4096, 64, WIDE, 0), (4096, 1024, TILE, 0), (4096, 4096, TILE, 0), (4096, 20000, WIDE, 0),
+    (5008, 64, WIDE, 0), (5008, 512, WIDE, 0), (5008, 20000, WIDE, 0), (6000, 2048, WIDE, 0), (6000, 12000, WIDE, 0),
+    (8192, 64, WIDE, 0), (8192, 12000, WIDE, 0),
+])
+def test_single_jobs_take_the_measured_kernel(P, n, t, shape, wgs):
+    assert choose(P, n, t) == (shape, wgs)
+
+
+def test_minimum_piece_length_limits_cuts_not_the_kernels(P):
+    # a job of more units than compute units is never left to one kernel alone
+    for min_stages in (1, 4, 64, 1 << 20):
+        assert choose(P, 4096, 64, min_stages=min_stages)[0] == WIDE
+        assert choose(P, 2048, 512, min_stages=min_stages) == (TILE, 136)
+
+
+@pytest.mark.parametrize("jobs,n,t,shape", [(4, 512, 3000, REGION), (4, 512, 20000, TILE), (16, 256, 3000, REGION),
+                                            (16, 256, 12000, TILE), (16, 256, 32768, TILE), (2, 640, 12000, REGION),
+                                            (2, 640, 32768, TILE), (8, 1024, 4096, TILE), (8, 2048, 4096, WIDE)])
+def test_batches_take_the_measured_kernel(P, jobs, n, t, shape):
+    assert P.host_choose_batch((ctypes.c_int32 * jobs)(*[n] * jobs), (ctypes.c_int64 * jobs)(*[t] * jobs), jobs,
+                               256) == shape
