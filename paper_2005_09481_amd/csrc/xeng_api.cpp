@@ -51,7 +51,7 @@ hipError_t launch_dump_batch(const DumpDesc *d_jobs, const int32_t *d_job_of, in
                              hipStream_t stream);
 hipError_t launch_dump_corr(const DumpDesc &jd, const int32_t *sums, int n4, int64_t t, int32_t *other,
                             hipStream_t stream);
-hipError_t launch_clear_slot(int32_t *acc, int64_t n_i32, int32_t *bias, int32_t *base, int64_t n_bias, int64_t *count,
+hipError_t launch_clear_slot(int32_t *acc, int64_t n_i32, int32_t *bias, int64_t n_bias, int64_t *count,
                              hipStream_t stream);
 hipError_t launch_zero(int32_t *p, int64_t n_i32, hipStream_t stream);
 hipError_t launch_reference(const uint8_t *s, int64_t n_samples, int n, int64_t stride,
@@ -544,10 +544,9 @@ struct xeng_ctx {
     int64_t slot_i32 = 0;
     int32_t *d_acc = nullptr;    // n_slots accumulators, then n_slots bias arrays
     int32_t *d_bias = nullptr;   // per slot bias_i32(N): see JobDesc::bias
-    // per slot two buffers of bias_i32(N) (after the pre-sums): the biases
-    // as of the slot's last reset in the current one; a resetting export
-    // reads it and stores the present biases to the other
-    int32_t *d_base = nullptr;
+    // per slot, which of its two bases (BASE_I32) holds the biases as of its
+    // last reset; a resetting export reads it and stores the present biases
+    // to the other
     std::vector<uint8_t> base_cur;
     int64_t *d_count = nullptr;  // per slot: samples integrated, kept on the device for prepared batches
     int32_t *d_counts = nullptr; // XENG_COUNTS: per slot, int32 [count_i32]: samples per pair from flagged calls
@@ -646,25 +645,17 @@ JobDesc make_job(const xeng_ctx *c, int32_t slot, const uint8_t *d_samples, int6
     return jd;
 }
 
-// Buffer `which` (0, 1) of the slot's bases.
-int32_t *base_buf(const xeng_ctx *c, int32_t slot, int which)
-{
-    return c->d_base + ((int64_t)slot * 2 + which) * bias_i32(c->n);
-}
-
 DumpDesc make_dump(const xeng_ctx *c, int32_t slot, int32_t *out, bool reset)
 {
     DumpDesc d;
-    const int cur = c->base_cur[(size_t)slot];
     d.acc = c->d_acc + (int64_t)slot * c->slot_i32;
     d.out = out;
     d.bias = c->d_bias + (int64_t)slot * bias_i32(c->n);
-    d.base = base_buf(c, slot, cur);
-    d.base_next = base_buf(c, slot, 1 - cur);
     d.count = c->bound[(size_t)slot] > 0 ? c->d_count + slot : nullptr;
     d.n = c->n;
     d.nt = c->nt;
     d.reset = reset ? 1 : 0;
+    d.cur = c->base_cur[(size_t)slot];
     d.first_tile = 0;
     return d;
 }
@@ -1243,9 +1234,7 @@ int create_ctx(const xeng_config *cfg, hipStream_t stream, xeng_ctx **out)
         delete c;
         return map_err(e);
     }
-    // per slot two pre-sum buffers, then per slot two bases of its biases
-    const int64_t sums_i32 = (int64_t)cfg->n_slots * 4 * (((int64_t)cfg->n_inputs + 3) / 4 * 4);
-    const int64_t psum_i32 = sums_i32 + (int64_t)cfg->n_slots * 2 * bias_i32(cfg->n_inputs);
+    const int64_t psum_i32 = (int64_t)cfg->n_slots * 4 * (((int64_t)cfg->n_inputs + 3) / 4 * 4);
     if ((e = hipMalloc(&c->d_psum, (size_t)psum_i32 * 4)) != hipSuccess) {
         (void)hipFree(c->d_acc);
         (void)hipFree(c->d_count);
@@ -1253,7 +1242,6 @@ int create_ctx(const xeng_config *cfg, hipStream_t stream, xeng_ctx **out)
         return map_err(e);
     }
     c->d_bias = c->d_acc + (int64_t)cfg->n_slots * c->slot_i32;
-    c->d_base = c->d_psum + sums_i32;
     if (count_i32) c->d_counts = c->d_bias + (int64_t)cfg->n_slots * bias_i32(cfg->n_inputs);
     e = launch_zero(c->d_acc, bytes / 4, stream);
     if (e == hipSuccess) e = launch_zero(c->d_psum, psum_i32, stream);
@@ -1634,8 +1622,8 @@ int xeng_reset(xeng_ctx *ctx, int32_t slot, void *hip_stream)
     const int rc = refuse_capture(stream);
     if (rc != XENG_OK) return rc;
     hipError_t e = launch_clear_slot(ctx->d_acc + (int64_t)slot * ctx->slot_i32, ctx->slot_i32,
-                                     ctx->d_bias + (int64_t)slot * bias_i32(ctx->n), base_buf(ctx, slot, 0),
-                                     bias_i32(ctx->n), ctx->bound[(size_t)slot] > 0 ? ctx->d_count + slot : nullptr,
+                                     ctx->d_bias + (int64_t)slot * bias_i32(ctx->n), bias_i32(ctx->n),
+                                     ctx->bound[(size_t)slot] > 0 ? ctx->d_count + slot : nullptr,
                                      stream);
     if (e == hipSuccess) e = settle_presum(ctx, slot, stream, true);
     if (e != hipSuccess) return map_err(e);

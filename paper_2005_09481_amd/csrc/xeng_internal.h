@@ -52,6 +52,11 @@ inline int64_t slot_i32(int n) { return tri64(n_tiles_side(n)) * TILE_I32; }
 // Per-slot int32 per input, rounded up to 64: the imaginary biases the
 // signed int8 kernels add (see JobDesc::bias).
 inline int64_t bias_i32(int n) { return ((int64_t)n + 63) / 64 * 64; }
+// Block (3, 0) of a diagonal tile lies below the diagonal, where no kernel
+// stores sums.  It holds two bases of the biases of the tile's 128 inputs,
+// int32 [2][TILE] (see DumpDesc).
+constexpr int64_t BASE_I32 = 3 * BLKS * BLOCK_I32;   // from the tile's start
+static_assert(2 * TILE <= BLOCK_I32, "two bases fit the block");
 
 // Register sums of one piece: the general kernel's B operands carry 16x the
 // sample values, so its sums reach 16 * 128 * length (pieces below 2^20
@@ -151,23 +156,27 @@ struct GuardJob {
 };
 constexpr int ZERO_BYTES = 256;
 
-// One export: a slot's accumulators and biases (see JobDesc::bias; base as
-// of the slot's last reset) and the caller's output, [n(n+1)/2][2] int32.
-// A resetting export zeroes the words it exports, stores the present biases
-// to base_next and, for a slot of a live prepared batch, zeroes the slot's
-// device sample counter.
+// One export: a slot's accumulators and biases (see JobDesc::bias) and the
+// caller's output, [n(n+1)/2][2] int32.  The biases as of the slot's last reset
+// are base `cur` in the slot's diagonal tiles.  A resetting export zeroes the
+// words it exports, stores the present biases to the other base and, for a
+// slot of a live prepared batch, zeroes the slot's device sample counter.
 struct DumpDesc {
     int32_t *acc;
     int32_t *out;
     const int32_t *bias;
-    const int32_t *base;
-    int32_t *base_next;
     int64_t *count;      // null: no device counter to clear
     int32_t n;
     int32_t nt;
     int32_t reset;
+    int32_t cur;
     int32_t first_tile;  // batched exports: tiles of the jobs before this one
 };
+// Base `which` of the inputs of tile column t.
+__device__ inline int32_t *base_of(const DumpDesc &jd, int t, int which)
+{
+    return jd.acc + ((int64_t)t * jd.nt - (int64_t)t * (t - 1) / 2) * TILE_I32 + BASE_I32 + which * TILE;
+}
 
 // Most tiles one batched export launch takes (N of 65535 alone has 131328).
 constexpr int64_t DUMP_MAX_TILES = INT64_C(1) << 24;

@@ -423,10 +423,11 @@ template <bool NT> __device__ __forceinline__ void store_word(gw64 *p, uint64_t 
 // if the slot holds zeros, else read-modify-write with the loads of a row of
 // blocks issued together (one memory latency per row, not one per value).
 // NT: past the caches (JOB_STREAM; the four-wave kernel has no registers for
-// a second form).
+// a second form).  `b0`: the four-wave kernel's column blocks before it lie
+// below the diagonal.
 template <typename L, int SHIFT, bool F, bool NT>
-__device__ __forceinline__ void flush_owned(gw64 *tb, const Acc<L, F> &acc, int wa, int cb0, bool fresh, int a0 = 0,
-                                            int a1 = 2)
+__device__ __forceinline__ void flush_owned(gw64 *tb, const Acc<L, F> &acc, int wa, int cb0, bool fresh, int a0, int a1,
+                                            int b0)
 {
     constexpr int BW = L::BW;
 #pragma unroll
@@ -437,15 +438,19 @@ __device__ __forceinline__ void flush_owned(gw64 *tb, const Acc<L, F> &acc, int 
         for (int b = 0; b < BW; ++b) blk[b] = tb + ((2 * wa + a) * BLKS + cb0 + b) * BLOCK_W;
         uint64_t old[BW][16];
 #pragma unroll
-        for (int b = 0; b < BW; ++b)
+        for (int b = 0; b < BW; ++b) {
+            if (BW == 4 && b < b0) continue;
 #pragma unroll
             for (int r = 0; r < 16; ++r) old[b][r] = fresh ? 0 : load_word<NT>(blk[b] + r * 64);
+        }
 #pragma unroll
-        for (int b = 0; b < BW; ++b)
+        for (int b = 0; b < BW; ++b) {
+            if (BW == 4 && b < b0) continue;
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 store_word<NT>(blk[b] + r * 64, old[b][r] + pack_pair(acc_val<SHIFT>(acc.re[a][b][r]),
                                                                       acc_val<SHIFT>(acc.im[a][b][r])));
+        }
         __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -645,6 +650,9 @@ __device__ __forceinline__ void run_workgroup(const KernelArgs &args)
                     add_bias<L, SHIFT>(jd.bias, acc, jd.n, ti, wa, cb0, lane, a0, a1);
             const int64_t tile_idx = (int64_t)ti * jd.nt - (int64_t)ti * (ti - 1) / 2 + (tj - ti);
             gw64 *tb = (gw64 *)(jd.acc + tile_idx * TILE_I32) + lane;
+            // blocks below the diagonal of a wave that has both are not
+            // stored (their words hold the slot's bias bases, see BASE_I32)
+            const int b0 = L::BW == 4 && tj == ti ? 2 * wa : 0;
             if (atomic) {
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
@@ -652,18 +660,19 @@ __device__ __forceinline__ void run_workgroup(const KernelArgs &args)
                     for (int b = 0; b < L::BW; ++b) {
                         if (L::TG == 2 && (a < a0 || a >= a1)) continue;
                         if (diag && a == 1 && b == 0) continue;   // below the diagonal, never computed
+                        if (L::BW == 4 && b < b0) continue;
                         flush_atomic<SHIFT>(tb + ((2 * wa + a) * BLKS + cb0 + b) * BLOCK_W, acc.re[a][b],
                                             acc.im[a][b]);
                         // one block at a time: keeps the register file for the main loop
                         __builtin_amdgcn_sched_barrier(0);
                     }
             } else if (L::NW == 8 && (jd.flags & JOB_STREAM)) {
-                if (jd.flags & JOB_FRESH) flush_owned<L, SHIFT, F, true>(tb, acc, wa, cb0, true, a0, a1);
-                else flush_owned<L, SHIFT, F, true>(tb, acc, wa, cb0, false, a0, a1);
+                if (jd.flags & JOB_FRESH) flush_owned<L, SHIFT, F, true>(tb, acc, wa, cb0, true, a0, a1, b0);
+                else flush_owned<L, SHIFT, F, true>(tb, acc, wa, cb0, false, a0, a1, b0);
             } else if (jd.flags & JOB_FRESH) {
-                flush_owned<L, SHIFT, F, false>(tb, acc, wa, cb0, true, a0, a1);
+                flush_owned<L, SHIFT, F, false>(tb, acc, wa, cb0, true, a0, a1, b0);
             } else {
-                flush_owned<L, SHIFT, F, false>(tb, acc, wa, cb0, false, a0, a1);
+                flush_owned<L, SHIFT, F, false>(tb, acc, wa, cb0, false, a0, a1, b0);
             }
         }
     }

@@ -503,9 +503,10 @@ __global__ __launch_bounds__(256, 2) void xcorr_mfma(KernelArgs args)
 
         const bool re_low = (jd.flags & JOB_RE_LOW) != 0;
         // a wave whose 64 x 64 region lies wholly past the last input (rows
-        // or columns >= N, never exported) stages its share but multiplies
-        // and flushes nothing
-        const bool compute = TILE * ti + 64 * wa < jd.n && TILE * tj + 64 * wb < jd.n;
+        // or columns >= N) or below the diagonal is never exported: it stages
+        // its share but multiplies and flushes nothing (a diagonal tile's
+        // words down there hold the slot's bias bases, see BASE_I32)
+        const bool compute = TILE * ti + 64 * wa < jd.n && TILE * tj + 64 * wb < jd.n && !(ti == tj && wa > wb);
         if (role_a) {
             if (re_low) run_piece<ALIGNED, true, true, UNSIGNED, FP8>(acc, smem, pc, lane, wa, wb, wslot, compute);
             else run_piece<ALIGNED, true, false, UNSIGNED, FP8>(acc, smem, pc, lane, wa, wb, wslot, compute);
@@ -610,7 +611,7 @@ __device__ __forceinline__ void dump_part(const DumpDesc &jd, int ti, int tj, in
         // once per 128 inputs: the biases as of this reset, and the pre-sum
         // buffer the slot's next calls use
         const int j = TILE * ti + (int)threadIdx.x;
-        if (jd.reset && threadIdx.x < TILE && j < n) jd.base_next[j] = jd.bias[j];
+        if (jd.reset && threadIdx.x < TILE && j < n) base_of(jd, ti, 1 - jd.cur)[threadIdx.x] = jd.bias[j];
         if constexpr (CORR) {
             if (threadIdx.x < TILE && j < pc.n4) {
                 pc.other[j] = 0;
@@ -639,8 +640,9 @@ __device__ __forceinline__ void dump_part(const DumpDesc &jd, int ti, int tj, in
     // of the first, and its pair is not stored
     const bool two = j0 + 1 < n;
     const int j1 = two ? j0 + 1 : j0;
-    const uint32_t d0 = (uint32_t)jd.bias[j0] - (uint32_t)jd.base[j0];
-    const uint32_t d1 = (uint32_t)jd.bias[j1] - (uint32_t)jd.base[j1];
+    const int32_t *base = base_of(jd, tj, jd.cur);
+    const uint32_t d0 = (uint32_t)jd.bias[j0] - (uint32_t)base[j0 - TILE * tj];
+    const uint32_t d1 = (uint32_t)jd.bias[j1] - (uint32_t)base[j1 - TILE * tj];
     int64_t rj0 = 0, ij0 = 0, rj1 = 0, ij1 = 0;
     if constexpr (CORR) {
         rj0 = pc.sums[j0];
@@ -735,19 +737,15 @@ __global__ __launch_bounds__(256) void fill_zero(int4 *__restrict__ p, int64_t n
         p[k] = make_int4(0, 0, 0, 0);
 }
 
-// A slot cleared without an export: its accumulators, its biases with both
-// bases (n_bias int32 each, a multiple of 4), and, if given, its device
-// sample counter.
+// A slot cleared without an export: its accumulators (with the bases of its
+// biases), its biases (n_bias int32, a multiple of 4), and, if given, its
+// device sample counter.
 __global__ __launch_bounds__(256) void clear_slot(int4 *__restrict__ acc, int64_t n4, int4 *__restrict__ bias,
-                                                  int4 *__restrict__ base, int n_bias4, int64_t *count)
+                                                  int n_bias4, int64_t *count)
 {
     const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
     for (int64_t k = first; k < n4; k += step) acc[k] = make_int4(0, 0, 0, 0);
-    for (int64_t k = first; k < n_bias4; k += step) {
-        bias[k] = make_int4(0, 0, 0, 0);
-        base[k] = make_int4(0, 0, 0, 0);
-        base[n_bias4 + k] = make_int4(0, 0, 0, 0);
-    }
+    for (int64_t k = first; k < n_bias4; k += step) bias[k] = make_int4(0, 0, 0, 0);
     if (first == 0 && count != nullptr) *count = 0;
 }
 
@@ -911,14 +909,14 @@ hipError_t launch_zero(int32_t *p, int64_t n_i32, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_clear_slot(int32_t *acc, int64_t n_i32, int32_t *bias, int32_t *base, int64_t n_bias, int64_t *count,
+hipError_t launch_clear_slot(int32_t *acc, int64_t n_i32, int32_t *bias, int64_t n_bias, int64_t *count,
                              hipStream_t stream)
 {
     const int64_t n4 = n_i32 / 4;
     int64_t blocks = (n4 + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     hipLaunchKernelGGL(clear_slot, dim3((unsigned)blocks), dim3(256), 0, stream, reinterpret_cast<int4 *>(acc), n4,
-                       reinterpret_cast<int4 *>(bias), reinterpret_cast<int4 *>(base), (int)(n_bias / 4), count);
+                       reinterpret_cast<int4 *>(bias), (int)(n_bias / 4), count);
     return hipGetLastError();
 }
 

@@ -136,3 +136,21 @@ assert chunks(flagged, 0) == 1 and F.fake_pool_bytes(1) == 128 * 2048      # (be
 assert chunks(flagged, 16 * 2048) == 1 and F.fake_pool_bytes(1) == 16 * 2048
 assert chunks(flagged, 16 * 1024) == 2
 """)
+
+
+def test_a_context_allocates_what_is_counted(run):
+    # accumulators and biases (xeng_slot_bytes, the memory budget), beside them
+    # the pre-sums (16 bytes per input, N rounded up to 4) and a counter per
+    # slot, with XENG_COUNTS the pair counts; nothing else per slot
+    run(r"""
+create(1)                                    # (the device's own set-up)
+for n in (1, 64, 100, 128, 130, 1000, 2048):
+    for slots in (1, 2, 33):
+        for flags in (0, X.XENG_COUNTS):
+            before = F.fake_device_bytes()
+            counts = -(-X.tri(n) // 4) * 16 if flags else 0
+            c = create(n, slots, flags, slots * (X.slot_bytes(n) + counts))
+            got = F.fake_device_bytes() - before
+            assert got == slots * (X.slot_bytes(n) + 16 * -(-n // 4) * 4 + counts) + 16 * -(-slots // 2), (n, slots, got)
+            assert L.xeng_destroy(c) == 0 and F.fake_device_bytes() == before
+""")
