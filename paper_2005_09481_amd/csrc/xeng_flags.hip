@@ -178,11 +178,15 @@ __global__ __launch_bounds__(256) void sk_flags_bytes(const uint8_t *__restrict_
 //
 // Bound by HBM: 2 N bytes a row.  A workgroup takes consecutive rows, 2^xs
 // threads side by side on a row, a thread 16 bytes of R rows (all loads before
-// the first store).  N = 1000, T = 32768: 16.0 us (a dword per thread, a row
-// per workgroup) -> 12.5 us with four rows (13.1 with two, 13.8 with one); with
-// flags, N = 2048, T = 32768 (134 MB) 21.0 us with two (22.0 with one, 22.3
-// with four, 20.6 for the aligned-only form it replaces), N = 500, T = 8192
-// 10.1 -> 9.7 us.
+// the first store).  Several rows a thread where that leaves COPY_WGS
+// workgroups, eight per compute unit: N = 1000, T = 32768 16.0 us (a dword per
+// thread, a row per workgroup) -> 12.5 us with four rows (13.1 with two, 13.8
+// with one); with flags, N = 2048, T = 32768 (134 MB) 21.0 us with two (22.0
+// with one, 22.3 with four, 20.6 for the aligned-only form it replaces), N =
+// 500, T = 8192 10.1 -> 9.7 us.  One row a thread below that, where few
+// workgroups wait on one row after the other: a batch of 16 jobs of N = 1000,
+// T = 256 131 us (four rows 155), T = 8192 313 (336); N = 300, T = 16384 141
+// (159).
 __device__ __forceinline__ uint32_t mask_word(uint32_t x, uint32_t f)
 {
     // bytes of f that are nonzero -> 0xFF
@@ -191,15 +195,14 @@ __device__ __forceinline__ uint32_t mask_word(uint32_t x, uint32_t f)
     return (x & ~m) | (0x88888888u & m);
 }
 
-template <bool MASK> constexpr int COPY_ROWS = MASK ? 2 : 4;
+constexpr int COPY_WGS = 2048;
 
-template <bool MASK>
+template <bool MASK, int R>
 __global__ __launch_bounds__(256) void copy_rows(const uint8_t *__restrict__ src, int64_t stride, int n, int64_t rows,
                                                  uint8_t *__restrict__ dst, int64_t pitch, int xs,
                                                  const uint8_t *__restrict__ flags, int block_len, int64_t t_first)
 {
     const int x = threadIdx.x & ((1 << xs) - 1), y = threadIdx.x >> xs, ny = 256 >> xs;
-    constexpr int R = COPY_ROWS<MASK>;
     for (int64_t t0 = (int64_t)blockIdx.x * ny * R + y; t0 < rows; t0 += (int64_t)gridDim.x * ny * R)
         for (int c = 16 * x; c < n; c += 16 << xs) {
             row16 v[R], f[R];
@@ -357,14 +360,16 @@ hipError_t launch_copy_rows(const uint8_t *src, int64_t stride, int n, int64_t r
     const int per_row = (n + 15) / 16;
     int xs = 0;
     while (xs < 8 && (1 << xs) < per_row) ++xs;
-    const int64_t per_wg = (int64_t)(256 >> xs) * (flags ? COPY_ROWS<true> : COPY_ROWS<false>);
-    const int64_t blocks = std::min<int64_t>(65535, (rows + per_wg - 1) / per_wg);
-    if (flags)
-        hipLaunchKernelGGL(copy_rows<true>, dim3((unsigned)blocks), dim3(256), 0, stream, src, stride, n, rows, dst,
-                           pitch, xs, flags, block_len, t_first);
-    else
-        hipLaunchKernelGGL(copy_rows<false>, dim3((unsigned)blocks), dim3(256), 0, stream, src, stride, n, rows, dst,
-                           pitch, xs, flags, block_len, t_first);
+    const int64_t one = (rows + (256 >> xs) - 1) / (256 >> xs);   // workgroups of one row a thread
+    auto go = [&](auto kernel, int r) {
+        const int64_t blocks = std::min<int64_t>(65535, (one + r - 1) / r);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream, src, stride, n, rows, dst, pitch, xs,
+                           flags, block_len, t_first);
+    };
+    if (flags && one >= 2 * COPY_WGS) go(copy_rows<true, 2>, 2);
+    else if (flags) go(copy_rows<true, 1>, 1);
+    else if (one >= 4 * COPY_WGS) go(copy_rows<false, 4>, 4);
+    else go(copy_rows<false, 1>, 1);
     return hipGetLastError();
 }
 

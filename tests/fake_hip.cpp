@@ -16,6 +16,8 @@ namespace {
 std::map<void *, size_t> allocs;    // hipMalloc
 std::vector<size_t> pool_allocs;    // hipMallocFromPoolAsync, in call order
 std::vector<std::string> kernels;   // in launch order
+std::vector<int64_t> grids;         // their workgroups
+dim3 pushed_grid, pushed_block;     // of the launch being configured
 int fail_records = 0;               // the next event records fail
 int stream_syncs = 0;
 unsigned char symbol[1 << 20];
@@ -38,12 +40,19 @@ int64_t fake_launches(const char *part)
     for (const auto &k : kernels) n += k.find(part) != std::string::npos;
     return n;
 }
+int64_t fake_workgroups(const char *part)   // of the last such launch
+{
+    for (size_t k = kernels.size(); k-- > 0;)
+        if (kernels[k].find(part) != std::string::npos) return grids[k];
+    return -1;
+}
 void fake_fail_records(int n) { fail_records = n; }
 int fake_stream_syncs() { return stream_syncs; }
 void fake_clear()
 {
     pool_allocs.clear();
     kernels.clear();
+    grids.clear();
     stream_syncs = 0;
 }
 
@@ -113,12 +122,25 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s)
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return ++stream_syncs, hipSuccess; }
 
-hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
-hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { return hipSuccess; }
-hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **, size_t, hipStream_t)
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t)
+{
+    pushed_grid = grid;
+    pushed_block = block;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *stream)
+{
+    *grid = pushed_grid;
+    *block = pushed_block;
+    *lds = 0;
+    *stream = nullptr;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **, size_t, hipStream_t)
 {
     Dl_info info;
     kernels.push_back(dladdr(f, &info) && info.dli_sname ? info.dli_sname : "?");
+    grids.push_back((int64_t)grid.x * grid.y * grid.z);
     return hipSuccess;
 }
 }

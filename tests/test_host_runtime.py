@@ -14,10 +14,10 @@ PRELUDE = r"""
 import ctypes, sys
 sys.path.insert(0, sys.argv[1])
 F = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)
-for f in ("fake_device_bytes", "fake_pool_allocs", "fake_pool_bytes", "fake_launches"):
+for f in ("fake_device_bytes", "fake_pool_allocs", "fake_pool_bytes", "fake_launches", "fake_workgroups"):
     getattr(F, f).restype = ctypes.c_int64
 F.fake_pool_bytes.argtypes = [ctypes.c_int64]
-F.fake_launches.argtypes = [ctypes.c_char_p]
+F.fake_launches.argtypes = F.fake_workgroups.argtypes = [ctypes.c_char_p]
 from paper_2005_09481_amd import xeng as X
 L = X.lib()
 P = 1 << 20          # a sample address: never read, kernels do nothing
@@ -153,4 +153,17 @@ for n in (1, 64, 100, 128, 130, 1000, 2048):
             got = F.fake_device_bytes() - before
             assert got == slots * (X.slot_bytes(n) + 16 * -(-n // 4) * 4 + counts) + 16 * -(-slots // 2), (n, slots, got)
             assert L.xeng_destroy(c) == 0 and F.fake_device_bytes() == before
+""")
+
+
+def test_short_copies_fill_the_chip(run):
+    # one row a thread until several leave eight workgroups per compute unit
+    run(r"""
+c, f = create(1000), create(1000, 1, X.XENG_COUNTS)       # four rows side by side in a workgroup
+for t, wgs in ((1, 1), (256, 64), (8192, 2048), (32764, 8191), (32768, 2048), (40000, 2500)):
+    assert L.xeng_correlate(c, 0, P, t, 1000, None) == 0
+    assert F.fake_workgroups(b"copy_rows") == wgs, (t, F.fake_workgroups(b"copy_rows"))
+for t, wgs in ((64, 16), (16380, 4095), (16384, 2048)):
+    assert L.xeng_correlate_flagged(f, 0, P, t, 1000, P, 64, None) == 0
+    assert F.fake_workgroups(b"copy_rows") == wgs, (t, F.fake_workgroups(b"copy_rows"))
 """)
