@@ -154,7 +154,7 @@ __global__ __launch_bounds__(1024) void sk_flags_vec(const uint8_t *__restrict__
     }
 }
 
-// N < 16: one thread per (input, block), byte loads.
+// One thread per (input, block), byte loads.
 __global__ __launch_bounds__(256) void sk_flags_bytes(const uint8_t *__restrict__ s, int64_t n_samples, int n,
                                                       int64_t stride, uint32_t re_low, int block_len, int64_t lo_num,
                                                       int64_t hi_num, int64_t den, uint8_t *__restrict__ flags)
@@ -330,7 +330,12 @@ hipError_t launch_sk_flags(const uint8_t *s, int64_t n_samples, int n, int64_t s
 {
     const int64_t nb = (n_samples + block_len - 1) / block_len;
     if (nb <= 0) return hipSuccess;
-    if (n < 16) {
+    // The byte form for N < 16 and for blocks too small for a workgroup of
+    // the other: its LDS sums and barriers then cost more than the block's
+    // samples.  T = 32768 (16384 for two), byte form / other, us: N = 64, blocks
+    // of 4 6.6 / 20, of 16 6.6 / 7.5, of 32 6.7 / 7.0; N = 500, of 4 16 / 20, of
+    // 8 14.0 / 12.3; N = 1000, of 2 22 / 29, of 4 33 / 29; N = 4096, of 2 84 / 92.
+    if (n < 16 || block_len <= 2 || (block_len <= 16 && n * block_len < 3000)) {
         hipLaunchKernelGGL(sk_flags_bytes, dim3((unsigned)((n + 255) / 256), (unsigned)nb), dim3(256), 0, stream, s,
                            n_samples, n, stride, re_low, block_len, lo_num, hi_num, den, flags);
         return hipGetLastError();
