@@ -48,7 +48,7 @@ hipError_t launch_correlate_narrow(const KernelArgs &a, int grid, hipStream_t st
 hipError_t init_dma_kernel();
 hipError_t launch_dump(const DumpDesc &jd, hipStream_t stream);
 hipError_t launch_dump_batch(const DumpDesc *d_jobs, const int32_t *d_job_of, int tiles, int64_t total_tiles,
-                             hipStream_t stream);
+                             int64_t reset_tiles, hipStream_t stream);
 hipError_t launch_dump_corr(const DumpDesc &jd, const int32_t *sums, int n4, int64_t t, int32_t *other,
                             hipStream_t stream);
 hipError_t launch_clear_slot(int32_t *acc, int64_t n_i32, int32_t *bias, int64_t n_bias, int64_t *count,
@@ -1573,7 +1573,7 @@ int xeng_dump_batch(const xeng_dump_job *jobs, int32_t n_jobs, void *hip_stream)
     }
     for (int32_t k0 = 0; k0 < n_jobs;) {
         // as many jobs as one launch's grid takes
-        int64_t total = 0;
+        int64_t total = 0, reset_tiles = 0;
         int32_t m = 0;
         bool same = true;
         for (; k0 + m < n_jobs; ++m) {
@@ -1582,6 +1582,7 @@ int xeng_dump_batch(const xeng_dump_job *jobs, int32_t n_jobs, void *hip_stream)
             if (m > 0 && total + tiles > DUMP_MAX_TILES) break;
             d.first_tile = (int32_t)total;
             total += tiles;
+            if (d.reset) reset_tiles += tiles;
             same = same && d.nt == descs[(size_t)k0].nt;
         }
         // [descriptors | the job of every tile, where their tiles differ]
@@ -1598,7 +1599,7 @@ int xeng_dump_batch(const xeng_dump_job *jobs, int32_t n_jobs, void *hip_stream)
         if (e == hipSuccess) {
             e = launch_dump_batch(reinterpret_cast<const DumpDesc *>(tb->d),
                                   same ? nullptr : reinterpret_cast<const int32_t *>(tb->d + b_desc),
-                                  (int)tri64(descs[(size_t)k0].nt), total, stream);
+                                  (int)tri64(descs[(size_t)k0].nt), total, reset_tiles, stream);
             // a chunk's slots are reset as its launch is queued, whatever
             // becomes of the calls behind it
             if (e == hipSuccess)

@@ -45,6 +45,8 @@
 // pieces stay below 2^19 samples (int32 register sums).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "xeng_internal.h"
 
 namespace xeng {
@@ -574,9 +576,20 @@ __global__ __launch_bounds__(256, 2) void xcorr_mfma(KernelArgs args)
 // and clearing every tile whole took 44 us + 4.5 for the diagonals; 64
 // sub-arrays of N 256 to 2048 136 us, where a grid sized for the largest
 // job's tiles took 202.
-constexpr int DUMP_ROWS = 8;
+//
+// PAST: what a resetting export does past the caches once its launch's
+// accumulators outgrow them (see STREAM_BYTES): from there on the output
+// (1), which would only push out the words that the next integration adds to;
+// from DUMP_PAST_BYTES on its reads and clears too, four rows per workgroup
+// (2).  us of one correlation of 1024 samples and the exports, form 0 / 1 / 2: 12
+// slots of N = 2048 236 / 227 / 243, 32 581 / 576 / 602, 64 (1 GiB) 1136 / 1134
+// / 1119; 8 of N = 4096 580 / 557 / 574.  The exports alone: 12 slots 120 / 80 /
+// 113, 32 322 / 326 / 294, 64 649 / 653 / 592.  Below, form 0: 6 slots 44 / 61
+// (2).  Exports that keep the sums: 64 slots 374 / 383 / 387.
+constexpr int64_t DUMP_PAST_BYTES = 4 * STREAM_BYTES;
+template <int PAST> constexpr int DUMP_ROWS = PAST == 2 ? 4 : 8;
 constexpr int DUMP_WAVES = 4;
-constexpr int DUMP_PARTS = TILE / DUMP_ROWS;   // workgroups per tile
+template <int PAST> constexpr int DUMP_PARTS = TILE / DUMP_ROWS<PAST>;   // workgroups per tile
 
 // A pending unsigned-form correction (CORR; see presum_correct): per
 // input, SR at sums[i] and SI at sums[n4 + i] over the t samples that form
@@ -598,15 +611,40 @@ __device__ __forceinline__ uint64_t corr_word(int64_t ri, int64_t ii, int64_t rj
     return ((uint64_t)d_im << 32) + (uint64_t)d_re;
 }
 
+typedef int dv4i __attribute__((ext_vector_type(4)));
 typedef int dv4i_u __attribute__((ext_vector_type(4), aligned(8)));
+typedef int dv2i __attribute__((ext_vector_type(2)));
+
+// A slot's words (two pairs); two output pairs, one pair.
+template <int PAST> __device__ __forceinline__ dv4i load_words(const dv4i *p)
+{
+    if constexpr (PAST == 2) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <int PAST> __device__ __forceinline__ void store_words(dv4i *p, dv4i v)
+{
+    if constexpr (PAST == 2) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+template <int PAST> __device__ __forceinline__ void store_two(int32_t *o, dv4i_u v)
+{
+    if constexpr (PAST > 0) __builtin_nontemporal_store(v, reinterpret_cast<dv4i_u *>(o));
+    else *reinterpret_cast<dv4i_u *>(o) = v;
+}
+template <int PAST> __device__ __forceinline__ void store_one(int32_t *o, dv2i v)
+{
+    if constexpr (PAST > 0) __builtin_nontemporal_store(v, reinterpret_cast<dv2i *>(o));
+    else *reinterpret_cast<dv2i *>(o) = v;
+}
 
 // Part `part` of tile (ti, tj) of one export.
-template <bool CORR>
+template <bool CORR, int PAST>
 __device__ __forceinline__ void dump_part(const DumpDesc &jd, int ti, int tj, int part, const PendingCorr &pc)
 {
+    constexpr int ROWS = DUMP_ROWS<PAST>;
     const int c = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = jd.n, nt = jd.nt;
-    const int i0 = TILE * ti + DUMP_ROWS * part;   // first row of the part
+    const int i0 = TILE * ti + ROWS * part;   // first row of the part
     if (ti == tj && part == 0) {
         // once per 128 inputs: the biases as of this reset, and the pre-sum
         // buffer the slot's next calls use
@@ -622,19 +660,19 @@ __device__ __forceinline__ void dump_part(const DumpDesc &jd, int ti, int tj, in
     }
     const int cb = c >> 4, cj0 = 2 * (c & 15);
     const int j0 = TILE * tj + BLK * cb + cj0;
-    const int ca = (DUMP_ROWS * part) >> 5;        // block row
+    const int ca = (ROWS * part) >> 5;        // block row
     // column block below the diagonal, or past the last input
     if (i0 >= n || j0 >= n || (ti == tj && cb < ca)) return;
     const int64_t tile = (int64_t)ti * nt - (int64_t)ti * (ti - 1) / 2 + (tj - ti);
     uint64_t *blk = reinterpret_cast<uint64_t *>(jd.acc) + tile * TILE_W + (ca * BLKS + cb) * BLOCK_W + cj0;
-    constexpr int PER = DUMP_ROWS / DUMP_WAVES;    // rows per wave
-    int4 w[PER];
-    int4 *pw[PER];
+    constexpr int PER = ROWS / DUMP_WAVES;    // rows per wave
+    dv4i w[PER];
+    dv4i *pw[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const int ra = (DUMP_ROWS * part + wave + DUMP_WAVES * k) & (BLK - 1);   // row in the block
-        pw[k] = reinterpret_cast<int4 *>(blk + (4 * (ra >> 3) + (ra & 3)) * 64 + 32 * ((ra >> 2) & 1));
-        w[k] = *pw[k];
+        const int ra = (ROWS * part + wave + DUMP_WAVES * k) & (BLK - 1);   // row in the block
+        pw[k] = reinterpret_cast<dv4i *>(blk + (4 * (ra >> 3) + (ra & 3)) * 64 + 32 * ((ra >> 2) & 1));
+        w[k] = load_words<PAST>(pw[k]);
     }
     // the second column may lie past the last input: its bias is then that
     // of the first, and its pair is not stored
@@ -654,7 +692,7 @@ __device__ __forceinline__ void dump_part(const DumpDesc &jd, int ti, int tj, in
     for (int k = 0; k < PER; ++k) {
         const int i = i0 + wave + DUMP_WAVES * k;
         if (i >= n) continue;
-        if (jd.reset) *pw[k] = make_int4(0, 0, 0, 0);
+        if (jd.reset) store_words<PAST>(pw[k], dv4i{0, 0, 0, 0});
         uint64_t w0 = (uint64_t)(uint32_t)w[k].x | ((uint64_t)(uint32_t)w[k].y << 32);
         uint64_t w1 = (uint64_t)(uint32_t)w[k].z | ((uint64_t)(uint32_t)w[k].w << 32);
         if constexpr (CORR) {
@@ -666,37 +704,38 @@ __device__ __forceinline__ void dump_part(const DumpDesc &jd, int ti, int tj, in
         const int b_re = pair_re(w1), b_im = (int32_t)((uint32_t)pair_im(w1) - d1);
         int32_t *o = jd.out + 2 * ((int64_t)i * n - (int64_t)i * (i - 1) / 2 + (j0 - i));
         if (j0 >= i && two)
-            *reinterpret_cast<dv4i_u *>(o) = dv4i_u{a_re, a_im, b_re, b_im};
+            store_two<PAST>(o, dv4i_u{a_re, a_im, b_re, b_im});
         else if (j0 >= i)
-            *reinterpret_cast<int2 *>(o) = make_int2(a_re, a_im);
+            store_one<PAST>(o, dv2i{a_re, a_im});
         else if (j0 + 1 >= i && two)
-            *reinterpret_cast<int2 *>(o + 2) = make_int2(b_re, b_im);
+            store_one<PAST>(o + 2, dv2i{b_re, b_im});
     }
 }
 
 // One slot's export: workgroup x is part x % DUMP_PARTS of tile
 // x / DUMP_PARTS of the triangle.
-template <bool CORR>
+template <bool CORR, int PAST>
 __global__ __launch_bounds__(64 * DUMP_WAVES) void vis_dump(DumpDesc jd, PendingCorr pc)
 {
     int ti, tj;
-    tile_of((int)(blockIdx.x / DUMP_PARTS), jd.nt, ti, tj);
-    dump_part<CORR>(jd, ti, tj, (int)(blockIdx.x % DUMP_PARTS), pc);
+    tile_of((int)(blockIdx.x / DUMP_PARTS<PAST>), jd.nt, ti, tj);
+    dump_part<CORR, PAST>(jd, ti, tj, (int)(blockIdx.x % DUMP_PARTS<PAST>), pc);
 }
 
 // Batched export: the jobs' tiles one after another, tile g being tile
 // g - first_tile of its job.  The job of a tile comes from the table
 // `job_of` (one entry per tile), or, with no table, every job having
 // `tiles` of them, by division.
+template <int PAST>
 __global__ __launch_bounds__(64 * DUMP_WAVES) void vis_dump_batch(const DumpDesc *__restrict__ jobs,
                                                                   const int32_t *__restrict__ job_of, int tiles)
 {
-    const int g = (int)(blockIdx.x / DUMP_PARTS);
+    const int g = (int)(blockIdx.x / DUMP_PARTS<PAST>);
     const int k = __builtin_amdgcn_readfirstlane(job_of ? job_of[g] : g / tiles);
     const DumpDesc jd = jobs[k];
     int ti, tj;
     tile_of(g - jd.first_tile, jd.nt, ti, tj);
-    dump_part<false>(jd, ti, tj, (int)(blockIdx.x % DUMP_PARTS), PendingCorr{nullptr, nullptr, 0, 0});
+    dump_part<false, PAST>(jd, ti, tj, (int)(blockIdx.x % DUMP_PARTS<PAST>), PendingCorr{nullptr, nullptr, 0, 0});
 }
 
 // Ingest of host-sourced frames (the streaming server): up to GATHER_MAX
@@ -846,36 +885,54 @@ hipError_t launch_correlate_unsigned(const KernelArgs &a, int grid, bool aligned
     return hipGetLastError();
 }
 
-hipError_t launch_dump(const DumpDesc &jd, hipStream_t stream)
+// The form (PAST) of a launch whose resetting exports hold this many tiles:
+// go(std::integral_constant<int, PAST>).
+template <typename Go> static hipError_t with_dump_form(int64_t reset_tiles, Go go)
 {
-    const int64_t parts = (int64_t)jd.nt * (jd.nt + 1) / 2 * DUMP_PARTS;
-    hipLaunchKernelGGL(vis_dump<false>, dim3((unsigned)parts), dim3(64 * DUMP_WAVES), 0, stream, jd,
-                       PendingCorr{nullptr, nullptr, 0, 0});
+    const int64_t bytes = reset_tiles * TILE_I32 * (int64_t)sizeof(int32_t);
+    if (bytes >= DUMP_PAST_BYTES) go(std::integral_constant<int, 2>());
+    else if (bytes >= STREAM_BYTES) go(std::integral_constant<int, 1>());
+    else go(std::integral_constant<int, 0>());
     return hipGetLastError();
 }
 
-// An export that also applies a slot's pending unsigned-form correction
-// (`sums`: its SR, SI over `t` samples, n4 apart) and clears `other`.
+hipError_t launch_dump(const DumpDesc &jd, hipStream_t stream)
+{
+    const int64_t tiles = (int64_t)jd.nt * (jd.nt + 1) / 2;
+    return with_dump_form(jd.reset ? tiles : 0, [&](auto form) {
+        constexpr int PAST = decltype(form)::value;
+        hipLaunchKernelGGL((vis_dump<false, PAST>), dim3((unsigned)(tiles * DUMP_PARTS<PAST>)), dim3(64 * DUMP_WAVES), 0,
+                           stream, jd, PendingCorr{nullptr, nullptr, 0, 0});
+    });
+}
+
+// A resetting export that also applies a slot's pending unsigned-form
+// correction (`sums`: its SR, SI over `t` samples, n4 apart) and clears
+// `other`.
 hipError_t launch_dump_corr(const DumpDesc &jd, const int32_t *sums, int n4, int64_t t, int32_t *other,
                             hipStream_t stream)
 {
-    const int64_t parts = (int64_t)jd.nt * (jd.nt + 1) / 2 * DUMP_PARTS;
-    hipLaunchKernelGGL(vis_dump<true>, dim3((unsigned)parts), dim3(64 * DUMP_WAVES), 0, stream, jd,
-                       PendingCorr{sums, other, n4, t});
-    return hipGetLastError();
+    const int64_t tiles = (int64_t)jd.nt * (jd.nt + 1) / 2;
+    return with_dump_form(tiles, [&](auto form) {
+        constexpr int PAST = decltype(form)::value;
+        hipLaunchKernelGGL((vis_dump<true, PAST>), dim3((unsigned)(tiles * DUMP_PARTS<PAST>)), dim3(64 * DUMP_WAVES), 0,
+                           stream, jd, PendingCorr{sums, other, n4, t});
+    });
 }
 
 // `d_jobs`: descriptors in device memory, `total_tiles` tiles in all (at most
-// DUMP_MAX_TILES); d_job_of: the job of each tile, or null where every job
-// has `tiles`.
+// DUMP_MAX_TILES), `reset_tiles` of them of resetting exports; d_job_of: the
+// job of each tile, or null where every job has `tiles`.
 hipError_t launch_dump_batch(const DumpDesc *d_jobs, const int32_t *d_job_of, int tiles, int64_t total_tiles,
-                             hipStream_t stream)
+                             int64_t reset_tiles, hipStream_t stream)
 {
-    static_assert(DUMP_MAX_TILES * DUMP_PARTS < (INT64_C(1) << 31), "a launch's workgroups fit its grid");
+    static_assert(DUMP_MAX_TILES * DUMP_PARTS<2> < (INT64_C(1) << 31), "a launch's workgroups fit its grid");
     if (total_tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(vis_dump_batch, dim3((unsigned)(total_tiles * DUMP_PARTS)), dim3(64 * DUMP_WAVES), 0, stream,
-                       d_jobs, d_job_of, tiles);
-    return hipGetLastError();
+    return with_dump_form(reset_tiles, [&](auto form) {
+        constexpr int PAST = decltype(form)::value;
+        hipLaunchKernelGGL(vis_dump_batch<PAST>, dim3((unsigned)(total_tiles * DUMP_PARTS<PAST>)), dim3(64 * DUMP_WAVES),
+                           0, stream, d_jobs, d_job_of, tiles);
+    });
 }
 
 // `n` frames of `bytes` each (a multiple of 16, below 2^31), every address

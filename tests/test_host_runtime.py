@@ -181,3 +181,28 @@ for n, block, want in ((15, 1024, "bytes"), (16, 16, "bytes"), (16, 17, "vec"), 
                        (1000, 2, "bytes"), (1000, 3, "vec"), (4096, 2, "bytes"), (4096, 4, "vec"), (2048, 256, "vec")):
     assert form(n, block) == want, (n, block)
 """)
+
+
+def test_large_resetting_exports_go_past_the_caches(run):
+    # from 192 MiB of accumulators that a launch resets (17 MiB a slot of N =
+    # 2048) their output does, from 768 MiB on all they touch
+    run(r"""
+c = create(2048, 46)
+def form(call, name):
+    F.fake_clear()
+    assert call() == 0
+    got = [f for f in range(3) if F.fake_launches(b"%sLi%dE" % (name, f))]
+    assert len(got) == 1
+    return got[0]
+def batch(resets):
+    return form(lambda: L.xeng_dump_batch(*dumps(*[(c, k, r) for k, r in enumerate(resets)])), b"vis_dump_batchI")
+assert [batch([1] * k) for k in (1, 11, 12, 45, 46)] == [0, 0, 1, 1, 2]
+assert batch([1] * 11 + [0] * 10) == 0 and batch([0] * 46) == 0 and batch([1] * 12 + [0] * 34) == 1
+big = create(8192)          # 260 MiB
+one = lambda reset: lambda: L.xeng_dump(big, 0, P, reset, None)
+assert form(one(1), b"vis_dumpILb0E") == 1 and form(one(0), b"vis_dumpILb0E") == 0
+assert L.xeng_correlate_presum(big, 0, P, 64, 8192, None) == 0
+assert form(one(1), b"vis_dumpILb1E") == 1
+small = create(64)
+assert form(lambda: L.xeng_dump(small, 0, P, 1, None), b"vis_dumpILb0E") == 0
+""")
