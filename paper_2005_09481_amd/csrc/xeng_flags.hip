@@ -332,10 +332,13 @@ hipError_t launch_sk_flags(const uint8_t *s, int64_t n_samples, int n, int64_t s
     if (nb <= 0) return hipSuccess;
     // The byte form for N < 16 and for blocks too small for a workgroup of
     // the other: its LDS sums and barriers then cost more than the block's
-    // samples.  T = 32768 (16384 for two), byte form / other, us: N = 64, blocks
-    // of 4 6.6 / 20, of 16 6.6 / 7.5, of 32 6.7 / 7.0; N = 500, of 4 16 / 20, of
-    // 8 14.0 / 12.3; N = 1000, of 2 22 / 29, of 4 33 / 29; N = 4096, of 2 84 / 92.
-    if (n < 16 || block_len <= 2 || (block_len <= 16 && n * block_len < 3000)) {
+    // samples.  Byte form / other, us: N = 1000, T = 16384, blocks of two 22 /
+    // 29; T = 32768, N = 64, of 4 6.6 / 20, of 16 6.6 / 7.5; N = 500, of 4 16 /
+    // 20, of 8 14.0 / 12.3; N = 1000, of 4 33 / 29; and for blocks up to eight
+    // while the samples are few: N = 1000, T = 8192, of 3 8.3 / 13.4, of 8 6.5 /
+    // 8.9, of 16 6.5 / 7.6; N = 2048, T = 8192, of 8 9.5 / 10.9, T = 32768 52 / 30.
+    if (n < 16 || block_len <= 2 || (block_len <= 16 && n * block_len < 3000) ||
+        (block_len <= 8 && n * n_samples <= 1 << 24)) {
         hipLaunchKernelGGL(sk_flags_bytes, dim3((unsigned)((n + 255) / 256), (unsigned)nb), dim3(256), 0, stream, s,
                            n_samples, n, stride, re_low, block_len, lo_num, hi_num, den, flags);
         return hipGetLastError();

@@ -171,15 +171,17 @@ for t, wgs in ((64, 16), (16380, 4095), (16384, 2048)):
 
 def test_small_flag_blocks_take_the_byte_form(run):
     run(r"""
-def form(n, block):
+def form(n, block, t):
     F.fake_clear()
     cfg = X._RfiConfig(block, 1000, 625, 1375, 0)
-    assert L.xeng_rfi_flags(P, 4096, n, n, 0, ctypes.byref(cfg), P, None) == 0
+    assert L.xeng_rfi_flags(P, t, n, n, 0, ctypes.byref(cfg), P, None) == 0
     return "bytes" if F.fake_launches(b"sk_flags_bytes") else "vec" if F.fake_launches(b"sk_flags_vec") else None
-for n, block, want in ((15, 1024, "bytes"), (16, 16, "bytes"), (16, 17, "vec"), (64, 4, "bytes"), (64, 16, "bytes"),
-                       (64, 32, "vec"), (500, 4, "bytes"), (500, 8, "vec"), (749, 4, "bytes"), (750, 4, "vec"),
-                       (1000, 2, "bytes"), (1000, 3, "vec"), (4096, 2, "bytes"), (4096, 4, "vec"), (2048, 256, "vec")):
-    assert form(n, block) == want, (n, block)
+for n, block, t, want in ((15, 1024, 4096, "bytes"), (16, 16, 4096, "bytes"), (16, 17, 4096, "vec"),
+                          (64, 16, 65536, "bytes"), (64, 32, 4096, "vec"), (749, 4, 32768, "bytes"),
+                          (750, 4, 32768, "vec"), (1000, 2, 65536, "bytes"), (1000, 3, 32768, "vec"),
+                          (1000, 8, 8192, "bytes"), (1000, 9, 8192, "vec"), (2048, 8, 8192, "bytes"),
+                          (2048, 8, 8193, "vec"), (2048, 256, 256, "vec")):
+    assert form(n, block, t) == want, (n, block, t)
 """)
 
 
