@@ -450,9 +450,11 @@ typedef struct {
  * Autotuner (Sec. 2.3: each GPU processes its share of frequency channels;
  * what runs fastest depends on their N and T).  Times every candidate launch
  * configuration on these jobs, `iters` launches each on hip_stream: the
- * kernel (the eight- or four-wave DMA kernel, or the general kernel with one
- * or two workgroups per CU), the minimum piece length and, for a single
- * job, the work order.  The trials read the jobs' samples and accumulate
+ * kernel (the wide, tile and region DMA kernels, which best->kernel all
+ * reports as XENG_KERNEL_AUTO, the four-wave one, or the general kernel with
+ * one or two workgroups per CU), the minimum piece length and, for a single
+ * job, the work order.  The DMA kernel measured fastest then takes the place
+ * of the modelled one for the class.  The trials read the jobs' samples and accumulate
  * into accumulators the library allocates for the call and frees after:
  * the jobs' slots, their contents and their sample counts are left as they
  * were.  The fastest configuration is kept for every later call on this
@@ -488,9 +490,12 @@ int xeng_tuning_lookup(const xeng_job *jobs, int32_t n_jobs, xeng_tuning *out);
  * buf (nothing if len is 0) and returns the path's full length;
  * XENG_ENOTSUP if none of the three variables is set, XENG_EDEVICE for a
  * device that does not exist.  The file holds one JSON object: the
- * architecture, and one entry per job class (N, T class, jobs class, DMA
- * eligibility) with the chosen kernel, workgroups per CU, minimum piece
- * length, work order and measured microseconds per launch.  Processes that
+ * architecture, the format's number, and one entry per job class (N, T class,
+ * jobs class, DMA eligibility) with the chosen kernel, the DMA kernel among
+ * those of XENG_KERNEL_AUTO, workgroups per CU, minimum piece length, work
+ * order and measured microseconds per launch.  A file of the older format,
+ * whose entries do not say which DMA kernel was measured, is not read; the
+ * next xeng_autotune replaces it.  Processes that
  * tune at the same time each write the whole file; the last write wins.
  */
 int32_t xeng_tune_cache_path(int32_t device, char *buf, int32_t len);

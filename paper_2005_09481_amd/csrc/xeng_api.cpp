@@ -110,6 +110,7 @@ Plan build_plan(const PlanJob *jobs, int n_jobs, int max_wgs, int min_stages, Ti
 // autotuner found best for calls of the same job sizes.
 struct Tuning {
     int kernel;       // XENG_KERNEL_*
+    TileShape shape;  // XENG_KERNEL_AUTO: the DMA kernel measured fastest, or Square: the modelled one
     int wgs_per_cu;   // general kernel
     int min_stages;
     int order;        // XENG_PLAN_* of single-job launches
@@ -119,8 +120,8 @@ struct Tuning {
 
 Tuning global_tuning()
 {
-    return Tuning{g_kernel.load(), g_wgs_per_cu.load(), g_min_stages.load(), g_plan_order.load(), XENG_TUNE_SETTINGS,
-                  0.0};
+    return Tuning{g_kernel.load(),     TileShape::Square,   g_wgs_per_cu.load(), g_min_stages.load(),
+                  g_plan_order.load(), XENG_TUNE_SETTINGS, 0.0};
 }
 
 // Waves per workgroup of the DMA kernel instance a configuration launches.
@@ -259,10 +260,28 @@ std::string tune_cache_path(const std::string &arch)
 }
 
 // One entry per line, so that the reader needs no JSON parser: the library
-// writes every line in exactly this form.
+// writes every line in exactly this form.  The format's number is part of the
+// first line.  Files of format 1 hold no "shape": what "kernel" 0 stood for in
+// them depends on the library that measured it, and their other kernels were
+// measured against it, so they are not read.
+constexpr const char *TUNE_HEAD = "{\"arch\": \"%s\", \"format\": 2,";
 constexpr const char *TUNE_LINE =
-    "  {\"n\": %d, \"t_class\": %d, \"jobs_class\": %d, \"dma\": %d, \"kernel\": %d, \"wgs_per_cu\": %d, "
-    "\"min_stages\": %d, \"plan_order\": %d, \"us_per_launch\": %lf}";
+    "  {\"n\": %d, \"t_class\": %d, \"jobs_class\": %d, \"dma\": %d, \"kernel\": %d, \"shape\": %d, "
+    "\"wgs_per_cu\": %d, \"min_stages\": %d, \"plan_order\": %d, \"us_per_launch\": %lf}";
+
+std::string tune_head(const std::string &arch)
+{
+    char b[160];
+    std::snprintf(b, sizeof b, TUNE_HEAD, arch.c_str());
+    return b;
+}
+
+// The DMA kernel an entry may name (0: none).
+bool tune_shape_ok(int kernel, int shape)
+{
+    return shape == 0 || (kernel == XENG_KERNEL_AUTO &&
+                          (shape == (int)TileShape::Wide || shape == (int)TileShape::Tile || shape == (int)TileShape::Region));
+}
 
 // The entries of the cache file at `path` written for `arch` (none if there
 // is no such file); lines that do not parse or hold values out of range are
@@ -275,7 +294,7 @@ void read_tune_file(const std::string &path, const std::string &arch,
     if (!f) return;
     char line[512];
     bool arch_ok = false;
-    const std::string head = "{\"arch\": \"" + arch + "\",";
+    const std::string head = tune_head(arch);
     while (std::fgets(line, sizeof line, f)) {
         if (std::strncmp(line, head.c_str(), head.size()) == 0) {
             arch_ok = true;
@@ -284,15 +303,18 @@ void read_tune_file(const std::string &path, const std::string &arch,
         if (!arch_ok) continue;
         TuneClass c;
         Tuning tu{};
+        int shape = 0;
         double us = 0.0;
-        if (std::sscanf(line, TUNE_LINE, &c.n, &c.t_class, &c.jobs_class, &c.dma, &tu.kernel, &tu.wgs_per_cu,
-                        &tu.min_stages, &tu.order, &us) != 9)
+        if (std::sscanf(line, TUNE_LINE, &c.n, &c.t_class, &c.jobs_class, &c.dma, &tu.kernel, &shape, &tu.wgs_per_cu,
+                        &tu.min_stages, &tu.order, &us) != 10)
             continue;
         if (c.n < 1 || c.t_class < 0 || c.t_class > 62 || c.jobs_class < 0 || c.jobs_class > 31 ||
             (c.dma != 0 && c.dma != 1) || tu.kernel < XENG_KERNEL_AUTO || tu.kernel > XENG_KERNEL_DMA4 ||
             tu.wgs_per_cu < 1 || tu.wgs_per_cu > 2 || tu.min_stages < 1 || tu.min_stages > (1 << 20) ||
-            (tu.order != XENG_PLAN_LINEAR && tu.order != XENG_PLAN_XCD) || !(us >= 0.0))
+            (tu.order != XENG_PLAN_LINEAR && tu.order != XENG_PLAN_XCD) || !tune_shape_ok(tu.kernel, shape) ||
+            !(us >= 0.0))
             continue;
+        tu.shape = (TileShape)shape;
         tu.source = XENG_TUNE_CACHE_FILE;
         tu.us = us;
         (*out)[c.key()] = DeviceState::Tuned{c, tu};
@@ -333,13 +355,13 @@ bool save_tune_cache(DeviceState *st)
     const std::string tmp = path + ".tmp." + std::to_string((long)getpid());
     FILE *f = std::fopen(tmp.c_str(), "w");
     if (!f) return false;
-    std::fprintf(f, "{\"arch\": \"%s\", \"format\": 1, \"entries\": [\n", arch.c_str());
+    std::fprintf(f, "%s \"entries\": [\n", tune_head(arch).c_str());
     size_t k = 0;
     for (const auto &kv : all) {
         const TuneClass &c = kv.second.cls;
         const Tuning &tu = kv.second.tu;
-        std::fprintf(f, TUNE_LINE, c.n, c.t_class, c.jobs_class, c.dma, tu.kernel, tu.wgs_per_cu, tu.min_stages,
-                     tu.order, tu.us);
+        std::fprintf(f, TUNE_LINE, c.n, c.t_class, c.jobs_class, c.dma, tu.kernel, (int)tu.shape, tu.wgs_per_cu,
+                     tu.min_stages, tu.order, tu.us);
         std::fprintf(f, "%s\n", ++k < all.size() ? "," : "");
     }
     std::fprintf(f, "]}\n");
@@ -702,7 +724,7 @@ struct Choice {
 Choice dma_choice(const DeviceState *st, const PlanJob &pj, const Tuning &tu)
 {
     if (tu.kernel != XENG_KERNEL_AUTO) return Choice{Kind::Wide, 0};
-    const DmaChoice c = choose_dma(pj.n, pj.t, st->cu_count, std::max(1, tu.min_stages));
+    const DmaChoice c = choose_dma(pj.n, pj.t, st->cu_count, std::max(1, tu.min_stages), tu.shape);
     return Choice{kind_of_shape(c.shape), c.wgs};
 }
 
@@ -968,7 +990,9 @@ std::vector<Part> split_by_kernel(const JobList &jl, const Tuning &tu)
         dma.kind = ch.kind;
         dma.wgs = ch.wgs;
     } else if (!dma.pj.empty() && tu.kernel == XENG_KERNEL_AUTO) {
-        dma.kind = kind_of_shape(choose_dma_batch(dma.pj.data(), (int)dma.pj.size(), jl.st->cu_count));
+        dma.kind = kind_of_shape(tu.shape != TileShape::Square
+                                     ? tu.shape
+                                     : choose_dma_batch(dma.pj.data(), (int)dma.pj.size(), jl.st->cu_count));
     }
     for (Part &p : by_kind) {
         int64_t bytes = 0;
@@ -1964,14 +1988,24 @@ int xeng_autotune(const xeng_job *jobs, int32_t n_jobs, int32_t iters, void *hip
 
     const bool any_dma = any_dma_job(jl);
     const bool single = jl.descs.size() == 1;
+    // the DMA kernels, each by itself (the narrow kernel has no choice)
+    bool wide_job = false;
+    for (const JobDesc &jd : jl.descs) wide_job = wide_job || ((jd.flags & JOB_DMA) && jd.n > NARROW_MAX_N);
+    const std::vector<TileShape> shapes = wide_job
+                                              ? std::vector<TileShape>{TileShape::Wide, TileShape::Tile, TileShape::Region}
+                                              : std::vector<TileShape>{TileShape::Square};
     std::vector<Tuning> cands;
     for (int ms : {1, 4, 16, 64})
         for (int order : {XENG_PLAN_XCD, XENG_PLAN_LINEAR}) {
             if (!single && order == XENG_PLAN_XCD) continue;   // batches always take the linear order
-            if (any_dma)
-                for (int kern : {XENG_KERNEL_AUTO, XENG_KERNEL_DMA4})
-                    cands.push_back(Tuning{kern, 2, ms, order, XENG_TUNE_MEASURED, 0.0});
-            for (int w : {1, 2}) cands.push_back(Tuning{XENG_KERNEL_GENERAL, w, ms, order, XENG_TUNE_MEASURED, 0.0});
+            auto add = [&](int kernel, TileShape shape, int wgs) {
+                cands.push_back(Tuning{kernel, shape, wgs, ms, order, XENG_TUNE_MEASURED, 0.0});
+            };
+            if (any_dma) {
+                for (TileShape shape : shapes) add(XENG_KERNEL_AUTO, shape, 2);
+                add(XENG_KERNEL_DMA4, TileShape::Square, 2);
+            }
+            for (int w : {1, 2}) add(XENG_KERNEL_GENERAL, TileShape::Square, w);
         }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     e = hipEventCreate(&e0);

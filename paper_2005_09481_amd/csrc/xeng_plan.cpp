@@ -430,7 +430,7 @@ bool whole_units(const ShapeCost &c, int64_t units, int64_t longest, int64_t sta
 
 }  // namespace
 
-DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages)
+DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages, TileShape only)
 {
     const int64_t ns = std::max<int64_t>(1, (t + STAGE - 1) / STAGE);
     DmaChoice best{TileShape::Wide, 0};
@@ -442,6 +442,7 @@ DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages)
         }
     };
     for (const ShapeCost &c : SHAPE_COSTS) {
+        if (only != TileShape::Square && c.shape != only) continue;
         const int64_t units = shape_units(n, c.shape);
         const double s = (double)units * (double)ns / cus, per_cu = (double)units / cus;
         if (units > cus) {

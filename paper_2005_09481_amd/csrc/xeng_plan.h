@@ -98,7 +98,8 @@ struct DmaChoice {
     TileShape shape;
     int wgs;
 };
-DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages);
+// `only`, unless Square: the best split of that shape alone.
+DmaChoice choose_dma(int32_t n, int64_t t, int cus, int min_stages, TileShape only = TileShape::Square);
 
 // The same choice for the jobs of a batch that one DMA launch takes, planned
 // over every compute unit: the modelled time of the planner's two regimes,

@@ -208,3 +208,72 @@ assert form(one(1), b"vis_dumpILb1E") == 1
 small = create(64)
 assert form(lambda: L.xeng_dump(small, 0, P, 1, None), b"vis_dumpILb0E") == 0
 """)
+
+
+FORMAT2 = ('{"arch": "gfx950", "format": %d, "entries": [\n'
+           '  {"n": 512, "t_class": 10, "jobs_class": 0, "dma": 1, "kernel": %d, %s"wgs_per_cu": 2, "min_stages": 4, '
+           '"plan_order": 1, "us_per_launch": 1.000000}\n]}\n')
+
+
+def tune_file(tmp_path, *args):
+    (tmp_path / "xeng_tune_gfx950.json").write_text(FORMAT2 % args)
+
+
+LOOKUP = r"""
+c = create(512)
+def lookup(t):
+    out = X._Tuning()
+    assert L.xeng_tuning_lookup(*jobs((c, 0, t, 512))[:2], ctypes.byref(out)) == 0
+    return out.kernel, out.source
+def launched(t, batch=False):
+    F.fake_clear()
+    if batch:
+        assert L.xeng_correlate_batch(*jobs((c, 0, t, 512))) == 0
+    else:
+        assert L.xeng_correlate(c, 0, P, t, 512, None) == 0
+    return [k for k in ("xcorr_dmaILi8", "xcorr_dmaILi4", "xcorr_tile", "xcorr_region", "xcorr_mfma")
+            if F.fake_launches(k.encode())]
+"""
+
+
+@pytest.mark.parametrize("fast", ["xcorr_dmaILi8", "xcorr_dmaILi4", "xcorr_tile", "xcorr_region", "xcorr_mfma"])
+def test_autotuner_times_every_kernel_and_keeps_the_fastest(run, fast):
+    # every DMA kernel is a candidate by itself, and the one measured fastest
+    # is what later calls of the class launch, here and in a new process
+    kernel = {"xcorr_dmaILi4": "DMA4", "xcorr_mfma": "GENERAL"}.get(fast, "AUTO")
+    run(LOOKUP + r"""
+F.fake_fast_kernel(b"%s")
+best = X._Tuning()
+F.fake_clear()
+assert L.xeng_autotune(*jobs((c, 0, 2000, 512))[:2], 1, None, ctypes.byref(best)) == 0
+for k in (b"xcorr_dmaILi8", b"xcorr_dmaILi4", b"xcorr_tile", b"xcorr_region", b"xcorr_mfma"):
+    assert F.fake_launches(k) > 0, k
+assert best.kernel == X.XENG_KERNEL_%s and best.saved == 1 and best.us_per_launch == 500.0
+assert lookup(1500) == (best.kernel, X.XENG_TUNE_MEASURED)
+assert launched(1500) == ["%s"] and launched(1500, True) == ["%s"]
+assert launched(9000) == ["xcorr_region"]          # another class: the modelled kernel
+""" % (fast, kernel, fast, fast))
+    run(LOOKUP + r"""
+assert lookup(1500) == (X.XENG_KERNEL_%s, X.XENG_TUNE_CACHE_FILE)
+assert launched(1500) == ["%s"] and launched(1500, True) == ["%s"]
+""" % (kernel, fast, fast))
+
+
+def test_tune_files_of_the_older_format_are_not_read(run, tmp_path):
+    # their kernel 0 does not say which DMA kernel was measured
+    for args in ((1, 1, ""), (1, 0, ""), (1, 0, '"shape": 3, '), (2, 1, "")):
+        tune_file(tmp_path, *args)
+        run(LOOKUP + "assert lookup(1500) == (X.XENG_KERNEL_AUTO, X.XENG_TUNE_SETTINGS)\n"
+            "assert launched(1500) == ['xcorr_region']\n")
+
+
+@pytest.mark.parametrize("kernel,shape,ok", [(0, 0, "xcorr_region"), (0, 1, "xcorr_dmaILi8"), (0, 3, "xcorr_tile"),
+                                             (0, 4, "xcorr_region"), (1, 0, "xcorr_mfma"), (2, 0, "xcorr_dmaILi4"),
+                                             (0, 2, None), (0, 5, None), (0, -1, None), (1, 3, None), (2, 1, None),
+                                             (3, 0, None)])
+def test_tune_file_entries_name_their_kernel(run, tmp_path, kernel, shape, ok):
+    tune_file(tmp_path, 2, kernel, '"shape": %d, ' % shape)
+    if ok:
+        run(LOOKUP + "assert lookup(1500) == (%d, X.XENG_TUNE_CACHE_FILE) and launched(1500) == [%r]\n" % (kernel, ok))
+    else:
+        run(LOOKUP + "assert lookup(1500)[1] == X.XENG_TUNE_SETTINGS\n")
