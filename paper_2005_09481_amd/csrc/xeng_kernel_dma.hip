@@ -361,15 +361,6 @@ __device__ __forceinline__ void idle_piece(uint32_t ring, const Tile &tl, int wa
 template <int SHIFT> __device__ __forceinline__ int32_t acc_val(int32_t v) { return v >> SHIFT; }
 template <int SHIFT> __device__ __forceinline__ int32_t acc_val(float v) { return (int32_t)(v * 262144.0f); }
 
-// An accumulator register's bits, and back.
-__device__ __forceinline__ int as_int(int32_t v) { return v; }
-__device__ __forceinline__ int as_int(float v) { return __float_as_int(v); }
-template <bool F> __device__ __forceinline__ auto as_acc(int v)
-{
-    if constexpr (F) return __int_as_float(v);
-    else return v;
-}
-
 template <int SHIFT, typename V>
 __device__ __forceinline__ void flush_atomic(gw64 *blk, const V &re, const V &im)
 {
@@ -459,7 +450,8 @@ __device__ __forceinline__ void flush_owned(gw64 *tb, const Acc<L, F> &acc, int 
 // through LDS (`mine`, `other`: 16 KiB each of the ring, which the end of a
 // piece has left free), wave KEEP of the pair ending with the sums of both
 // over row block KEEP of the region.
-template <typename L, int KEEP, bool F> __device__ __forceinline__ void give_half(uint8_t *mine, const Acc<L, F> &acc, int lane)
+template <typename L, int KEEP>
+__device__ __forceinline__ void give_half(uint8_t *mine, const Acc<L, false> &acc, int lane)
 {
 #pragma unroll
     for (int b = 0; b < L::BW; ++b)
@@ -468,10 +460,11 @@ template <typename L, int KEEP, bool F> __device__ __forceinline__ void give_hal
             const auto &v = q < 4 ? acc.re[1 - KEEP][b] : acc.im[1 - KEEP][b];
             const int r = 4 * (q & 3);
             *reinterpret_cast<v4i *>(mine + ((b * 8 + q) * 64 + lane) * 16) =
-                v4i{as_int(v[r]), as_int(v[r + 1]), as_int(v[r + 2]), as_int(v[r + 3])};
+                v4i{v[r], v[r + 1], v[r + 2], v[r + 3]};
         }
 }
-template <typename L, int KEEP, bool F> __device__ __forceinline__ void take_half(const uint8_t *other, Acc<L, F> &acc, int lane)
+template <typename L, int KEEP>
+__device__ __forceinline__ void take_half(const uint8_t *other, Acc<L, false> &acc, int lane)
 {
 #pragma unroll
     for (int b = 0; b < L::BW; ++b)
@@ -481,7 +474,7 @@ template <typename L, int KEEP, bool F> __device__ __forceinline__ void take_hal
             auto &v = q < 4 ? acc.re[KEEP][b] : acc.im[KEEP][b];
             const int r = 4 * (q & 3);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[r + k] += as_acc<F>(w[k]);
+            for (int k = 0; k < 4; ++k) v[r + k] += w[k];
         }
 }
 
@@ -493,6 +486,7 @@ template <typename L, bool U, bool F>
 __device__ __forceinline__ void run_workgroup(const KernelArgs &args)
 {
     static_assert(U || !F, "the FP8 form multiplies the unsigned nibbles");
+    static_assert(L::TG == 1 || !U, "two time groups: the signed form only");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     // a prepared batch's device guard refused this launch
     if (args.skip != nullptr && *args.skip != 0) return;
@@ -628,13 +622,13 @@ __device__ __forceinline__ void run_workgroup(const KernelArgs &args)
             uint8_t *mine = lds + wave * 16384;
             const uint8_t *other = lds + ((wave + GW) % L::NW) * 16384;
             if (work) {
-                if (tg == 0) give_half<L, 0, F>(mine, acc, lane);
-                else give_half<L, 1, F>(mine, acc, lane);
+                if (tg == 0) give_half<L, 0>(mine, acc, lane);
+                else give_half<L, 1>(mine, acc, lane);
             }
             __syncthreads();
             if (work) {
-                if (tg == 0) take_half<L, 0, F>(other, acc, lane);
-                else take_half<L, 1, F>(other, acc, lane);
+                if (tg == 0) take_half<L, 0>(other, acc, lane);
+                else take_half<L, 1>(other, acc, lane);
             }
             __syncthreads();   // the next piece's DMA reuses the ring
             a0 = tg;
@@ -689,10 +683,9 @@ __global__ __launch_bounds__(64 * NW, 1) void xcorr_dma(KernelArgs args)
 }
 
 // The tile kernel: 128 x 128 tiles, each quarter's time split over two waves.
-template <bool U = false, bool F = false>
 __global__ __launch_bounds__(64 * TileLayout::NW, 1) void xcorr_tile(KernelArgs args)
 {
-    run_workgroup<TileLayout, U, F>(args);
+    run_workgroup<TileLayout, false, false>(args);
 }
 
 }  // namespace dma
@@ -720,7 +713,7 @@ hipError_t init_dma_kernel()
         e = hipFuncSetAttribute((const void *)dma::xcorr_dma<8, true, true>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, DMA_LDS_BYTES);
     if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)dma::xcorr_tile<>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        e = hipFuncSetAttribute((const void *)dma::xcorr_tile, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 dma::TileLayout::LDS_BYTES);
     return e;
 }
@@ -728,7 +721,7 @@ hipError_t init_dma_kernel()
 hipError_t launch_correlate_tile(const KernelArgs &a, int grid, hipStream_t stream)
 {
     if (grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(dma::xcorr_tile<>, dim3(grid), dim3(64 * dma::TileLayout::NW), dma::TileLayout::LDS_BYTES, stream, a);
+    hipLaunchKernelGGL(dma::xcorr_tile, dim3(grid), dim3(64 * dma::TileLayout::NW), dma::TileLayout::LDS_BYTES, stream, a);
     return hipGetLastError();
 }
 
