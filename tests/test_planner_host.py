@@ -180,3 +180,64 @@ def test_minimum_piece_length_limits_cuts_not_the_kernels(P):
 def test_batches_take_the_measured_kernel(P, jobs, n, t, shape):
     assert P.host_choose_batch((ctypes.c_int32 * jobs)(*[n] * jobs), (ctypes.c_int64 * jobs)(*[t] * jobs), jobs,
                                256) == shape
+
+
+def assert_covers_once(pieces, jobs, shape, wgs, cap=0, gaps=False):
+    """Every unit x sample of every job once, in runs of whole stages of at
+    most `cap` (by default the longest for which the kernel's int32 sums stay
+    exact); shared units, and only those, flushed with atomics; the workgroups
+    in order from 0, without gaps but in XCD plans (where some places on the
+    last XCD stay empty)."""
+    cap = cap or (16383 if shape == SQUARE else 1023)
+    runs = {}
+    for job, i, j, t0, t1, atomic, _ in pieces.tolist():
+        runs.setdefault((job, i, j), []).append((t0, t1, atomic))
+    assert set(runs) == {(k, i, j) for k, (n, t) in enumerate(jobs) if t > 0 for i, j in units_of(n, shape)}
+    for (job, _, _), r in runs.items():
+        r.sort()
+        assert [a for a, _, _ in r] + [jobs[job][1]] == [0] + [b for _, b, _ in r]
+        assert all(a % 64 == 0 and 0 < b - a <= 64 * cap for a, b, _ in r)
+        assert all(atomic == (len(r) > 1) for _, _, atomic in r)
+    assert np.all(np.diff(pieces[:, 6]) >= 0) and pieces[0, 6] >= 0 and pieces[-1, 6] < wgs
+    assert gaps or pieces[-1, 6] + 1 == len(set(pieces[:, 6].tolist()))
+
+
+SHAPES = [SQUARE, WIDE, NARROW, TILE, REGION]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("seed", range(6))
+def test_plans_cover_every_unit_once(P, shape, seed):
+    rng = np.random.default_rng(100 * seed + shape)
+    for _ in range(25):
+        # batches with empty jobs among them, on whole chips and on a few units
+        jobs = [(int(rng.integers(1, 65 if shape == NARROW else 1500)), int(rng.choice([0, 1, 63, 64, 65, rng.integers(1, 9000)])))
+                for _ in range(int(rng.integers(1, 7)))]
+        if not any(t for _, t in jobs):
+            continue
+        wgs, min_stages, cap = int(rng.choice([8, 240, 256, 512])), int(rng.choice([1, 4, 32])), int(rng.choice([0, 0, 5, 100]))
+        pieces = plan(P, jobs, wgs, shape, min_stages, cap=cap)
+        assert_covers_once(pieces, jobs, shape, wgs, cap)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_long_jobs_stay_below_the_piece_limit(P, shape):
+    # one unit's samples past the longest piece, on one workgroup and on all
+    for t in (64 * 1023, 64 * 1023 + 1, 64 * 3000 - 7):
+        for wgs in (1, 256):
+            assert_covers_once(plan(P, [(64, t)], wgs, shape), [(64, t)], shape, wgs)
+
+
+@pytest.mark.parametrize("shape", [SQUARE, WIDE, TILE, REGION])
+@pytest.mark.parametrize("seed", range(4))
+def test_xcd_plans_cover_every_unit_once(P, shape, seed):
+    rng = np.random.default_rng(1000 + 10 * seed + shape)
+    found = 0
+    for _ in range(40):
+        job = (int(rng.integers(65, 3000)), int(rng.integers(2000, 70000)))
+        wgs, cap = int(rng.choice([64, 240, 256, 512])), int(rng.choice([0, 0, 200]))
+        pieces = plan(P, [job], wgs, shape, xcd=True, cap=cap)
+        if pieces is not None:
+            found += 1
+            assert_covers_once(pieces, [job], shape, wgs, cap, gaps=True)
+    assert found
