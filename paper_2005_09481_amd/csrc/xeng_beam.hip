@@ -261,7 +261,7 @@ hipError_t launch_waves(const uint8_t *s, int64_t n_samples, int n, int64_t stri
     return hipGetLastError();
 }
 
-// Enough rows for eight waves of 16 on every compute unit (T from 96 per
+// Enough rows for six waves of 16 on every compute unit (T from 96 per
 // unit up): each wave its own rows, two pairs of k-steps ahead -- N = 2048, T =
 // 32768: 13.8 us (eight pairs ahead 17.0, rows shared by two waves 15.6).
 // Fewer: two waves per row block, four pairs ahead, and below 32 rows per

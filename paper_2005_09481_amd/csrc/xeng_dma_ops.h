@@ -1,5 +1,5 @@
 // Device code shared by the kernels that stage packed samples by LDS DMA
-// (the wide kernel and the region kernel): LDS DMA, transposed LDS reads, the
+// (the wide, tile and region kernels): LDS DMA, transposed LDS reads, the
 // nibble unpack and the MFMAs of a k-step.  `L` is the kernel's shape: it
 // gives PITCH_A, PITCH_B (bytes per time row of its A and B sides in LDS),
 // BW (B blocks per wave) and the instruction mix of a k-step.
@@ -66,7 +66,7 @@ __device__ __forceinline__ void dma16_v(const uint8_t *addr, uint32_t lds_addr)
 }
 
 // Scalar-base form, wave-uniform 64-bit base + per-lane 32-bit offsets: a
-// whole stage's share of DMAs (K = 6 or 3) in one statement:
+// whole stage's share of DMAs (K of them) in one statement:
 // M0 saved once, one s_nop 4 ahead of the first instruction (covering a
 // VALU write of any SGPR operand, which the statement's own instructions
 // never make), and between instructions only the one wait state an SALU

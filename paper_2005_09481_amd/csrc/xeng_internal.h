@@ -71,7 +71,6 @@ constexpr int MAX_PIECE_STAGES_UNSIGNED = ((1 << 19) - 1) / STAGE;   // 8191 sta
 // 450 per sample stay exact integers below 2^24 over 582 stages.
 constexpr int MAX_PIECE_STAGES_FP8_UNSIGNED = ((1 << 24) - 1) / (450 * STAGE);   // 582 stages
 
-// Largest row stride: lane offsets inside a stage (up to 31 rows) stay 32-bit.
 // Most workgroups one tile is shared among in a launch.  Every share of a
 // tile flushes all of it with atomics, and shares of one tile end together,
 // so their atomics meet on the same addresses: past about 16 shares the
@@ -79,7 +78,10 @@ constexpr int MAX_PIECE_STAGES_FP8_UNSIGNED = ((1 << 24) - 1) / (450 * STAGE);  
 // 512 with T of 4096 and 8192).
 constexpr int64_t MAX_UNIT_SPLIT = 16;
 
+// Largest row stride: lane offsets inside a stage (its rows 0 to 63) stay
+// 32-bit.
 constexpr int64_t MAX_STRIDE = INT64_C(1) << 26;
+static_assert((STAGE - 1) * MAX_STRIDE + 65535 < INT64_C(1) << 32, "a lane's offset from a stage's first row");
 
 // Largest number of samples a slot may integrate: the largest |term| of
 // x_i conj(x_j) with parts in [-8, 7] is 128 (Re), so 128 * T_MAX <= 2^31-1.
