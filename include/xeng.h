@@ -109,7 +109,8 @@ int xeng_destroy(xeng_ctx *ctx);
  * Samples whose base and row stride are multiples of 16 bytes with N a
  * multiple of 16 are read in place; otherwise, for N >= 256, the call first
  * copies them (in chunks of at most 256 MiB) into rows of N rounded up to
- * 16 bytes, in stream-ordered scratch from a pool the library keeps per
+ * whole 128-byte lines, or to 16 bytes where lines would take more chunks,
+ * in stream-ordered scratch from a pool the library keeps per
  * device (up to 1 GiB retained), and correlates the copy; XENG_ENOMEM if
  * that scratch cannot be had (nothing queued).  A device error in a later
  * chunk leaves the chunks already queued integrated and counted in
@@ -128,8 +129,8 @@ int xeng_correlate(xeng_ctx *ctx, int32_t slot, const uint8_t *d_samples,
  * each GPU holds from the library's set-up until the process ends.  Every
  * call on a GPU shares that array (and each call overwrites it), so calls
  * that may overlap on one GPU -- on different streams, from different
- * threads -- race; calls ordered on one stream do not.  Samples the wide
- * kernel cannot read in place take the 128 x 128 kernel directly.
+ * threads -- race; calls ordered on one stream do not.  Samples the DMA
+ * kernels cannot read in place take the 128 x 128 kernel directly.
  * XENG_ENOMEM, nothing queued, if the plan would not fit the array (about
  * 65000 pieces: N = 2048 fits at any T up to xeng_max_integration()).
  * XENG_ENOTSUP while hip_stream is capturing, like xeng_correlate.
@@ -214,7 +215,7 @@ int xeng_dump_counts(xeng_ctx *ctx, int32_t slot, int32_t *out, void *hip_stream
  * integers on the GPU: the wide kernel's unsigned instance where the array
  * allows it in place (int8, or FP8 under XENG_KERNEL_FP8), else the
  * 128 x 128 kernel's (int8), which XENG_KERNEL_GENERAL also selects.  The
- * per-slot pre-sums (8 N bytes) are allocated with the context.
+ * per-slot pre-sums (two buffers of 8 N bytes) are allocated with the context.
  */
 int xeng_correlate_presum(xeng_ctx *ctx, int32_t slot, const uint8_t *d_samples, int64_t n_samples,
                           int64_t row_stride, void *hip_stream);
@@ -273,10 +274,11 @@ typedef struct {
  * (recurring job sizes are planned once; the plans are kept on the host) to
  * the device on hip_stream through a pinned staging ring, and never
  * synchronizes the device, so that a loop of calls with changing sizes
- * keeps the GPU busy.  Jobs with N >= 256 that the wide kernel cannot read
+ * keeps the GPU busy.  Jobs with N >= 256 that the DMA kernels cannot read
  * in place (see xeng_correlate) are copied into padded rows in scratch from
- * the library's pool first, up to 256 MiB of them per call; the rest run
- * the 128 x 128 kernel.  For graph capture use xeng_batch_* below (which
+ * the library's pool first, up to 256 MiB of them per call (counted in rows
+ * of N rounded up to 16 bytes; whole lines where there is room left); the
+ * rest run the 128 x 128 kernel.  For graph capture use xeng_batch_* below (which
  * reads every job in place).
  */
 int xeng_correlate_batch(const xeng_job *jobs, int32_t n_jobs, void *hip_stream);
@@ -682,8 +684,8 @@ int xeng_set_pad_chunk_bytes(int64_t bytes);
 /*
  * Clock probe, for measurement (results never depend on it).  `dev_buf` is
  * device memory on `device` of at least 4 int64, or NULL to stop.  While
- * set, every launch of the wide (DMA) correlation kernel on that device
- * stores, from its workgroup 0, the shader-clock cycle counter and the
+ * set, every launch of a DMA correlation kernel (wide, tile or region) on
+ * that device stores, from its workgroup 0, the shader-clock cycle counter and the
  * 100 MHz real-time counter at the workgroup's start ([0], [1]) and end
  * ([2], [3]); the caller derives the shader clock the launch ran at as
  * ([2] - [0]) / (([3] - [1]) / 1e8).  The buffer stays the caller's and must

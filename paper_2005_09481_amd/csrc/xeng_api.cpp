@@ -564,7 +564,7 @@ struct xeng_ctx {
     uint32_t flags = 0;
     int32_t nt = 0;
     int64_t slot_i32 = 0;
-    int32_t *d_acc = nullptr;    // n_slots accumulators, then n_slots bias arrays
+    int32_t *d_acc = nullptr;    // n_slots accumulators (bias bases in their diagonal tiles), then n_slots bias arrays
     int32_t *d_bias = nullptr;   // per slot bias_i32(N): see JobDesc::bias
     // per slot, which of its two bases (BASE_I32) holds the biases as of its
     // last reset; a resetting export reads it and stores the present biases
@@ -751,8 +751,8 @@ hipError_t launch(const KernelArgs &a, int32_t grid, Kind kind, int waves, uint3
 // A single-channel call the DMA kernel cannot read in place (N not a
 // multiple of 16, or a base or stride not a multiple of 16 bytes) with N of
 // at least PAD_MIN_N: the samples are copied, in chunks of time rows, into
-// stream-ordered scratch with rows of N rounded up to 16 bytes padded with
-// zero samples, and each chunk is correlated from there by the DMA kernel
+// stream-ordered scratch with rows padded with zero samples (see pad_pitch),
+// and each chunk is correlated from there by the DMA kernel
 // (about twice the general kernel's rate for a copy that moves each sample
 // twice).  Below PAD_MIN_N the general kernel's 128 x 128 tiles waste less.
 constexpr int PAD_MIN_N = 256;
